@@ -387,7 +387,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
                                  (double)bn * (bm / wm) * conflict_ways(v, hw, bk, 1, vn) + (bm + bn)) / lds_bw;
   const double l2_bw = hw.l2_bandwidth_gbs * 1e3 / hw.compute_units;
   const double gather = (v.bsrc == B_CONV && !direct) ? 16.0 : 1.0;     // element-wise loads and their index arithmetic
-  const double scalar = vec ? 1.0 : 6.0;
+  // operands off the vector boundaries: the same loads, each spread over two cache lines; the gather's filters, too, but
+  // there the gather's own element loads set the pace
+  const double scalar = vec ? 1.0 : (v.bsrc == B_CONV ? 6.0 : 2.0);
   const double t_feed = scalar * e * kp * (bm + gather * bn) / l2_bw;
   double par = resident * nwaves / hw.simds_per_cu;
   if (par > 4.0) par = 4.0;

@@ -11,7 +11,8 @@
 //              V = 1 is the plain layout, whose fragment reads conflict ceil(x / W) ways
 //   STAGES     LDS buffers (1: single buffer, 2: double buffer, 3 and more: a ring that keeps STAGES-1
 //              k tiles in flight; direct staging only)
-//   VEC        global accesses are 16-byte vectors (true) or single elements (false)
+//   VEC        operands start every row on a 16-byte boundary and rows are whole vectors (true), or lie
+//              anywhere on element boundaries with any extents (false)
 //   DIRECT     K-contiguous operands go global->LDS without passing through registers
 //
 // Operand sources.  A (the m x k operand) is k-contiguous, A[m][k] (A_KC), or m-contiguous, A stored
@@ -212,7 +213,7 @@ struct Cfg {
   static_assert(!DIRECT || (VEC && (BSRC == B_KC || (BSRC == B_NC && BN * ES / 16 >= 16))),
                 "direct-to-LDS needs vector loads; an n-contiguous B needs rows of at least 16 chunks for its swizzle");
   static_assert(!NC_DIRECT || (B_CHUNKS % THREADS == 0), "direct staging deposits whole waves");
-  static_assert(BSRC != B_NCS2 || VEC, "the sampled source exists only with vector loads");
+  static_assert(BSRC != B_NCS2 || VEC, "the sampled source exists only with aligned vector loads");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS capacity");
   static_assert(STAGES <= 2 || (DIRECT && VEC && (BSRC == B_KC || BSRC == B_NC) && KSTEPS % 2 == 0),
                 "rings of three and more stages are filled by direct loads");
@@ -318,6 +319,13 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   const int cols_valid = min(BN, args.N - n0);
   const char* a_tile = (C::ASRC == A_KC) ? Ab + (int64_t)m0 * args.lda * ES : Ab + (int64_t)m0 * ES;
   const char* b_tile = (C::BSRC == B_KC) ? Bb + (int64_t)n0 * args.ldb * ES : (C::BSRC == B_NCS2 ? Bb : Bb + (int64_t)n0 * ES);
+  // Operands without VEC start anywhere: the descriptor begins at the 16-byte granule that holds the tile's first
+  // element (`skew` bytes before it) and ends on a dword boundary, so that it covers every dword that holds an
+  // element; a granule or dword that holds one lies in the element's own page.
+  auto loose_rsrc = [&](const char* first, int64_t bytes, uint32_t& skew) {
+    skew = (uint32_t)((uintptr_t)first & 15u);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(first - skew), 0, bytes <= 0 ? 0u : clamp_records((bytes + skew + 3) & ~3ll), RSRC_FLAGS);
+  };
   auto rsrc_a = [&](int k0) {
     if constexpr (C::ASRC == A_KC)
       return __builtin_amdgcn_make_buffer_rsrc((void*)(a_tile + (int64_t)k0 * ES), 0,
@@ -342,8 +350,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   // k-contiguous tile (slot q = row q/CPR, physical chunk q%CPR) and fetches the logical
   // chunk that the swizzle maps there; the same ownership serves the register-staged and
   // the direct path (a direct load deposits lane l's 16 bytes at slot base + l).
-  constexpr bool SCALAR_A = !C::VEC;
-  constexpr bool SCALAR_B = !C::VEC || C::BSRC == B_CONV;
+  constexpr bool LOOSE_A = !C::VEC;
+  constexpr bool GATHER_B = C::BSRC == B_CONV;
+  constexpr bool LOOSE_B = !C::VEC && !GATHER_B;
   uint32_t a_voff[C::A_LOADS], a_kch[C::A_LOADS];
 #pragma unroll
   for (int i = 0; i < C::A_LOADS; ++i) {
@@ -392,31 +401,63 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   u32x4 ra[C::DIRECT ? 1 : C::A_LOADS];
   u32x4 rb[C::DIRECT ? 1 : C::B_LOADS * (C::BSRC == B_NCS2 ? 2 : 1)];
 
-  // element-wise access for the scalar path and the convolution gather
-  auto a_elem_bits = [&](int row, int k) -> uint32_t {
-    if (row < args.M && k < Kx) {
-      int64_t idx = (C::ASRC == A_KC) ? (int64_t)row * args.lda + k : (int64_t)k * args.lda + row;
-      if constexpr (ES == 4) return ((const uint32_t*)Ab)[idx];
-      else return ((const uint16_t*)Ab)[idx];
-    }
-    return 0u;
-  };
+  // element-wise access of the convolution gather
   auto b_elem_bits = [&](int k, int col) -> uint32_t {
     if (col >= args.N || k >= Kx) return 0u;
-    int64_t idx;
-    if constexpr (C::BSRC == B_KC) idx = (int64_t)col * args.ldb + k;
-    else if constexpr (C::BSRC == B_NC) idx = (int64_t)k * args.ldb + col;
-    else {
-      const int rs = args.cR * args.cS;
-      const int c = k / rs, rr = (k - c * rs) / args.cS, ss = k - c * rs - rr * args.cS;
-      const int pq = args.cP * args.cQ;
-      const int img = col / pq, p = (col - img * pq) / args.cQ, q = col - img * pq - p * args.cQ;
-      const int y = p * args.cStride - args.cPad + rr, x = q * args.cStride - args.cPad + ss;
-      if (y < 0 || y >= args.cH || x < 0 || x >= args.cW) return 0u;
-      idx = (((int64_t)img * args.cC + c) * args.cH + y) * args.cW + x;
-    }
+    const int rs = args.cR * args.cS;
+    const int c = k / rs, rr = (k - c * rs) / args.cS, ss = k - c * rs - rr * args.cS;
+    const int pq = args.cP * args.cQ;
+    const int img = col / pq, p = (col - img * pq) / args.cQ, q = col - img * pq - p * args.cQ;
+    const int y = p * args.cStride - args.cPad + rr, x = q * args.cStride - args.cPad + ss;
+    if (y < 0 || y >= args.cH || x < 0 || x >= args.cW) return 0u;
+    const int64_t idx = (((int64_t)img * args.cC + c) * args.cH + y) * args.cW + x;
     if constexpr (ES == 4) return ((const uint32_t*)Bb)[idx];
     else return ((const uint16_t*)Bb)[idx];
+  };
+  // Operands that lie anywhere on element boundaries are fetched with the same 16-byte loads, at whatever address
+  // a chunk starts (the memory path takes any).  `inner` says that no chunk of the tile holds an element beyond K and
+  // none that is needed runs past the operand's last element: then that is all (rows and columns beyond the matrix
+  // read other elements or zero and are never stored).  Otherwise, in the last one or two k tiles, a chunk is
+  // fetched as the five aligned dwords around it -- the range check drops whole dwords, so the last element would
+  // be lost to a dword that straddles the end -- shifted into place, and its elements beyond K are cleared (both
+  // operands': a stray infinity times zero is not zero).
+  // Element loads, two bytes a lane, were what bounded these instances: 2039 x 1511 x 1003 in bf16 took 100 us.
+  auto fetch_loose = [&](const char* first, int64_t bytes, bool inner, int k_left, const uint32_t* voff, const uint32_t* kch, u32x4* regs,
+                         auto k_contiguous_tag, auto chunks_tag) {
+    constexpr bool k_contiguous = decltype(k_contiguous_tag)::value;
+    constexpr int CHUNKS = decltype(chunks_tag)::value, LOADS = (CHUNKS + C::THREADS - 1) / C::THREADS;
+    uint32_t skew;
+    const __amdgpu_buffer_rsrc_t r = loose_rsrc(first, bytes, skew);
+    if (inner) {
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i) {
+        if (CHUNKS % C::THREADS != 0 && tid + i * C::THREADS >= CHUNKS) break;
+        regs[i] = __builtin_amdgcn_raw_buffer_load_b128(r, voff[i] + skew, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i) {
+        if (CHUNKS % C::THREADS != 0 && tid + i * C::THREADS >= CHUNKS) break;
+        const int left = k_left - (int)kch[i];             // k left from this chunk's first (or only) k
+        const uint32_t off = left > 0 ? voff[i] + skew : OOB;
+        u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off & ~3u, 0, 0);
+        if constexpr (ES == 2) {
+          const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(r, (off & ~3u) + 16u, 0, 0);
+          const uint32_t half = off & 2u;
+          const uint32_t d[5] = {v[0], v[1], v[2], v[3], w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_alignbyte(d[e + 1], d[e], half);
+        }
+        if constexpr (k_contiguous) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (ES == 4) v[e] = left > e ? v[e] : 0u;
+            else v[e] &= left > 2 * e + 1 ? 0xffffffffu : (left > 2 * e ? 0xffffu : 0u);
+          }
+        }
+        regs[i] = v;
+      }
+    }
   };
   auto pack_chunk = [&](auto&& elem) -> u32x4 {   // elem(e) for e in [0, EPC)
     u32x4 v;
@@ -435,19 +476,13 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   // sent out of range; this can only happen in the last k tile.
   auto fetch_a = [&](int k0, int st, int part = 0, int parts = 1) {
     const bool full = Kx - k0 >= BK;
-    if constexpr (SCALAR_A) {
-#pragma unroll
-      for (int i = 0; i < C::A_LOADS; ++i) {
-        const int q = tid + i * C::THREADS;
-        if (C::A_CHUNKS % C::THREADS != 0 && q >= C::A_CHUNKS) break;
-        if constexpr (C::ASRC == A_KC) {
-          const int row = q / C::CPR, ch = swizzled_chunk(row, q % C::CPR, C::RPP, C::VM);
-          ra[i] = pack_chunk([&](int e) { return a_elem_bits(m0 + row, k0 + ch * EPC + e); });
-        } else {
-          constexpr int CPRM = BM * ES / 16;
-          ra[i] = pack_chunk([&](int e) { return a_elem_bits(m0 + (q % CPRM) * EPC + e, k0 + q / CPRM); });
-        }
-      }
+    if constexpr (LOOSE_A) {
+      if constexpr (C::ASRC == A_KC)
+        fetch_loose(a_tile + (int64_t)k0 * ES, ((int64_t)(rows_valid - 1) * args.lda + (Kx - k0)) * ES, full, Kx - k0,
+                    a_voff, a_kch, ra, std::true_type{}, std::integral_constant<int, C::A_CHUNKS>{});
+      else
+        fetch_loose(a_tile + (int64_t)k0 * args.lda * ES, ((int64_t)(Kx - k0 - 1) * args.lda + (args.M - m0)) * ES, Kx - k0 >= BK + EPC - 1, Kx - k0,
+                    a_voff, a_kch, ra, std::false_type{}, std::integral_constant<int, C::A_CHUNKS>{});
     } else {
       const __amdgpu_buffer_rsrc_t r = rsrc_a(k0);
 #pragma unroll
@@ -466,20 +501,22 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   };
   auto fetch_b = [&](int k0, int st, int part = 0, int parts = 1) {
     const bool full = Kx - k0 >= BK;
-    if constexpr (SCALAR_B) {
+    if constexpr (GATHER_B) {
 #pragma unroll
       for (int i = 0; i < C::B_LOADS; ++i) {
         const int q = tid + i * C::THREADS;
         if (C::B_CHUNKS % C::THREADS != 0 && q >= C::B_CHUNKS) break;
-        if constexpr (C::BSRC == B_KC) {
-          const int row = q / C::CPR, ch = swizzled_chunk(row, q % C::CPR, C::RPP, C::VN);
-          rb[i] = pack_chunk([&](int e) { return b_elem_bits(k0 + ch * EPC + e, n0 + row); });
-        } else {
-          constexpr int CPRN = BN * ES / 16;
-          const int krow = q / CPRN, ch = q % CPRN;
-          rb[i] = pack_chunk([&](int e) { return b_elem_bits(k0 + krow, n0 + ch * EPC + e); });
-        }
+        constexpr int CPRN = BN * ES / 16;
+        const int krow = q / CPRN, ch = q % CPRN;
+        rb[i] = pack_chunk([&](int e) { return b_elem_bits(k0 + krow, n0 + ch * EPC + e); });
       }
+    } else if constexpr (LOOSE_B) {
+      if constexpr (C::BSRC == B_KC)
+        fetch_loose(b_tile + (int64_t)k0 * ES, ((int64_t)(cols_valid - 1) * args.ldb + (Kx - k0)) * ES, full, Kx - k0,
+                    b_voff, b_kch, rb, std::true_type{}, std::integral_constant<int, C::B_CHUNKS>{});
+      else
+        fetch_loose(b_tile + (int64_t)k0 * args.ldb * ES, ((int64_t)(Kx - k0 - 1) * args.ldb + (args.N - n0)) * ES, Kx - k0 >= BK + EPC - 1, Kx - k0,
+                    b_voff, b_kch, rb, std::false_type{}, std::integral_constant<int, C::B_CHUNKS>{});
     } else {
       const __amdgpu_buffer_rsrc_t r = rsrc_b(k0);
 #pragma unroll

@@ -82,7 +82,7 @@ def lattice():
         for bsrc in ("KC", "NC", "CONV"):
             for (bm, bn, bk, wm, wn, mb, vm, vn) in tiles16:
                 out.append(_inst(dt, "f32", bm, bn, bk, wm, wn, mb, vm, vn, bsrc))
-            # scalar-access instance: any alignment, any extents
+            # any alignment, any extents
             out.append(_inst(dt, "f32", 64, 64, 32, 32, 32, 16, None, None, bsrc, vec=0))
         # pointwise convolution with stride 2: the n-contiguous B operand sampled while it is fetched
         for (bm, bn, bk, wm, wn, mb, vm, vn) in tiles16:
@@ -186,6 +186,15 @@ def lattice():
     for dt in ("f16", "bf16"):
         for (bm, bn) in ((128, 256), (256, 128)):
             out.append(_inst(dt, "f32", bm, bn, 64, 64, 64, 32, bsrc="NC", stages=3, direct=1))
+    # operands at any alignment and with any extents (vec = 0), register-staged: the tiles a large problem wants, beside
+    # the 64x64x32 ones above
+    for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+        for dt in ("f16", "bf16"):
+            for odt in ("f32", dt):
+                for (bm, bn, wm, wn) in ((128, 128, 64, 64), (128, 64, 64, 32), (64, 64, 32, 32)):
+                    out.append(_inst(dt, odt, bm, bn, 64, wm, wn, 32, bsrc=bsrc, vec=0, asrc=asrc))
+        for (bm, bn, wm, wn) in ((128, 128, 64, 64), (64, 64, 32, 32)):
+            out.append(_inst("f32", "f32", bm, bn, 32, wm, wn, 32, bsrc=bsrc, vec=0, asrc=asrc))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],

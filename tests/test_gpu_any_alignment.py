@@ -1,0 +1,67 @@
+"""Operands that start anywhere on an element boundary, with odd leading dimensions and extents: every GEMM instance
+that does not ask for aligned vectors, bit-exact on integers, with infinities stored in every element around the
+operands (an element from beyond K must not reach a product: infinity times zero is not zero)."""
+import numpy as np
+import pytest
+
+from oracle import ops
+from paper_2502_11407_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gs():
+    from paper_2502_11407_amd import binding
+    return binding
+
+
+def _embed(gs, x, dtype, offset, pad, tail):
+    """x as a strided view inside a buffer of infinities: `offset` elements before it, rows `pad` elements longer than
+    they need to be, `tail` elements after its last one (0: the buffer ends with it)."""
+    import torch
+    r, c = x.shape
+    ld = c + pad
+    buf = gs.empty_device((offset + (r - 1) * ld + c + tail,), dtype).fill_(float("inf"))
+    view = torch.as_strided(buf, (r, c), (ld, 1), offset)
+    view.copy_(gs.to_device(x, dtype))
+    return view
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("k_of", [lambda bk: 1, lambda bk: 3, lambda bk: bk - 1, lambda bk: bk, lambda bk: bk + 2, lambda bk: 2 * bk + 1,
+                                  lambda bk: 3 * bk - 6], ids=["1", "3", "bk-1", "bk", "bk+2", "2bk+1", "3bk-6"])
+def test_gemm_at_any_alignment_bit_exact(gs, dtype, ta, tb, k_of):
+    import torch
+    ran = 0
+    for out in ([dtype, "f32"] if dtype != "f32" else ["f32"]):
+        for idx in range(gs.num_instances()):
+            s = gs.instance_schedule(idx, gs.gemm_problem(dtype, 64, 64, 64, ta, tb, 1, out))
+            if s is None or s.vec_bytes == 16:
+                continue
+            bm, bn, bk = s.tile[0][0], s.tile[1][0], s.tile[2][0]
+            M, N, K = bm + 1, bn + 3, k_of(bk)
+            print("instance", idx, dtype, out, (M, N, K), "transA", ta, "transB", tb, flush=True)
+            A = inputs.small_ints(10 + idx, (K, M) if ta else (M, K), dtype, -1, 1)
+            B = inputs.small_ints(20 + idx, (N, K) if tb else (K, N), dtype, -1, 1)
+            want = ops.gemm(A, B, dtype, transA=ta, transB=tb)
+            for offset, pad, tail in ((0, 0, 0), (3, 1, 0), (1, 0, 5), (2, 4, 1)):
+                dA, dB = _embed(gs, A, dtype, offset, pad, tail), _embed(gs, B, dtype, offset + 1, pad, tail)
+                C = gs.empty_device((M, N), out).fill_(float("nan"))
+                gs.gemm(gs.gemm_problem(dtype, M, N, K, ta, tb, 1, out), dA, dB, C, schedule=s, lda=A.shape[1] + pad, ldb=B.shape[1] + pad)
+                torch.cuda.synchronize()
+                assert np.array_equal(gs.to_host_f64(C), want), (idx, offset, pad, tail)
+            ran += 1
+    assert ran >= 2
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (2, 3, 1), (1, 5, 9), (3, 1, 70), (5, 2, 2)])
+def test_tiny_operands_bit_exact(gs, dtype, M, N, K):
+    """Whole operands smaller than one vector."""
+    for tb in (0, 1):
+        A, B = inputs.small_ints(1, (M, K), dtype, -3, 3), inputs.small_ints(2, (N, K) if tb else (K, N), dtype, -3, 3)
+        C = gs.empty_device((M, N)).fill_(float("nan"))
+        gs.gemm(gs.gemm_problem(dtype, M, N, K, 0, tb), gs.to_device(A, dtype), gs.to_device(B, dtype), C)
+        assert np.array_equal(gs.to_host_f64(C), ops.gemm(A, B, dtype, transB=tb))
