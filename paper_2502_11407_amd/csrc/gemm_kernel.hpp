@@ -202,6 +202,12 @@ struct Cfg {
   static constexpr int B_CHUNKS = (BSRC == B_KC) ? BN * CPR : BK * (BN * ES / 16);
   static constexpr int A_LOADS = (A_CHUNKS + THREADS - 1) / THREADS;
   static constexpr int B_LOADS = (B_CHUNKS + THREADS - 1) / THREADS;
+  // Register-staged double buffer: two register sets, i.e. two k tiles of loads in flight, where they fit beside the
+  // accumulators, the fragments and the addresses into the 256 registers of a lane that two waves per SIMD leave
+  // (a set more than that would halve the resident waves)
+  static constexpr int STAGE_REGS = 4 * (A_LOADS + B_LOADS * (BSRC_ == B_NCS2 ? 2 : 1));
+  static constexpr int OTHER_REGS = WM_ * WN_ / 64 + 8 * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
+  static constexpr int RSETS = (!DIRECT_ && STAGES_ == 2 && KSTEPS % 2 == 0 && BSRC_ != B_CONV && 2 * STAGE_REGS + OTHER_REGS <= 256) ? 2 : 1;
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");
   static_assert(WM % MB == 0 && WN % MB == 0, "wave tiles are whole MFMA blocks");
   static_assert(VM >= 1 && (VM & (VM - 1)) == 0 && VM <= (ASRC == A_KC ? V_MAX_K : V_MAX_N), "V of the m operand: a power of two up to the chunks per row");
@@ -398,8 +404,8 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   }
 
   // ---- staging registers (global -> registers -> LDS)
-  u32x4 ra[C::DIRECT ? 1 : C::A_LOADS];
-  u32x4 rb[C::DIRECT ? 1 : C::B_LOADS * (C::BSRC == B_NCS2 ? 2 : 1)];
+  u32x4 ra[C::RSETS][C::DIRECT ? 1 : C::A_LOADS];
+  u32x4 rb[C::RSETS][C::DIRECT ? 1 : C::B_LOADS * (C::BSRC == B_NCS2 ? 2 : 1)];
 
   // element-wise access of the convolution gather
   auto b_elem_bits = [&](int k, int col) -> uint32_t {
@@ -426,6 +432,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
                          auto k_contiguous_tag, auto chunks_tag) {
     constexpr bool k_contiguous = decltype(k_contiguous_tag)::value;
     constexpr int CHUNKS = decltype(chunks_tag)::value, LOADS = (CHUNKS + C::THREADS - 1) / C::THREADS;
+    if (k_left <= 0) return;                 // a k tile beyond the last: nothing of it is used
     uint32_t skew;
     const __amdgpu_buffer_rsrc_t r = loose_rsrc(first, bytes, skew);
     if (inner) {
@@ -474,15 +481,15 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   // ---- fetch the k tile starting at k0: into registers, or straight into LDS stage `st`.
   // In a k-contiguous row a chunk beyond K would alias the next row, so those lanes are
   // sent out of range; this can only happen in the last k tile.
-  auto fetch_a = [&](int k0, int st, int part = 0, int parts = 1) {
+  auto fetch_a = [&](int k0, int st, int part = 0, int parts = 1, int set = 0) {
     const bool full = Kx - k0 >= BK;
     if constexpr (LOOSE_A) {
       if constexpr (C::ASRC == A_KC)
         fetch_loose(a_tile + (int64_t)k0 * ES, ((int64_t)(rows_valid - 1) * args.lda + (Kx - k0)) * ES, full, Kx - k0,
-                    a_voff, a_kch, ra, std::true_type{}, std::integral_constant<int, C::A_CHUNKS>{});
+                    a_voff, a_kch, ra[set], std::true_type{}, std::integral_constant<int, C::A_CHUNKS>{});
       else
         fetch_loose(a_tile + (int64_t)k0 * args.lda * ES, ((int64_t)(Kx - k0 - 1) * args.lda + (args.M - m0)) * ES, Kx - k0 >= BK + EPC - 1, Kx - k0,
-                    a_voff, a_kch, ra, std::false_type{}, std::integral_constant<int, C::A_CHUNKS>{});
+                    a_voff, a_kch, ra[set], std::false_type{}, std::integral_constant<int, C::A_CHUNKS>{});
     } else {
       const __amdgpu_buffer_rsrc_t r = rsrc_a(k0);
 #pragma unroll
@@ -495,11 +502,11 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (GENSOR_LDS void*)(lds + st * C::STAGE_BYTES + (i * C::THREADS + wave * 64) * 16),
                                                    16, off, 0, 0, 0);
         else
-          ra[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+          ra[set][i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
       }
     }
   };
-  auto fetch_b = [&](int k0, int st, int part = 0, int parts = 1) {
+  auto fetch_b = [&](int k0, int st, int part = 0, int parts = 1, int set = 0) {
     const bool full = Kx - k0 >= BK;
     if constexpr (GATHER_B) {
 #pragma unroll
@@ -508,15 +515,15 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         if (C::B_CHUNKS % C::THREADS != 0 && q >= C::B_CHUNKS) break;
         constexpr int CPRN = BN * ES / 16;
         const int krow = q / CPRN, ch = q % CPRN;
-        rb[i] = pack_chunk([&](int e) { return b_elem_bits(k0 + krow, n0 + ch * EPC + e); });
+        rb[set][i] = pack_chunk([&](int e) { return b_elem_bits(k0 + krow, n0 + ch * EPC + e); });
       }
     } else if constexpr (LOOSE_B) {
       if constexpr (C::BSRC == B_KC)
         fetch_loose(b_tile + (int64_t)k0 * ES, ((int64_t)(cols_valid - 1) * args.ldb + (Kx - k0)) * ES, full, Kx - k0,
-                    b_voff, b_kch, rb, std::true_type{}, std::integral_constant<int, C::B_CHUNKS>{});
+                    b_voff, b_kch, rb[set], std::true_type{}, std::integral_constant<int, C::B_CHUNKS>{});
       else
         fetch_loose(b_tile + (int64_t)k0 * args.ldb * ES, ((int64_t)(Kx - k0 - 1) * args.ldb + (args.N - n0)) * ES, Kx - k0 >= BK + EPC - 1, Kx - k0,
-                    b_voff, b_kch, rb, std::false_type{}, std::integral_constant<int, C::B_CHUNKS>{});
+                    b_voff, b_kch, rb[set], std::false_type{}, std::integral_constant<int, C::B_CHUNKS>{});
     } else {
       const __amdgpu_buffer_rsrc_t r = rsrc_b(k0);
 #pragma unroll
@@ -529,16 +536,16 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (GENSOR_LDS void*)(lds + st * C::STAGE_BYTES + C::A_BYTES + (i * C::THREADS + wave * 64) * 16),
                                                    16, off, 0, 0, 0);
         } else if constexpr (C::BSRC == B_NCS2) {
-          rb[2 * i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-          rb[2 * i + 1] = __builtin_amdgcn_raw_buffer_load_b128(r, b_voff2[i], 0, 0);
+          rb[set][2 * i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+          rb[set][2 * i + 1] = __builtin_amdgcn_raw_buffer_load_b128(r, b_voff2[i], 0, 0);
         } else {
-          rb[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+          rb[set][i] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
         }
       }
     }
   };
   // ---- registers -> LDS stage `st`
-  auto commit = [&](int st) {
+  auto commit = [&](int st, int set = 0) {
     if constexpr (!C::DIRECT) {
       GENSOR_LDS char* abase = lds + st * C::STAGE_BYTES;
       GENSOR_LDS char* bbase = abase + C::A_BYTES;
@@ -547,10 +554,10 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         const int q = tid + i * C::THREADS;
         if (C::A_CHUNKS % C::THREADS != 0 && q >= C::A_CHUNKS) break;
         if constexpr (C::ASRC == A_KC) {
-          *(GENSOR_LDS u32x4*)(abase + q * 16) = ra[i];
+          *(GENSOR_LDS u32x4*)(abase + q * 16) = ra[set][i];
         } else {
           constexpr int CPRM = BM * ES / 16;
-          *(GENSOR_LDS u32x4*)(abase + (q / CPRM) * C::PITCH_M + (q % CPRM) * 16) = ra[i];
+          *(GENSOR_LDS u32x4*)(abase + (q / CPRM) * C::PITCH_M + (q % CPRM) * 16) = ra[set][i];
         }
       }
 #pragma unroll
@@ -558,11 +565,11 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         const int q = tid + i * C::THREADS;
         if (C::B_CHUNKS % C::THREADS != 0 && q >= C::B_CHUNKS) break;
         if constexpr (C::BSRC == B_KC) {
-          *(GENSOR_LDS u32x4*)(bbase + q * 16) = rb[i];
+          *(GENSOR_LDS u32x4*)(bbase + q * 16) = rb[set][i];
         } else if constexpr (C::BSRC == B_NCS2) {
           // keep every other element of the two 16-byte runs
           constexpr int CPRN = BN * ES / 16;
-          const u32x4 v0 = rb[2 * i], v1 = rb[2 * i + 1];
+          const u32x4 v0 = rb[set][2 * i], v1 = rb[set][2 * i + 1];
           u32x4 o;
           if constexpr (ES == 4) {
             o[0] = v0[0]; o[1] = v0[2]; o[2] = v1[0]; o[3] = v1[2];
@@ -575,7 +582,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           *(GENSOR_LDS u32x4*)(bbase + (q / CPRN) * C::PITCH_N + (q % CPRN) * 16) = o;
         } else {
           constexpr int CPRN = BN * ES / 16;
-          *(GENSOR_LDS u32x4*)(bbase + (q / CPRN) * C::PITCH_N + (q % CPRN) * 16) = rb[i];
+          *(GENSOR_LDS u32x4*)(bbase + (q / CPRN) * C::PITCH_N + (q % CPRN) * 16) = rb[set][i];
         }
       }
     }
@@ -759,6 +766,10 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   if constexpr (C::STAGES <= 2) {
     fetch_a(0, 0);
     fetch_b(0, 0);
+    if constexpr (C::RSETS == 2) {
+      fetch_a(BK, 0, 0, 1, 1);
+      fetch_b(BK, 0, 0, 1, 1);
+    }
     commit(0);
     wait_deposits();
     __syncthreads();
@@ -862,6 +873,42 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     for (; kt + S - 1 < nk; ++kt) cur = k_tile(kt, cur, std::true_type{}, std::true_type{});
     for (; kt + 1 < nk; ++kt) cur = k_tile(kt, cur, std::false_type{}, std::true_type{});
     k_tile(kt, cur, std::false_type{}, std::false_type{});
+  } else if constexpr (C::RSETS == 2) {
+    // Register-staged, two k tiles of loads in flight: tile kt+2 is requested at the top of tile kt into the register
+    // set that tile kt left, and tile kt+1 (requested a whole k tile earlier) goes to LDS at the end of kt.  With one
+    // set a tile's loads had one tile's MFMA time to arrive, less than the memory latency for most tiles, and every
+    // k tile waited.  Requests beyond K fall out of range and return at once.
+    auto k_tile = [&](int kt, auto set_tag, auto more_tag) {
+      constexpr int set = decltype(set_tag)::value;
+      constexpr bool more = decltype(more_tag)::value;
+      const int cur = kt & 1, nxt = cur ^ 1;
+#pragma unroll
+      for (int ks = 0; ks < C::KSTEPS; ++ks) {
+        if constexpr (more) {
+          if (ks == 0) {
+            fetch_a((kt + 2) * BK, 0, 0, 1, set);
+            fetch_b((kt + 2) * BK, 0, 0, 1, set);
+          }
+        }
+        if (ks + 1 < C::KSTEPS) {
+          read_frags(cur, ks + 1, (ks + 1) & 1);
+        } else if constexpr (more) {
+          commit(nxt, set ^ 1);
+          block_sync();
+          read_frags(nxt, 0, 0);
+        }
+        mma(ks & 1, std::integral_constant<int, 0>{});
+        interleave();
+      }
+    };
+    read_frags(0, 0, 0);
+    int kt = 0;
+    for (; kt + 2 < nk; kt += 2) {
+      k_tile(kt, std::integral_constant<int, 0>{}, std::true_type{});
+      k_tile(kt + 1, std::integral_constant<int, 1>{}, std::true_type{});
+    }
+    if (kt + 1 < nk) k_tile(kt++, std::integral_constant<int, 0>{}, std::true_type{});
+    k_tile(kt, std::integral_constant<int, 0>{}, std::false_type{});
   } else if constexpr (PIPE) {
     // Whether a further k tile follows is a compile-time property of the loop body: the last k
     // tile is peeled.  With a run-time test the two paths would meet in front of the last k
