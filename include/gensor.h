@@ -172,13 +172,10 @@ gensor_status gensor_instance_schedule(int32_t id, const gensor_problem* p, gens
  * s->round_units.  The tiles of the last round, if it is not full (every
  * tile when there are fewer tiles than units), are each computed by split_k workgroups,
  * every one over its own range of whole k tiles (needs ceil(K / BK) >= split_k, else
- * NO_SCHEDULE); the parts of a tile leave fp32 partial tiles in `workspace` and the part
- * that finishes last adds them up (two parts: one order of addition; more: in part order,
- * so the result is reproducible) and writes C.  This is what a contraction with few output
+ * NO_SCHEDULE); the parts of a tile leave fp32 partial tiles in `workspace`, and a second launch
+ * behind the operator adds them up (in part order, so the result is reproducible) and writes C.  This is what a contraction with few output
  * tiles and a deep k needs to occupy the chip.  `workspace` is device memory, 256-byte
- * aligned, at least gensor_workspace_bytes(s, p) bytes (WORKSPACE otherwise): arrival
- * counters, which the call clears itself with a small launch of its own in front of the
- * operator, then the partial tiles.  It is scratch: nothing is kept in it between calls, and
+ * aligned, at least gensor_workspace_bytes(s, p) bytes (WORKSPACE otherwise), for the partial tiles.  It is scratch: nothing is kept in it between calls, and
  * two calls that overlap in time must not share it.  If the tile count is a whole number of
  * rounds nothing is split and no workspace is needed (gensor_workspace_bytes returns 0).
  * With s == NULL split-k schedules are ranked only when a workspace is passed, and one too
@@ -193,14 +190,13 @@ gensor_status gensor_gemm(const gensor_schedule* s, const gensor_problem* p, flo
 /*
  * gensor_gemm for callers that cannot allocate device memory for a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same operator, the same
- * kernels and the same results, with the split-k counters and partial tiles kept in a device array
+ * kernels and the same results, with the split-k partial tiles kept in a device array
  * of GENSOR_STATIC_SCRATCH_BYTES that is part of the library's code object (every GPU the library
  * runs on holds its own copy until the process ends).  The call allocates and frees nothing.
  * A schedule whose gensor_workspace_bytes(s, p) exceeds GENSOR_STATIC_SCRATCH_BYTES is refused with
  * GENSOR_ERR_WORKSPACE and nothing is launched; with s == NULL split-k schedules are ranked and one
  * that does not fit falls back to the best unsplit schedule, as in gensor_gemm.  Every call on one
- * GPU shares that GPU's array, which keeps the last call's contents (the call clears the counters it
- * uses itself): calls that overlap in time on one GPU -- different streams, or graphs replayed
+ * GPU shares that GPU's array, which keeps the last call's contents: calls that overlap in time on one GPU -- different streams, or graphs replayed
  * concurrently -- race on it and must be serialised by the caller.
  */
 #define GENSOR_STATIC_SCRATCH_BYTES (32 * 1024 * 1024 + 65536)
@@ -239,7 +235,7 @@ gensor_status gensor_conv2d(const gensor_schedule* s, const gensor_problem* p,
                             void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Bytes of workspace the operator call on `p` with schedule `s` needs: the compacted input of a
- * strided pointwise convolution, or the counters and partial tiles of a split-k GEMM/BMM
+ * strided pointwise convolution, or the partial tiles of a split-k GEMM/BMM
  * (s required); 0 if none.  For a convolution s == NULL gives the most any schedule the
  * library may construct can ask for. */
 size_t gensor_workspace_bytes(const gensor_schedule* s, const gensor_problem* p);

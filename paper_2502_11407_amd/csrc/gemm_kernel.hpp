@@ -63,7 +63,6 @@ struct KernelArgs {
   // `split` workgroups each, every one over its own range of k tiles (split == 1: whole == all tiles)
   int32_t split, whole;
   float* partials;                 // [tile - whole][split][BM * BN] fp32, lane-major inside a slot
-  uint32_t* counters;              // [tile - whole][waves per workgroup], zero at launch
   // convolution geometry (B_CONV only)
   int32_t cC, cH, cW, cR, cS, cP, cQ, cStride, cPad;
   // patch-staged convolution only: images, LDS plan and tensor sizes in bytes (each < 2^31)
@@ -233,6 +232,25 @@ __device__ inline int swizzled_chunk(int row, int chunk, int rpp, int v) { retur
 // different 32-byte halves.
 __device__ inline int nc_swizzle(int krow, int v) { return ((krow & (v - 1)) << 6) ^ (v >= 4 ? (((krow >> 3) & 1) << 5) : 0); }
 
+template <int N, int I = 0, typename F>
+__device__ inline __attribute__((always_inline)) void static_for(F&& f) {      // f(integral_constant<int, 0 .. N-1>)
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// tile number inside a batch -> tile coordinates: panels of `panel` tile rows, walked column by column
+__device__ inline void tile_of(const KernelArgs& args, int t, int& tile_m, int& tile_n) {
+  const int panel = args.panel;
+  const int per_panel = panel * args.tiles_n;
+  const int pi = t / per_panel;
+  const int rows_here = min(panel, args.tiles_m - pi * panel);
+  const int r = t - pi * per_panel;
+  tile_m = pi * panel + r % rows_here;
+  tile_n = r / rows_here;
+}
+
 // ---------------------------------------------------------------- the kernel
 // SPLIT: the launch has split tiles (KernelArgs::split > 1); without it the kernel knows at compile time
 // that every workgroup owns a whole tile.
@@ -264,27 +282,19 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   } else if (wg < args.whole) {
     if ((args.whole & 7) == 0) wg = (wg & 7) * (args.whole >> 3) + (wg >> 3);
   } else {
-    // the split tiles come last in launch order; with workgroup ids dealt round-robin to the XCDs the parts
-    // of one tile are neighbours on one XCD (a matter of locality only)
+    // the split tiles come last in launch order, part by part: an XCD then holds neighbouring tiles over one range of
+    // k and its L2 fetches each operand's range once for all of them.  Tile by tile it fetched the slabs of its few tiles
+    // over the whole of k: 512 x 512 x 32768 in 16 parts read its operands three times over, 38.7 against 29-30 us.
     kparts = args.split;
+    const int tiles = total - args.whole, units = tiles * kparts;
     int u = wg - args.whole;
-    const int units = (total - args.whole) * kparts;
     if ((units & 7) == 0) u = (u & 7) * (units >> 3) + (u >> 3);
-    wg = args.whole + u / kparts;
-    kpart = u - (wg - args.whole) * kparts;
+    kpart = u / tiles;
+    wg = args.whole + u - kpart * tiles;
   }
   const int bidx = wg / tiles_per_batch;
-  int t = wg - bidx * tiles_per_batch;
   int tile_m, tile_n;
-  {
-    const int panel = args.panel;
-    const int per_panel = panel * args.tiles_n;
-    const int pi = t / per_panel;
-    const int rows_here = min(panel, args.tiles_m - pi * panel);
-    const int r = t - pi * per_panel;
-    tile_m = pi * panel + r % rows_here;
-    tile_n = r / rows_here;
-  }
+  tile_of(args, wg - bidx * tiles_per_batch, tile_m, tile_n);
   const int m0 = tile_m * BM;
   const int n0 = tile_n * BN;
 
@@ -978,64 +988,26 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     }
   }
 
-  // ---- split tile: exchange the partial sums; one wave per (tile, wave position) goes on to the epilogue
+  // ---- split tile: this part's sums go to its slot, 16 bytes per lane and store, a wave's store one contiguous KiB;
+  // split_reduce, launched behind this kernel, adds a tile's slots up and writes C.  (Written through: the lines
+  // are on their way to memory while the other parts still multiply.)
   if (SPLIT && kparts > 1) {
-    // Every wave leaves its accumulators in this workgroup's slot (16 bytes per lane and store, a wave's store
-    // one contiguous KiB) and counts itself in.  The wave that finds the other parts-1 already counted adds
-    // their slots to its own registers and goes on to the epilogue; the others are done.  Nothing waits.
-    // Two parts: own registers plus the other slot (the sum of two terms has one order).  More: the slots are
-    // summed from memory in part order, so the result does not depend on who came last.
-    // The parts of a tile may run on different XCDs, whose L2s do not see each other's lines: the slot
-    // stores and loads carry the device-scope cache policy (write through / fetch again), a wave counts
-    // itself in only after its stores have completed, and the count is a device-scope atomic.  Nothing else
-    // in the kernel pays for this (a device-scope fence would write back and invalidate the whole L2 here).
     constexpr int NV = C::MBLK * C::NBLK * MF::NACC / 4;       // 16-byte groups per lane
     constexpr int SLOT_BYTES = BM * BN * 4;
-    constexpr int DEVICE_SCOPE = 16;                           // sc1: the access is coherent across the whole device
-    const int64_t tile_slot = (int64_t)(wg - args.whole) * kparts;
-    auto slot = [&](int o) {
-      return __builtin_amdgcn_make_buffer_rsrc((void*)((char*)args.partials + (tile_slot + o) * (int64_t)SLOT_BYTES), 0,
-                                               (uint32_t)SLOT_BYTES, RSRC_FLAGS);
-    };
-    const __amdgpu_buffer_rsrc_t own = slot(kpart);
+    constexpr int WRITE_THROUGH = 16;                          // sc1
+    const int64_t own = (int64_t)(wg - args.whole) * kparts + kpart;
+    const __amdgpu_buffer_rsrc_t slot = __builtin_amdgcn_make_buffer_rsrc((void*)((char*)args.partials + own * (int64_t)SLOT_BYTES), 0,
+                                                                          (uint32_t)SLOT_BYTES, RSRC_FLAGS);
 #pragma unroll
     for (int g = 0; g < NV; ++g) {
       const int b = g / (MF::NACC / 4), q = g % (MF::NACC / 4);
       u32x4 v;
 #pragma unroll
       for (int x = 0; x < 4; ++x) v[x] = as_u32(acc[b / C::NBLK][b % C::NBLK][4 * q + x]);
-      __builtin_amdgcn_raw_buffer_store_b128(v, own, (uint32_t)((g * C::THREADS + tid) * 16), 0, DEVICE_SCOPE);
+      __builtin_amdgcn_raw_buffer_store_b128(v, slot, (uint32_t)((g * C::THREADS + tid) * 16), 0, WRITE_THROUGH);
       if (g % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // compiler ordering
-    __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): this wave's slot stores have completed
-    __builtin_amdgcn_sched_barrier(0);
-    uint32_t before = 0;
-    if (lane == 0) before = atomicAdd(args.counters + (int64_t)(wg - args.whole) * C::WAVES + wave, 1u);
-    before = __builtin_amdgcn_readfirstlane(before);
-    if (before != (uint32_t)(kparts - 1)) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const bool from_memory = kparts > 2;
-    if (from_memory) {
-#pragma unroll
-      for (int i = 0; i < C::MBLK; ++i)
-#pragma unroll
-        for (int j = 0; j < C::NBLK; ++j)
-#pragma unroll
-          for (int v = 0; v < MF::NACC; ++v) acc[i][j][v] = 0.f;
-    }
-    for (int o = 0; o < kparts; ++o) {
-      if (!from_memory && o == kpart) continue;
-      const __amdgpu_buffer_rsrc_t src = slot(o);
-#pragma unroll
-      for (int g = 0; g < NV; ++g) {
-        const int b = g / (MF::NACC / 4), q = g % (MF::NACC / 4);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(src, (uint32_t)((g * C::THREADS + tid) * 16), 0, DEVICE_SCOPE);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) acc[b / C::NBLK][b % C::NBLK][4 * q + x] += as_f32(v[x]);
-        if (g % 8 == 7) __builtin_amdgcn_sched_barrier(0);     // eight loads in flight, not all of them: registers
-      }
-    }
+    return;
   }
 
   // ---- epilogue: C = alpha * acc + beta * C through a buffer descriptor that starts at this
@@ -1115,6 +1087,60 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         else store_block(bi, bj, lane_off, std::false_type{});
       }
     }
+  }
+}
+
+// ---- split-k: C = alpha * (sum of a tile's slots) + beta * C, one 16-byte group of a slot (four rows of one column) per
+// thread.  The slots are added in part order, so the result does not depend on when a part finished.  Bound by the
+// fp32 partial tiles it reads, (tiles - whole) * split * BM * BN * 4 bytes, spread over the whole chip.  An
+// earlier form counted the parts of a tile in with atomics and let the last one add the slots up: that read them
+// with one workgroup per tile, 16 of 256 CUs on 512 x 512 x 32768, and needed a launch of its own all the same,
+// to clear the counters (that shape in 16 parts: 51.4 us, 38.7 us with this launch instead).
+template <typename OutT>
+__global__ __launch_bounds__(256) void split_reduce(const KernelArgs args, int bm, int bn, int wm, int wn, int mb) {
+  const int threads = (bm / wm) * (bn / wn) * 64;          // of a workgroup of the contraction
+  const int groups = bm * bn / 4;                          // 16-byte groups of a slot
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int u = (int)(idx / groups), r = (int)(idx - (int64_t)u * groups);
+  const int tiles_per_batch = args.tiles_m * args.tiles_n;
+  const int wg = args.whole + u;
+  if (wg >= tiles_per_batch * args.batch) return;
+  // group r = g * threads + tid of the contraction's store: block g / (groups per block), four rows 8 * (g % ...) down
+  const int g = r / threads, tid = r - g * threads;
+  const int lane = tid & 63, wave = tid >> 6, waves_n = bn / wn, nblk = wn / mb;
+  const int per_block = mb == 32 ? 4 : 1;
+  const int b = g / per_block, q = g - b * per_block;
+  const int row = (wave / waves_n) * wm + (b / nblk) * mb + 8 * q + 4 * (lane / mb);
+  const int col = (wave % waves_n) * wn + (b % nblk) * mb + lane % mb;
+  const f32x4* slot = (const f32x4*)args.partials + (int64_t)u * args.split * groups + r;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  int o = 0;
+  for (; o + 4 <= args.split; o += 4) {                    // four loads in flight
+    f32x4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = slot[(int64_t)(o + i) * groups];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) sum[x] += v[i][x];
+  }
+  for (; o < args.split; ++o) {
+    const f32x4 v = slot[(int64_t)o * groups];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) sum[x] += v[x];
+  }
+  const int bidx = wg / tiles_per_batch;
+  int tile_m, tile_n;
+  tile_of(args, wg - bidx * tiles_per_batch, tile_m, tile_n);
+  const int m = tile_m * bm + row, n = tile_n * bn + col;
+  if (n >= args.N) return;
+  const int64_t c0 = (int64_t)bidx * args.strideC + (int64_t)m * args.ldc + n;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    if (m + x >= args.M) break;
+    float v = args.alpha * sum[x];
+    if (args.beta != 0.f) v = fmaf(args.beta, to_float<OutT>(args.C, c0 + x * args.ldc), v);
+    store_out<OutT>(args.C, c0 + x * args.ldc, v);
   }
 }
 

@@ -60,8 +60,7 @@ const InstanceDesc* find_instance(const gensor_schedule* s, const GemmView& v);
 struct SplitPlan {
   int split;               // parts per split tile (1: nothing is split)
   int64_t whole;           // tiles computed by one workgroup each
-  int64_t counter_bytes;   // arrival counters at the start of the workspace, padded to 256 bytes
-  size_t bytes;            // counters + partial tiles
+  size_t bytes;            // partial tiles
 };
 // round_units: the compute units a round of tiles is dealt over (gensor_schedule::round_units; 0: the MI355X's).
 SplitPlan split_plan(const InstanceDesc& d, const GemmView& v, int split, int round_units);
