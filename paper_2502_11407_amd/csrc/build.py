@@ -65,7 +65,7 @@ def generate():
     for d in L:
         es = 4 if d["dt"] == "f32" else 2
         kg = (64 // d["mb"]) * (16 // es)
-        a_bytes = d["bm"] * d["bk"] * es if d["asrc"] == "KC" else d["bk"] * (d["bm"] * es + lattice.pad_m(d))
+        a_bytes = d["bm"] * d["bk"] * es if d["asrc"] == "KC" else d["bk"] * (d["bm"] * es + (0 if d["direct"] else lattice.pad_m(d)))
         b_bytes = d["bn"] * d["bk"] * es if (d["bsrc"] == "KC" or d["direct"]) else d["bk"] * (d["bn"] * es + lattice.pad_n(d))
         lds = 0 if d["units"] else (a_bytes + b_bytes) * d["stages"]
         threads = (d["bm"] // d["wm"]) * (d["bn"] // d["wn"]) * 64

@@ -16,7 +16,7 @@
 //   DIRECT     K-contiguous operands go global->LDS without passing through registers
 //
 // Operand sources.  A (the m x k operand) is k-contiguous, A[m][k] (A_KC), or m-contiguous, A stored
-// [k][m] (A_MC, "transA": staged and read exactly like an n-contiguous B, register-staged only).  B is
+// [k][m] (A_MC, "transA": staged and read exactly like an n-contiguous B).  B is
 //   KC   k-contiguous,  B stored [n][k]   (column-major B / "transB")
 //   NC   n-contiguous,  B stored [k][n]   (row-major B)
 //   CONV n = (image, out row, out col), k = (channel, filter row, filter col): element
@@ -183,6 +183,7 @@ struct Cfg {
   // (direct staging deposits whole 1 KB runs, so there the rows are unpadded and 32-byte
   // column segments are XOR-swizzled with the k row instead)
   static constexpr bool NC_DIRECT = DIRECT_ && BSRC_ == B_NC;
+  static constexpr bool MC_DIRECT = DIRECT_ && ASRC_ == A_MC;
   static constexpr int V_MAX_K = CPR;                        // deepest interleave of a k-contiguous tile
   static constexpr int V_MAX_N = (ES == 2) ? 4 : 2;          // ... of an n-contiguous tile
   // the pad puts consecutive k rows 64 bytes (V = 4) or 32 bytes (V = 2) apart modulo the 256 bytes of all banks
@@ -192,7 +193,7 @@ struct Cfg {
   // m-contiguous A tile: [BK][BM] + pad, the same rule
   static constexpr int PAD_TM = (VM >= 4) ? 64 : 32;
   static constexpr int PAD_M = (VM == 1) ? 0 : (PAD_TM + 2 * PAD_TM - (BM * ES) % (2 * PAD_TM)) % (2 * PAD_TM);
-  static constexpr int PITCH_M = BM * ES + PAD_M;
+  static constexpr int PITCH_M = MC_DIRECT ? BM * ES : BM * ES + PAD_M;
   static constexpr int A_BYTES = (ASRC == A_KC) ? BM * PITCH_K : BK * PITCH_M;
   static constexpr int B_BYTES = (BSRC == B_KC) ? BN * PITCH_K : BK * PITCH_N;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
@@ -210,7 +211,8 @@ struct Cfg {
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");
   static_assert(WM % MB == 0 && WN % MB == 0, "wave tiles are whole MFMA blocks");
   static_assert(VM >= 1 && (VM & (VM - 1)) == 0 && VM <= (ASRC == A_KC ? V_MAX_K : V_MAX_N), "V of the m operand: a power of two up to the chunks per row");
-  static_assert(ASRC == A_KC || (!DIRECT_ && BSRC != B_CONV && BSRC != B_NCS2), "an m-contiguous A is register-staged, GEMM only");
+  static_assert(ASRC == A_KC || (BSRC != B_CONV && BSRC != B_NCS2), "an m-contiguous A is for GEMM only");
+  static_assert(!MC_DIRECT || (ES == 2 && BM * ES / 16 >= 16 && A_CHUNKS % THREADS == 0), "its direct staging deposits whole waves of swizzled rows of at least 16 chunks");
   static_assert(VN >= 1 && (VN & (VN - 1)) == 0 && VN <= (BSRC == B_KC ? V_MAX_K : V_MAX_N), "V of the n operand");
   static_assert(BK % KG == 0, "BK must be a multiple of the fragment k extent");
   static_assert(MB == 32 || MB == 16, "MFMA block edge");
@@ -379,7 +381,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       a_kch[i] = ch * EPC;
     } else {
       constexpr int CPRM = BM * ES / 16;
-      a_voff[i] = (uint32_t)(((q / CPRM) * (int)args.lda + (q % CPRM) * EPC) * ES);
+      int ch = q % CPRM;
+      if constexpr (C::MC_DIRECT) ch ^= nc_swizzle(q / CPRM, C::VM) >> 4;
+      a_voff[i] = (uint32_t)(((q / CPRM) * (int)args.lda + ch * EPC) * ES);
       a_kch[i] = q / CPRM;
     }
   }
@@ -624,8 +628,23 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   // hence ordered: "at most N outstanding", with N no more than the number of such reads issued after the awaited
   // ones, means the awaited ones have landed.  The halves stay separate values until that wait (a copy of a pending
   // register would read stale data); the compiler's own waits only get more conservative by operations it does not see.
-  constexpr bool ASM_TR = C::NC_DIRECT && ES == 2;
-  u32x2 fbl[ASM_TR ? FSETS : 1][ASM_TR ? C::NBLK : 1], fbh[ASM_TR ? FSETS : 1][ASM_TR ? C::NBLK : 1];
+  // An m-contiguous A staged directly is read the same way, and a k-contiguous one beside such a B too: left to the
+  // compiler, its waits counted only its own reads and so waited for reads issued a moment earlier, in every k step
+  // (8192 x 768 x 3072 f16, 128x256 ring: 46.5 -> 42.7 us, eight-wave 128x128 tile 49.8 -> 46.9).
+  constexpr bool ASM_A = C::MC_DIRECT, ASM_B = C::NC_DIRECT && ES == 2, ASM_TR = ASM_A || ASM_B;
+  u32x2 fal[ASM_A ? FSETS : 1][ASM_A ? C::MBLK : 1], fah[ASM_A ? FSETS : 1][ASM_A ? C::MBLK : 1];
+  u32x2 fbl[ASM_B ? FSETS : 1][ASM_B ? C::NBLK : 1], fbh[ASM_B ? FSETS : 1][ASM_B ? C::NBLK : 1];
+  // The two transposing reads of one block from an unpadded, XOR-swizzled tile stored [k][rows].  The swizzle of a lane's
+  // k rows is the same in every k step and four rows further down, so those are immediate offsets.
+  auto issue_transposed = [&](GENSOR_LDS char* base, auto pitch_tag, int first, auto ks_tag, int v, u32x2& lo, u32x2& hi) {
+    constexpr int pitch = decltype(pitch_tag)::value, ks = decltype(ks_tag)::value;
+    const int g = lane >> 4, s = lane & 15;
+    const int krow = (MB == 32 ? (g >> 1) * 8 : g * 8) + (s >> 2);
+    const int col = first + (MB == 32 ? (g & 1) * 16 : 0) + (s & 3) * 4;
+    const uint32_t at = (uint32_t)(uintptr_t)(base + krow * pitch + ((col * 2) ^ nc_swizzle(krow, v)));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(ks * C::KG * pitch));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"((ks * C::KG + 4) * pitch));
+  };
   // Fragment of one MFMA block from a tile stored [k][rows] (an n-contiguous B or an m-contiguous A), `first` =
   // the block's first row/column inside the tile, `direct` = the tile is unpadded and XOR-swizzled.
   auto read_transposed = [&](GENSOR_LDS char* base, int pitch, int first, int ks, auto direct_tag, int v) -> u32x4 {
@@ -663,7 +682,39 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       return r;
     }
   };
+  auto read_frags_asm = [&](int st, auto ks_tag, int buf) {
+    constexpr int ks = decltype(ks_tag)::value;
+    GENSOR_LDS char* abase = lds + st * C::STAGE_BYTES;
+    GENSOR_LDS char* bbase = abase + C::A_BYTES;
+    const int ch = ks * C::LANE_GROUPS + fgrp;
+    static_for<C::MBLK>([&](auto bi) {
+      if constexpr (ASM_A) {
+        issue_transposed(abase, std::integral_constant<int, C::PITCH_M>{}, block_row(bi), ks_tag, C::VM, fal[buf][bi], fah[buf][bi]);
+      } else {
+        // rows MB apart share their swizzle: blocks are immediate offsets
+        const int row = block_row(0) + frow;
+        const uint32_t at = (uint32_t)(uintptr_t)(abase + row * C::PITCH_K + swizzled_chunk(row, ch, C::RPP, C::VM) * 16);
+        u32x4& frag = fa[buf][bi];
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(frag) : "v"(at), "n"(decltype(bi)::value * MB * C::PITCH_K));
+      }
+    });
+    static_for<C::NBLK>([&](auto bj) {
+      if constexpr (ASM_B) {
+        issue_transposed(bbase, std::integral_constant<int, C::PITCH_N>{}, block_col(bj), ks_tag, C::VN, fbl[buf][bj], fbh[buf][bj]);
+      } else {
+        const int row = block_col(0) + frow;
+        const uint32_t at = (uint32_t)(uintptr_t)(bbase + row * C::PITCH_K + swizzled_chunk(row, ch, C::RPP, C::VN) * 16);
+        u32x4& frag = fb[buf][bj];
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(frag) : "v"(at), "n"(decltype(bj)::value * MB * C::PITCH_K));
+      }
+    });
+  };
   auto read_frags = [&](int st, int ks, int buf) {
+    if constexpr (ASM_TR) {
+      // (ks is a constant at every call once the k steps are unrolled: one of these remains)
+      static_for<C::KSTEPS>([&](auto k) { if (ks == decltype(k)::value) read_frags_asm(st, k, buf); });
+      return;
+    }
     GENSOR_LDS char* abase = lds + st * C::STAGE_BYTES;
     GENSOR_LDS char* bbase = abase + C::A_BYTES;
     const int ch = ks * C::LANE_GROUPS + fgrp;
@@ -681,36 +732,44 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       if constexpr (C::BSRC == B_KC) {
         const int row = block_col(bj) + frow;
         fb[buf][bj] = *(GENSOR_LDS u32x4*)(bbase + row * C::PITCH_K + swizzled_chunk(row, ch, C::RPP, C::VN) * 16);
-      } else if constexpr (ASM_TR) {
-        const int g = lane >> 4, s = lane & 15;
-        int krow, col;
-        if constexpr (MB == 32) {
-          krow = ks * C::KG + (g >> 1) * 8 + (s >> 2);
-          col = block_col(bj) + (g & 1) * 16 + (s & 3) * 4;
-        } else {
-          krow = ks * C::KG + g * 8 + (s >> 2);
-          col = block_col(bj) + (s & 3) * 4;
-        }
-        const uint32_t a0 = (uint32_t)(uintptr_t)(bbase + krow * C::PITCH_N + ((col * 2) ^ nc_swizzle(krow, C::VN)));
-        const uint32_t a1 = (uint32_t)(uintptr_t)(bbase + (krow + 4) * C::PITCH_N + ((col * 2) ^ nc_swizzle(krow + 4, C::VN)));
-        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(fbl[buf][bj]) : "v"(a0));
-        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(fbh[buf][bj]) : "v"(a1));
       } else {
         fb[buf][bj] = read_transposed(bbase, C::PITCH_N, block_col(bj), ks, std::integral_constant<bool, C::NC_DIRECT>{}, C::VN);
       }
     }
   };
-  // groups: how many later read_frags calls (each 2 * NBLK transposing reads) have been issued since the one that
-  // filled register set buf -- a lower bound; 0 waits for every LDS operation
+  // groups: how many later read_frags calls (READS LDS reads each) have been issued since the one that filled register
+  // set buf -- a lower bound; 0 waits for every LDS operation
   auto settle = [&](int buf, auto groups_tag) {
     if constexpr (ASM_TR) {
-      constexpr int N = decltype(groups_tag)::value * 2 * C::NBLK > 15 ? 15 : decltype(groups_tag)::value * 2 * C::NBLK;
+      constexpr int READS = (ASM_A ? 2 : 1) * C::MBLK + (ASM_B ? 2 : 1) * C::NBLK;
+      constexpr int N = decltype(groups_tag)::value * READS > 15 ? 15 : decltype(groups_tag)::value * READS;
+      bool waited = false;
+      auto take = [&](auto& x) {
+        if (!waited) asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
+        else asm volatile("" : "+v"(x));
+        waited = true;
+      };
+#pragma unroll
+      for (int bi = 0; bi < C::MBLK; ++bi) {
+        if constexpr (ASM_A) {
+          take(fal[buf][bi]);
+          take(fah[buf][bi]);
+          const u32x4 v = {fal[buf][bi][0], fal[buf][bi][1], fah[buf][bi][0], fah[buf][bi][1]};
+          fa[buf][bi] = v;
+        } else {
+          take(fa[buf][bi]);
+        }
+      }
 #pragma unroll
       for (int bj = 0; bj < C::NBLK; ++bj) {
-        if (bj == 0) asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(fbl[buf][bj]), "+v"(fbh[buf][bj]) : "n"(N));
-        else asm volatile("" : "+v"(fbl[buf][bj]), "+v"(fbh[buf][bj]));
-        const u32x4 v = {fbl[buf][bj][0], fbl[buf][bj][1], fbh[buf][bj][0], fbh[buf][bj][1]};
-        fb[buf][bj] = v;
+        if constexpr (ASM_B) {
+          take(fbl[buf][bj]);
+          take(fbh[buf][bj]);
+          const u32x4 v = {fbl[buf][bj][0], fbl[buf][bj][1], fbh[buf][bj][0], fbh[buf][bj][1]};
+          fb[buf][bj] = v;
+        } else {
+          take(fb[buf][bj]);
+        }
       }
     }
   };

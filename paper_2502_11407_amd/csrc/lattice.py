@@ -50,8 +50,11 @@ def pad_m(d):
 
 
 def splittable(d):
-    """Instances also compiled with split tiles (split-k): plainly fetched operands, vector loads, double buffer."""
-    return d["bsrc"] in ("KC", "NC") and d["vec"] == 1 and d["stages"] == 2 and not d["units"]
+    """Instances also compiled with split tiles (split-k): plainly fetched operands, two or three LDS stages; off the
+    vector boundaries the fp32-output ones with a deep k tile."""
+    if d["bsrc"] not in ("KC", "NC") or d["units"] or d["stages"] == 1:
+        return False
+    return d["vec"] == 1 or (d["out"] == "f32" and d["mb"] == 32)
 
 
 def lattice():
@@ -195,6 +198,13 @@ def lattice():
                     out.append(_inst(dt, odt, bm, bn, 64, wm, wn, 32, bsrc=bsrc, vec=0, asrc=asrc))
         for (bm, bn, wm, wn) in ((128, 128, 64, 64), (64, 64, 32, 32)):
             out.append(_inst("f32", "f32", bm, bn, 32, wm, wn, 32, bsrc=bsrc, vec=0, asrc=asrc))
+    # A stored [k][m] staged directly, as an n-contiguous B is: two stages, and rings of three for the mid-size tiles
+    for bsrc in ("KC", "NC"):
+        for dt in ("f16", "bf16"):
+            for (bm, bn, wm, wn) in ((256, 256, 128, 64), (256, 128, 64, 64), (128, 256, 64, 64), (128, 128, 64, 64), (128, 128, 64, 32)):
+                out.append(_inst(dt, "f32", bm, bn, 64, wm, wn, 32, bsrc=bsrc, direct=1, asrc="MC"))
+            for (bm, bn) in ((128, 256), (256, 128)):
+                out.append(_inst(dt, "f32", bm, bn, 64, 64, 64, 32, bsrc=bsrc, stages=3, direct=1, asrc="MC"))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],
