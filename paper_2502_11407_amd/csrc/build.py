@@ -35,20 +35,21 @@ def generate():
     L = lattice.lattice()
     tus = []
     # translation units hold instances of one kernel template only (they are built with different flags)
-    ordered = [d for d in L if not d["units"]]
-    ordered += [None] * (-len(ordered) % PER_TU) + [d for d in L if d["units"]]
+    conv = [d for d in L if d["units"] or lattice.conv_rows(d)]
+    ordered = [d for d in L if not (d["units"] or lattice.conv_rows(d))]
+    ordered += [None] * (-len(ordered) % PER_TU) + conv
     for t in range(0, len(ordered), PER_TU):
         group = [d for d in ordered[t:t + PER_TU] if d is not None]
         src = ['#include "registry.hpp"', "namespace gensor {"]
         for d in group:
             src.append("typedef %s C_%d;" % (lattice.cfg_type(d), d["id"]))
-            src.append("hipError_t launch_%d(const KernelArgs& a, hipStream_t st) { return %s<C_%d>(a, st); }"
-                       % (d["id"], "launch_conv_instance" if d["units"] else "launch_instance", d["id"]))
+            launcher = "launch_conv_instance" if d["units"] else "launch_conv_rows" if lattice.conv_rows(d) else "launch_instance"
+            src.append("hipError_t launch_%d(const KernelArgs& a, hipStream_t st) { return %s<C_%d>(a, st); }" % (d["id"], launcher, d["id"]))
             if lattice.splittable(d):
                 src.append("hipError_t launch_split_%d(const KernelArgs& a, hipStream_t st) { return launch_instance<C_%d, true>(a, st); }"
                            % (d["id"], d["id"]))
         src.append("}  // namespace gensor\n")
-        path = os.path.join(GEN, "%s_%03d.hip" % ("conv" if group[0]["units"] else "inst", t // PER_TU))
+        path = os.path.join(GEN, "%s_%03d.hip" % ("conv" if group[0]["units"] or lattice.conv_rows(group[0]) else "inst", t // PER_TU))
         _write_if_changed(path, "\n".join(src))
         tus.append(path)
     for f in os.listdir(GEN):                      # units of an earlier lattice
@@ -67,7 +68,7 @@ def generate():
         kg = (64 // d["mb"]) * (16 // es)
         a_bytes = d["bm"] * d["bk"] * es if d["asrc"] == "KC" else d["bk"] * (d["bm"] * es + (0 if d["direct"] else lattice.pad_m(d)))
         b_bytes = d["bn"] * d["bk"] * es if (d["bsrc"] == "KC" or d["direct"]) else d["bk"] * (d["bn"] * es + lattice.pad_n(d))
-        lds = 0 if d["units"] else (a_bytes + b_bytes) * d["stages"]
+        lds = 0 if d["units"] or lattice.conv_rows(d) else (a_bytes + b_bytes) * d["stages"]
         threads = (d["bm"] // d["wm"]) * (d["bn"] // d["wn"]) * 64
         reg.append("  {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, launch_%d, %s}," % (
             d["id"], lattice.DT[d["dt"]], lattice.DT[d["out"]], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"],
@@ -85,7 +86,7 @@ def generate():
 
 def _compile(src):
     obj = os.path.join(GEN, os.path.basename(src).rsplit(".", 1)[0] + ".o")
-    deps = [src, os.path.join(HERE, "gemm_kernel.hpp"), os.path.join(HERE, "conv_kernel.hpp"), os.path.join(HERE, "registry.hpp"),
+    deps = [src, os.path.join(HERE, "gemm_kernel.hpp"), os.path.join(HERE, "conv_kernel.hpp"), os.path.join(HERE, "conv_rows_kernel.hpp"), os.path.join(HERE, "registry.hpp"),
             os.path.join(HERE, "host_common.hpp"), os.path.join(PKG, "..", "include", "gensor.h")]
     if os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps if os.path.exists(d)):
         return obj

@@ -338,12 +338,54 @@ double predict_patch(const GemmView& v, const gensor_hw& hw, int bm, int bn, int
   return (t_cu > t_hbm ? t_cu : t_hbm) + 0.3 * (t_cu > t_hbm ? t_hbm : t_cu) + hw.launch_us;
 }
 
+// Row-staged convolution: per stage of channels a workgroup loads, writes LDS, waits and multiplies; the workgroups
+// resident on a CU overlap these with each other.
+double predict_rows(const GemmView& v, const gensor_hw& hw, int bm, int bn, int wm, int wn) {
+  ConvRowsPlan pl;
+  if (!conv_rows_plan(bm, bn, v, &pl, hw.compute_units)) return -1.0;
+  const int nwaves = (bm / wm) * (bn / wn);
+  if (nwaves < 1 || nwaves > hw.max_waves_per_wg) return -1.0;
+  const int epc = 16 / v.esize;
+  const int regs = wm * wn / 64 + 120;
+  int64_t occ = hw.lds_bytes_per_cu / pl.stage_bytes;
+  const int64_t by_regs = (hw.simds_per_cu * (hw.regs_per_lane / regs)) / nwaves;
+  if (by_regs < occ) occ = by_regs;
+  if (occ > 8) occ = 8;
+  if (occ < 1) return -1.0;
+  const double N = (double)v.cn * v.P * v.Q;
+  const double tiles = std::ceil((double)v.M / bm) * std::ceil(N / pl.tile_px);
+  const double cu_tiles = std::ceil(tiles / hw.compute_units);
+  const double resident = (double)occ < cu_tiles ? (double)occ : cu_tiles;
+  const double sc = std::ceil((double)v.cs / epc), nst = std::ceil((double)v.cc / pl.channels);
+  const double steps = std::ceil(pl.channels * v.cr * sc / 2.0);                   // two chunks each
+  double share = resident * nwaves / hw.simds_per_cu;
+  if (share < 1.0) share = 1.0;
+  const double peak_simd = (v.esize == 2 ? hw.mfma_tflops_16bit : hw.mfma_tflops_f32) * 1e6 / (double)(hw.compute_units * hw.simds_per_cu);
+  // the shift and mask of a B fragment's dwords: 8 vector instructions of 4 cycles per fragment
+  const double t_valu = steps * (wn / 32) * 12.0 * 4.0 / (hw.clock_ghz * 1e3) * share;
+  const double t_mfma = steps * (wm / 32) * (wn / 32) * (2.0 * 32 * 32 * 2 * epc) / peak_simd * share;
+  // staging: a round trip per batch of loads, and about a hundred vector instructions per 16-byte unit and thread
+  const double threads = 64.0 * nwaves, a_units = (double)bm * (2.0 * steps), p_units = (double)pl.channels * pl.rows * std::ceil((double)v.cw / epc);
+  const double a_batches = std::ceil(a_units / (6.0 * threads)), p_batches = std::ceil(p_units / (4.0 * threads));
+  const double t_load = (a_batches > p_batches ? a_batches : p_batches) * 1.5 * hw.latency_ns[0] * 1e-3 +
+                        (a_units + p_units) / threads * 100.0 * 4.0 / (hw.clock_ghz * 1e3) * share;
+  const double t_stage = (t_mfma > t_valu ? t_mfma : t_valu) + 0.3 * (t_mfma > t_valu ? t_valu : t_mfma) + t_load;
+  const double hbm_bw_cu = hw.bandwidth_gbs[0] * 1e3 / hw.compute_units;
+  const double t_epi = (double)bm * pl.tile_px * v.osize / (1.2 * hbm_bw_cu) * resident;
+  const double rounds = std::ceil(cu_tiles / (double)occ);
+  const double t_cu = rounds * (nst * t_stage + t_epi) + 1.5 * hw.latency_ns[0] * 1e-3;
+  const double bytes = (double)(pl.in_bytes + pl.w_bytes + pl.out_bytes);
+  const double t_hbm = bytes / (0.6 * hw.bandwidth_gbs[0] * 1e3);
+  return (t_cu > t_hbm ? t_cu : t_hbm) + 0.3 * (t_cu > t_hbm ? t_hbm : t_cu) + hw.launch_us;
+}
+
 // split > 1: the tiles that do not fill a whole round of compute units (all of them when there are fewer tiles
 // than units) are computed by `split` workgroups each, every one over 1/split of the k tiles; the parts of a
 // tile exchange fp32 partial tiles through device memory (measured: about a quarter of the HBM rate) and a
 // dependent launch clears their arrival counters first.  Infeasible if there is nothing to split.
 double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, int wm, int wn, int kg,
                int vm, int vn, int vec, int stages, int direct, int split) {
+  if (v.bsrc == B_CONV && direct && !vec) return split == 1 ? predict_rows(v, hw, bm, bn, wm, wn) : -1.0;
   if (v.bsrc == B_CONV && direct) return split == 1 ? predict_patch(v, hw, bm, bn, bk, wm, wn, kg, stages) : -1.0;
   if (split < 1 || (split > 1 && v.bsrc != B_KC && v.bsrc != B_NC)) return -1.0;
   if (vm < 1 || vn < 1 || bm < 1 || bn < 1 || bk < 1 || wm < 1 || wn < 1 || kg < 1 || stages < 1) return -1.0;
@@ -496,12 +538,12 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
     ++scored;
     // a compiled instance realises the state if it sits on the same lattice point: T_2 and T_1 of m, n
     // and k, and both V.  What the walk does not decide (LDS stages, direct staging, vector width) is
-    // whatever was compiled.  A patch-staged convolution instance has a k order and an LDS layout of its own
+    // whatever was compiled.  A patch- or row-staged convolution instance has a k order and an LDS layout of its own
     // (channels per stage, the halo patch), so only its spatial tiles are compared.
     for (int i = 0; i < g_num_instances; ++i) {
       const InstanceDesc& d = g_instances[i];
       if (d.bm != e.tile[0][0] || d.bn != e.tile[1][0] || d.wm != e.tile[0][1] || d.wn != e.tile[1][1]) continue;
-      if (!d.units && (d.bk != e.tile[2][0] || d.kg != e.tile[2][1] || d.vm != e.v[0] || d.vn != e.v[1])) continue;
+      if (!d.units && !d.conv_rows() && (d.bk != e.tile[2][0] || d.kg != e.tile[2][1] || d.vm != e.v[0] || d.vn != e.v[1])) continue;
       if (!usable(d, v, vec_ok)) continue;
       for (int split : kSplits) {
         if (split > 1 && c.opts.no_split_k) break;

@@ -67,6 +67,8 @@ struct KernelArgs {
   int32_t cC, cH, cW, cR, cS, cP, cQ, cStride, cPad;
   // patch-staged convolution only: images, LDS plan and tensor sizes in bytes (each < 2^31)
   int32_t cN, cApitch, cPatchRows, cStageBytes;
+  int32_t cRowPitch, cStageCh;     // row-staged convolution only: bytes of an input row in LDS, channels per stage
+  uint32_t cRec[7];                // ... and ceil(2^32 / d) (0 for d = 1) of what its kernel divides by
   int32_t cTilePx;                 // output pixels per workgroup (at most BN; whole output rows when they are shorter than BN)
   int64_t cInBytes, cWBytes, cOutBytes;
 };

@@ -6,6 +6,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <utility>
 
 #include "../../include/gensor.h"
 #include "host_common.hpp"
@@ -132,9 +133,63 @@ bool conv_patch_plan(const InstanceDesc& d, const GemmView& v, ConvPlan* plan, i
   return true;
 }
 
+bool conv_rows_plan(int bm, int bn, const GemmView& v, ConvRowsPlan* plan, int round_units) {
+  const int64_t lim = 0x7fffffffll - 64;      // 32-bit offsets, with room for the descriptor's alignment
+  const int64_t epc = 16 / v.esize;
+  ConvRowsPlan pl;
+  pl.in_bytes = v.cn * v.cc * v.ch * v.cw * v.esize;
+  pl.w_bytes = v.cc * v.cr * v.cs * v.M * v.esize;
+  pl.out_bytes = v.M * v.cn * v.P * v.Q * v.osize;
+  if (pl.in_bytes >= lim || pl.w_bytes >= lim || pl.out_bytes >= lim) return false;
+  const int64_t hp = v.ch + 2 * v.cpad;
+  const int64_t cus = round_units > 0 ? round_units : gensor_hw_mi355x()->compute_units;
+  const int64_t N = v.cn * v.P * v.Q;
+  if (hp * v.cn > lim || v.cw + 2 * v.cpad > lim / 64) return false;
+  const int64_t px = conv_tile_px(bn, N, v.Q, (v.M + bm - 1) / bm, cus);
+  pl.tile_px = (int)px;
+  // the most stacked padded input rows a pixel tile can touch: it covers out_rows output rows (one more than it fills
+  // unless it is whole rows) and starts at any row of an image
+  int64_t out_rows = px % v.Q == 0 ? px / v.Q : (px + v.Q - 2) / v.Q + 1;
+  if (out_rows > v.cn * v.P) out_rows = v.cn * v.P;
+  int64_t rows = 0;
+  for (int64_t first = 0; first < v.P; ++first) {
+    const int64_t last = first + out_rows - 1 < v.cn * v.P ? first + out_rows - 1 : v.cn * v.P - 1;
+    const int64_t r = (last / v.P) * hp + (last % v.P - first) * v.cstride + v.cr;
+    if (r > rows) rows = r;
+  }
+  pl.rows = (int)rows;
+  const int64_t xo = (v.cpad + epc - 1) / epc * epc;
+  const int64_t right = (v.cw + v.cpad + epc - 1) / epc * epc;
+  pl.row_pitch = (int)((xo + right) * v.esize);
+  const int64_t sc = (v.cs + epc - 1) / epc;
+  // Channels per stage: as many as fit an equal share of the LDS for every workgroup of a CU, up to three of them (a
+  // stage is a round trip to memory that only the CU's other workgroups cover), at least one
+  const int64_t wgs = ((v.M + bm - 1) / bm * ((N + px - 1) / px) + cus - 1) / cus;
+  const int64_t share = 160 * 1024 / (wgs < 3 ? wgs : 3) / 16 * 16;
+  auto bytes = [&](int64_t ch) {
+    int64_t chunks = (ch * v.cr * sc + 1) / 2 * 2 + 1;        // an odd number of 16-byte chunks
+    // (a lane's window may reach a chunk and a dword beyond the last row: read and cleared, never used)
+    return std::make_pair((int64_t)bm * chunks * 16, ch * rows * pl.row_pitch + (sc * 16 + 32));
+  };
+  auto total = [&](int64_t ch) { auto b = bytes(ch); return (b.first + b.second + 15) / 16 * 16; };
+  int64_t ch = v.cc;
+  while (ch > 1 && total(ch) > share) ch = (ch + 1) / 2;
+  // the kernel divides unit numbers by multiplying with a reciprocal: number times divisor stay below 2^31
+  const int64_t segs = (v.cw + epc - 1) / epc, chunks = ch * v.cr * sc + 1, slack = 10 * 256;
+  if (total(ch) > 160 * 1024 || sc > 15 || (bm * chunks + slack) * chunks > lim || (ch * rows * segs + slack) * (segs > rows ? segs : rows) > lim ||
+      (hp * v.cn + rows) * hp > lim || (v.Q + bn) * v.Q > lim || (v.P + bn) * v.P > lim)
+    return false;
+  pl.channels = (int)ch;
+  pl.a_pitch = (int)(bytes(ch).first / bm);
+  pl.stage_bytes = (int)total(ch);
+  if (plan) *plan = pl;
+  return true;
+}
+
 bool instance_serves(const InstanceDesc& d, const GemmView& v) {
   if (d.in_dtype != v.in_dtype || d.out_dtype != v.out_dtype || d.bsrc != v.bsrc || d.asrc != v.asrc) return false;
   if (d.units) return conv_patch_plan(d, v, nullptr);
+  if (d.conv_rows()) return conv_rows_plan(d.bm, d.bn, v, nullptr);
   return true;
 }
 
@@ -293,7 +348,7 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   }
   if (!d) return GENSOR_ERR_NO_SCHEDULE;
   if (d->vec && !vec_ok) return GENSOR_ERR_NO_SCHEDULE;          // schedule asks for vector accesses the operands cannot give
-  if (d->direct && !d->units && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
+  if (d->direct && v.bsrc != B_CONV && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
   if (s->split_k < 1 || !split_allowed(*d, v, s->split_k)) return GENSOR_ERR_NO_SCHEDULE;
   SplitPlan sp = split_plan(*d, v, s->split_k, s->round_units);
   if (sp.split > 1 && (!ws_aligned || workspace_bytes < sp.bytes)) return GENSOR_ERR_WORKSPACE;
@@ -329,6 +384,20 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
     a.tiles_n = (int32_t)((v.N + pl.tile_px - 1) / pl.tile_px);
     if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return GENSOR_ERR_UNSUPPORTED;
     a.cN = (int32_t)p->n; a.cApitch = pl.a_pitch; a.cPatchRows = pl.patch_rows; a.cStageBytes = pl.stage_bytes;
+    a.cInBytes = pl.in_bytes; a.cWBytes = pl.w_bytes; a.cOutBytes = pl.out_bytes;
+    a.batch = 1;
+  }
+  if (d->conv_rows()) {
+    ConvRowsPlan pl;
+    if (!conv_rows_plan(d->bm, d->bn, v, &pl, s->round_units)) return GENSOR_ERR_NO_SCHEDULE;
+    a.cTilePx = pl.tile_px;
+    a.tiles_n = (int32_t)((v.N + pl.tile_px - 1) / pl.tile_px);
+    if ((int64_t)a.tiles_m * a.tiles_n > INT32_MAX) return GENSOR_ERR_UNSUPPORTED;
+    a.cN = (int32_t)p->n; a.cApitch = pl.a_pitch; a.cPatchRows = pl.rows; a.cStageBytes = pl.stage_bytes;
+    a.cRowPitch = pl.row_pitch; a.cStageCh = pl.channels;
+    const int64_t epc = 16 / v.esize, sc = (v.cs + epc - 1) / epc;
+    const int64_t divisors[7] = {(pl.channels * v.cr * sc + 1) / 2 * 2, sc, (v.cw + epc - 1) / epc, pl.rows, v.ch + 2 * v.cpad, v.Q, v.P};
+    for (int i = 0; i < 7; ++i) a.cRec[i] = divisors[i] > 1 ? (uint32_t)(((1ll << 32) + divisors[i] - 1) / divisors[i]) : 0u;
     a.cInBytes = pl.in_bytes; a.cWBytes = pl.w_bytes; a.cOutBytes = pl.out_bytes;
     a.batch = 1;
   }

@@ -40,6 +40,13 @@ inline int64_t conv_tile_px(int64_t bn, int64_t N, int64_t Q, int64_t tiles_m, i
     if (cost(r * Q) < cost(best)) best = r * Q;
   return best;
 }
+// The same for the row-staged convolution: input rows as they lie, `channels` of them per LDS stage.
+struct ConvRowsPlan {
+  int a_pitch, rows, row_pitch, channels, stage_bytes, tile_px;
+  int64_t in_bytes, w_bytes, out_bytes;
+};
+// False if a row-staged instance with tile bm x bn cannot run the convolution in v.
+bool conv_rows_plan(int bm, int bn, const GemmView& v, ConvRowsPlan* plan, int round_units = 0);
 // False if instance d (a patch-staged convolution) cannot run the convolution in v.  round_units: the
 // compute units the tiles are dealt over (0: the MI355X's).
 bool conv_patch_plan(const InstanceDesc& d, const GemmView& v, ConvPlan* plan, int round_units = 0);

@@ -32,6 +32,11 @@ def _convp(dt, out, bm, bn, bkc, wm, wn, units, stages=2):
     return _inst(dt, out, bm, bn, bkc, wm, wn, 32, 1, 1, "CONV", 1, stages, 1, units)
 
 
+def conv_rows(d):
+    """Convolution with the input rows staged in LDS as they lie, any alignment (direct = 1, vec = 0 on the CONV source)."""
+    return d["bsrc"] == "CONV" and d["direct"] == 1 and d["vec"] == 0
+
+
 def _pad(v, row_bytes):
     if v == 1:
         return 0
@@ -205,6 +210,10 @@ def lattice():
                 out.append(_inst(dt, "f32", bm, bn, 64, wm, wn, 32, bsrc=bsrc, direct=1, asrc="MC"))
             for (bm, bn) in ((128, 256), (256, 128)):
                 out.append(_inst(dt, "f32", bm, bn, 64, 64, 64, 32, bsrc=bsrc, stages=3, direct=1, asrc="MC"))
+    # row-staged convolution: (BM filters, BN pixels, WM, WN); channels per stage are chosen per problem
+    for dt, odt in (("f16", "f32"), ("f16", "f16"), ("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")):
+        for (bm, bn, wm, wn) in ((64, 256, 64, 64), (64, 256, 32, 64), (32, 256, 32, 32), (32, 128, 32, 32)):
+            out.append(_inst(dt, odt, bm, bn, 16 if dt != "f32" else 8, wm, wn, 32, 1, 1, "CONV", vec=0, stages=1, direct=1))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],
@@ -214,6 +223,8 @@ def lattice():
 
 
 def cfg_type(d):
+    if conv_rows(d):
+        return "ConvRowsCfg<%s, %s, %d, %d, %d, %d>" % (CT[d["dt"]], CT[d["out"]], d["bm"], d["bn"], d["wm"], d["wn"])
     if d["units"]:
         return "ConvCfg<%s, %s, %d, %d, %d, %d, %d, %d, %d, %d>" % (
             CT[d["dt"]], CT[d["out"]], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["units"], d["stages"])

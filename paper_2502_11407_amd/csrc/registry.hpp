@@ -7,6 +7,7 @@
 #include <atomic>
 
 #include "conv_kernel.hpp"
+#include "conv_rows_kernel.hpp"
 #include "gemm_kernel.hpp"
 
 namespace gensor {
@@ -20,6 +21,7 @@ struct InstanceDesc {
   int vec, stages, direct;
   int lds_bytes, threads, kg;           // kg: k consumed per fragment read (lds_bytes 0: set per problem)
   int units;                            // patch-staged convolution: transpose units per thread
+  bool conv_rows() const { return bsrc == B_CONV && direct && !vec; }      // the row-staged convolution
   hipError_t (*launch)(const KernelArgs&, hipStream_t);
   hipError_t (*launch_split)(const KernelArgs&, hipStream_t);   // the same instance with split tiles; null if not compiled
 };
@@ -52,6 +54,20 @@ hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
   const unsigned grid = SPLIT ? (unsigned)a.whole + (tiles - (unsigned)a.whole) * (unsigned)a.split : tiles;
   hipLaunchKernelGGL((contraction_kernel<C, SPLIT>), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, st, a);
   return hipGetLastError();
+}
+
+// row-staged convolution: the LDS size depends on the problem
+template <typename C, bool ONE_CHUNK>
+hipError_t launch_conv_rows_as(const KernelArgs& a, hipStream_t st) {
+  static std::atomic<uint64_t> done{0};
+  hipError_t e = allow_dynamic_lds(conv_rows_kernel<C, ONE_CHUNK>, 160 * 1024, done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((conv_rows_kernel<C, ONE_CHUNK>), dim3((unsigned)a.tiles_m * (unsigned)a.tiles_n), dim3(C::THREADS), a.cStageBytes, st, a);
+  return hipGetLastError();
+}
+template <typename C>
+hipError_t launch_conv_rows(const KernelArgs& a, hipStream_t st) {
+  return a.cS <= C::EPC ? launch_conv_rows_as<C, true>(a, st) : launch_conv_rows_as<C, false>(a, st);
 }
 
 // patch-staged convolution: the LDS size depends on the problem (a.cStageBytes per LDS stage
