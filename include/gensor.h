@@ -245,8 +245,8 @@ size_t gensor_workspace_bytes(const gensor_schedule* s, const gensor_problem* p)
  * A is row-major [M][lda] (lda >= N, in elements) and x has N elements, both of in_dtype on
  * the device; y is fp32 on the device and is read only if beta != 0.  Products and sums are
  * carried in fp32.  A memory-bound streaming kernel with a fixed internal schedule (no
- * gensor_schedule): 16-byte vector loads when A and x are 16-byte aligned and lda is a whole
- * number of vectors, element loads otherwise.  Enqueued on hip_stream; nothing is allocated.
+ * gensor_schedule): 16-byte vector loads whatever the alignment of A, x and lda.  Enqueued on
+ * hip_stream; nothing is allocated.
  * INVALID_ARG for null pointers, non-positive extents or lda < N.
  */
 gensor_status gensor_gemv(gensor_dtype in_dtype, int64_t M, int64_t N, float alpha,

@@ -31,123 +31,96 @@ __device__ inline float wave_sum(float v) {
 }
 
 // ---------------------------------------------------------------------------------------
-// GEMV, y_i = alpha * sum_n A_in x_n + beta * y_i.  A workgroup of 4 waves owns 8 rows (two
-// per wave, so every x vector read from LDS is used twice); x is staged through LDS in
-// panels of PANEL elements; a lane reads 16-byte vectors of its rows, UNROLL of them in
-// flight per row.  The last partial vector of a row (N not a multiple of the vector) is
-// read element by element.  Needs A and x 16-byte aligned and lda a whole number of vectors.
+// GEMV, y_i = alpha * sum_n A_in x_n + beta * y_i.  Bound by reading A once: what it needs is enough bytes in flight on
+// every CU and no wait that another load does not cover.  A wave takes ROWS rows (every x vector it reads serves all of
+// them) and UNROLL 16-byte vectors of each per trip, all requested together with the x vectors; x comes through the L1
+// (it is used by every wave of the CU) rather than through LDS panels, whose fill and barrier stood in front of the
+// first product.  SPLIT waves share their rows, taking turns at the vectors: a trip then covers SPLIT times as much of
+// a row, and few rows still occupy the chip.  Rows may start anywhere: a 16-byte load takes any address (element
+// loads, used before for rows off the 16-byte boundaries, reached 2 TB/s).  The vectors counted here lie wholly inside
+// a row; what is left of it is read element by element.
+// Same-run A/B against 32 KB panels of x, fp16, inputs changing from call to call: 16384 x 16384 91.7 -> 75.7 us (7.1
+// TB/s), 16384 x 8192 51.5 -> 40.2, 16384 x 8191 128 -> 44, 4096 x 8192 12.9 -> 11.2, 1024 x 5003 25.4 -> 3.9,
+// 16384 x 1000 8.8 -> 6.6.
 // ---------------------------------------------------------------------------------------
-constexpr int GEMV_PANEL_BYTES = 32768;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;       // 16 bytes at any element's address
 
-// STREAM: the rows of A are read with the non-temporal hint.  A matrix larger than the 256 MiB Infinity
-// Cache only evicts itself from it (16384^2 fp16, 512 MiB: 98.7 -> 89.4 us with the hint); one that fits is
-// served from it on repeated calls and loses that with the hint (16384 x 8192: 41.8 -> 45.6 us), so the
-// launch sets it by the size of A.
+// STREAM: the rows of A are read with the non-temporal hint.  A matrix that does not fit the 256 MiB Infinity Cache
+// together with x and y only evicts itself from it (16384 x 16384 fp16: 81.4 -> 75.7 us with the hint, 16384 x 8192:
+// 43.6 -> 40.2); one that fits is served from it on repeated calls and loses that (4096 x 8192: 11.2 -> 12.4).
 template <bool STREAM>
 __device__ inline u32x4 load_row_vector(const char* p) {
-  if constexpr (STREAM) return __builtin_nontemporal_load((const u32x4*)p);
-  else return *(const u32x4*)p;
+  if constexpr (STREAM) return __builtin_nontemporal_load((const u32x4_any*)p);
+  else return *(const u32x4_any*)p;
 }
 
-template <typename T, bool STREAM>
-__global__ __launch_bounds__(256) void gemv_vec_kernel(const char* A, int64_t lda, const char* x, float* y, int M, int N,
-                                                       float alpha, float beta) {
-  constexpr int ES = ElemSize<T>::value, EPC = 16 / ES, PANEL = GEMV_PANEL_BYTES / ES, UNROLL = 4;
-  __shared__ __attribute__((aligned(16))) char xs[GEMV_PANEL_BYTES];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = blockIdx.x * 8 + wave * 2;
-  const bool ok0 = row0 < M, ok1 = row0 + 1 < M;
-  const char* a0 = A + (int64_t)(ok0 ? row0 : 0) * lda * ES;
-  const char* a1 = A + (int64_t)(ok1 ? row0 + 1 : 0) * lda * ES;
-  float acc0 = 0.f, acc1 = 0.f;
-  for (int p0 = 0; p0 < N; p0 += PANEL) {
-    const int pn = min(PANEL, N - p0);                 // elements of x in this panel
-    const int full = pn / EPC;                         // whole vectors
-    __syncthreads();                                   // the previous panel has been consumed
-    // all of a thread's vectors of the panel are requested before the first is written to LDS
-    constexpr int XV = GEMV_PANEL_BYTES / 16 / 256;
-    u32x4 xv[XV];
+template <typename T, bool STREAM, int SPLIT>
+__global__ __launch_bounds__(256) void gemv_kernel(const char* A, int64_t lda, const char* x, float* y, int M, int N, float alpha,
+                                                   float beta) {
+  constexpr int ES = ElemSize<T>::value, EPC = 16 / ES, ROWS = 2, UNROLL = 4;
+  __shared__ float part_sums[4][ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, part = wave % SPLIT;
+  const int row0 = (int)((blockIdx.x * (4 / SPLIT) + wave / SPLIT) * ROWS);
+  const char* a[ROWS];
+  float acc[ROWS];
 #pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      const int c = tid + i * 256;
-      xv[i] = u32x4{0u, 0u, 0u, 0u};
-      if (c < full) {
-        xv[i] = *(const u32x4*)(x + ((int64_t)p0 + (int64_t)c * EPC) * ES);
-      } else if (c < (pn + EPC - 1) / EPC) {           // ragged end of x: element by element, zero beyond N
-        for (int e = 0; e < pn - full * EPC; ++e) {
-          if constexpr (ES == 4) xv[i][e] = ((const uint32_t*)x)[p0 + c * EPC + e];
-          else xv[i][e >> 1] |= (uint32_t)((const uint16_t*)x)[p0 + c * EPC + e] << ((e & 1) * 16);
-        }
+  for (int r = 0; r < ROWS; ++r) {
+    a[r] = A + (int64_t)(row0 + r < M ? row0 + r : 0) * lda * ES;
+    acc[r] = 0.f;
+  }
+  const int full = N / EPC, rem = N - full * EPC;          // whole vectors of a row, elements behind them
+  for (int c = part * 64 + lane; c < full; c += 64 * SPLIT * UNROLL) {
+    u32x4 xv[UNROLL], av[UNROLL][ROWS];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int64_t off = (int64_t)(c + u * 64 * SPLIT) * 16;
+      xv[u] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) av[u][r] = u32x4{0u, 0u, 0u, 0u};
+      if (c + u * 64 * SPLIT < full) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) av[u][r] = load_row_vector<STREAM>(a[r] + off);
+        xv[u] = *(const u32x4_any*)(x + off);
       }
     }
 #pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      const int c = tid + i * 256;
-      if (c < (pn + EPC - 1) / EPC) *(u32x4*)(xs + c * 16) = xv[i];
+    for (int u = 0; u < UNROLL; ++u) {
+      float fx[EPC];
+      unpack_chunk<T>(xv[u], fx);
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) {
+        float fa[EPC];
+        unpack_chunk<T>(av[u][r], fa);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[r] = fmaf(fa[e], fx[e], acc[r]);
+      }
     }
+  }
+  if (part == 0 && lane < rem) {                           // lane e takes element e of the partial vector
+    const int64_t i = (int64_t)full * EPC + lane;
+    const float xl = to_float<T>(x, i);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r] = fmaf(to_float<T>(a[r], i), xl, acc[r]);
+  }
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum(acc[r]);
+  if constexpr (SPLIT > 1) {
+    if (lane == 0)
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) part_sums[wave][r] = acc[r];
     __syncthreads();
-    int c = lane;
-    for (; c + (UNROLL - 1) * 64 < full; c += UNROLL * 64) {
-      u32x4 va[UNROLL], vb[UNROLL];
+    if (part) return;
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const int64_t off = ((int64_t)p0 + (int64_t)(c + u * 64) * EPC) * ES;
-        va[u] = load_row_vector<STREAM>(a0 + off);
-        vb[u] = load_row_vector<STREAM>(a1 + off);
-      }
+    for (int r = 0; r < ROWS; ++r) {
+      acc[r] = part_sums[wave][r];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        float fx[EPC], fa[EPC], fb[EPC];
-        unpack_chunk<T>(*(const u32x4*)(xs + (c + u * 64) * 16), fx);
-        unpack_chunk<T>(va[u], fa);
-        unpack_chunk<T>(vb[u], fb);
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-          acc0 = fmaf(fa[e], fx[e], acc0);
-          acc1 = fmaf(fb[e], fx[e], acc1);
-        }
-      }
-    }
-    for (; c < full; c += 64) {
-      const int64_t off = ((int64_t)p0 + (int64_t)c * EPC) * ES;
-      float fx[EPC], fa[EPC], fb[EPC];
-      unpack_chunk<T>(*(const u32x4*)(xs + c * 16), fx);
-      unpack_chunk<T>(*(const u32x4*)(a0 + off), fa);
-      unpack_chunk<T>(*(const u32x4*)(a1 + off), fb);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) {
-        acc0 = fmaf(fa[e], fx[e], acc0);
-        acc1 = fmaf(fb[e], fx[e], acc1);
-      }
-    }
-    // ragged end of the rows: lane e takes element e of the partial vector
-    const int rem = pn - full * EPC;
-    if (lane < rem) {
-      const int64_t i = (int64_t)p0 + (int64_t)full * EPC + lane;
-      const float xv = to_float<T>(xs, full * EPC + lane);
-      acc0 = fmaf(to_float<T>(a0, i), xv, acc0);
-      acc1 = fmaf(to_float<T>(a1, i), xv, acc1);
+      for (int p = 1; p < SPLIT; ++p) acc[r] += part_sums[wave + p][r];
     }
   }
-  acc0 = wave_sum(acc0);
-  acc1 = wave_sum(acc1);
-  if (lane == 0) {
-    if (ok0) y[row0] = alpha * acc0 + (beta != 0.f ? beta * y[row0] : 0.f);
-    if (ok1) y[row0 + 1] = alpha * acc1 + (beta != 0.f ? beta * y[row0 + 1] : 0.f);
+  if (lane < ROWS && row0 + lane < M) {
+    const float sum = lane ? acc[1] : acc[0];
+    y[row0 + lane] = alpha * sum + (beta != 0.f ? beta * y[row0 + lane] : 0.f);
   }
-}
-
-// any alignment: one wave per row, element loads
-template <typename T>
-__global__ __launch_bounds__(256) void gemv_scalar_kernel(const char* A, int64_t lda, const char* x, float* y, int M, int N,
-                                                          float alpha, float beta) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= M) return;                                // whole waves leave together; no barrier follows
-  float acc = 0.f;
-  for (int n = lane; n < N; n += 64) acc = fmaf(to_float<T>(A, (int64_t)row * lda + n), to_float<T>(x, n), acc);
-  acc = wave_sum(acc);
-  if (lane == 0) y[row] = alpha * acc + (beta != 0.f ? beta * y[row] : 0.f);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -248,20 +221,17 @@ __global__ __launch_bounds__(256) void avgpool_direct_kernel(const void* in, voi
   store_out<OutT>(out, idx, acc / (float)(F * F));
 }
 
+// Four waves share two rows where that leaves each a trip's worth of vectors (256 vectors a row: at 250 both splits take
+// 10.7-10.9 us for 16384 rows, at 475 the shared rows 20.8 against 22.7 us, at 125 9.2 against 7.0).
 template <typename T>
 hipError_t launch_gemv(const void* A, int64_t lda, const void* x, float* y, int64_t M, int64_t N, float alpha, float beta, hipStream_t st) {
   constexpr int ES = ElemSize<T>::value, EPC = 16 / ES;
-  const bool vec = ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(x)) & 15u) == 0 && lda % EPC == 0;
-  const bool stream = M * lda * ES > (int64_t)256 * 1024 * 1024;      // larger than the Infinity Cache
-  if (vec && stream)
-    hipLaunchKernelGGL((gemv_vec_kernel<T, true>), dim3((unsigned)((M + 7) / 8)), dim3(256), 0, st, (const char*)A, lda, (const char*)x, y,
-                       (int)M, (int)N, alpha, beta);
-  else if (vec)
-    hipLaunchKernelGGL((gemv_vec_kernel<T, false>), dim3((unsigned)((M + 7) / 8)), dim3(256), 0, st, (const char*)A, lda, (const char*)x, y,
-                       (int)M, (int)N, alpha, beta);
-  else
-    hipLaunchKernelGGL(gemv_scalar_kernel<T>, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const char*)A, lda, (const char*)x, y,
-                       (int)M, (int)N, alpha, beta);
+  const bool stream = M * lda * ES + N * ES + M * 4 > (int64_t)256 * 1024 * 1024;
+  const bool shared = N / EPC >= 256;
+  const dim3 grid((unsigned)(shared ? (M + 1) / 2 : (M + 7) / 8)), block(256);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, (const char*)A, lda, (const char*)x, y, (int)M, (int)N, alpha, beta); };
+  if (shared) stream ? go(gemv_kernel<T, true, 4>) : go(gemv_kernel<T, false, 4>);
+  else stream ? go(gemv_kernel<T, true, 1>) : go(gemv_kernel<T, false, 1>);
   return hipGetLastError();
 }
 
@@ -309,7 +279,7 @@ using namespace gensor;
 extern "C" gensor_status gensor_gemv(gensor_dtype in_dtype, int64_t M, int64_t N, float alpha, const void* A, int64_t lda,
                                      const void* x, float beta, float* y, void* hip_stream) {
   if (!A || !x || !y || M <= 0 || N <= 0 || lda < N) return GENSOR_ERR_INVALID_ARG;
-  if (M > INT32_MAX - 8 || N > INT32_MAX - GEMV_PANEL_BYTES) return GENSOR_ERR_UNSUPPORTED;
+  if (M > INT32_MAX - 8 || N > INT32_MAX - 32768) return GENSOR_ERR_UNSUPPORTED;
   hipError_t e;
   switch (in_dtype) {
     case GENSOR_F32: e = launch_gemv<f32_t>(A, lda, x, y, M, N, alpha, beta, (hipStream_t)hip_stream); break;

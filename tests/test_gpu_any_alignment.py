@@ -65,3 +65,24 @@ def test_tiny_operands_bit_exact(gs, dtype, M, N, K):
         C = gs.empty_device((M, N)).fill_(float("nan"))
         gs.gemm(gs.gemm_problem(dtype, M, N, K, 0, tb), gs.to_device(A, dtype), gs.to_device(B, dtype), C)
         assert np.array_equal(gs.to_host_f64(C), ops.gemm(A, B, dtype, transB=tb))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("M", [1, 2, 3, 9])
+@pytest.mark.parametrize("vectors,extra", [(0, 1), (1, 0), (63, 3), (255, 1), (256, 0), (257, 1), (1024, 1), (1300, 3)])
+def test_gemv_at_any_alignment_bit_exact(gs, dtype, M, vectors, extra):
+    """Rows around the length from which four waves share them, at odd offsets and leading dimensions, with infinities
+    around the matrix and the vector."""
+    import torch
+    N = vectors * (4 if dtype == "f32" else 8) + extra
+    A, x = inputs.small_ints(81, (M, N), dtype, -2, 2), inputs.small_ints(82, (1, N), dtype, -2, 2)
+    want = ops.gemv(A, x[0], dtype)
+    for offset, pad in ((0, 0), (1, 0), (3, 5)):
+        dA, dx = _embed(gs, A, dtype, offset, pad, 2), _embed(gs, x, dtype, 2 * offset + 1, 0, 1)[0]
+        y = torch.full((M,), float("nan"), dtype=torch.float32, device="cuda")
+        gs.gemv(dtype, dA, dx, y, lda=N + pad)
+        assert np.array_equal(gs.to_host_f64(y), want), (offset, pad)
+        y0 = inputs.small_ints(83, (M,), "f32", -4, 4)
+        y = gs.to_device(y0, "f32")
+        gs.gemv(dtype, dA, dx, y, 2.0, -1.0, lda=N + pad)
+        assert np.array_equal(gs.to_host_f64(y), 2.0 * want - y0)
