@@ -380,9 +380,8 @@ double predict_rows(const GemmView& v, const gensor_hw& hw, int bm, int bn, int 
 }
 
 // split > 1: the tiles that do not fill a whole round of compute units (all of them when there are fewer tiles
-// than units) are computed by `split` workgroups each, every one over 1/split of the k tiles; the parts of a
-// tile exchange fp32 partial tiles through device memory (measured: about a quarter of the HBM rate) and a
-// dependent launch clears their arrival counters first.  Infeasible if there is nothing to split.
+// than units) are computed by `split` workgroups each, every one over 1/split of the k tiles; the parts leave fp32
+// partial tiles in device memory and a dependent launch adds them up.  Infeasible if there is nothing to split.
 double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, int wm, int wn, int kg,
                int vm, int vn, int vec, int stages, int direct, int split) {
   if (v.bsrc == B_CONV && direct && !vec) return split == 1 ? predict_rows(v, hw, bm, bn, wm, wn) : -1.0;
@@ -474,22 +473,17 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // beyond four waves per SIMD nothing more is hidden
   double hide = resident * nwaves / hw.simds_per_cu;
   if (hide > 4.0) hide = 4.0;
-  // a part writes its partial tile, and one part in `split` reads the others' and stores C
-  const double t_swap = bm * bn * 4.0 / (0.8 * hbm_bw_cu);
-  // the exchange is a chain of memory round trips whatever the tile size: the slot stores written through and awaited,
-  // the arrival count, the other parts' slots fetched past the L2 (measured: a two-way split of the 128x128 tiles of
-  // 8192x768x3072 takes 9 us longer than its halved k loop explains)
-  const double t_chain = 10.0 * hw.latency_ns[0] * 1e-3;
-  const double t_cu = cu_whole * (t_main + t_epi / hide) +
-                      cu_part * (t_part + t_chain + t_swap + (t_swap * (split - 1) + t_epi) / split / hide) + t_fill;
+  // a part stores its partial tile
+  const double t_swap = bm * bn * 4.0 / (1.2 * hbm_bw_cu);
+  const double t_cu = cu_whole * (t_main + t_epi / hide) + cu_part * (t_part + t_swap / hide) + t_fill;
   const double bytes_total = (double)v.batch * ((double)e * ((double)v.M * v.K + (double)v.K * v.N) + (double)eo * v.M * v.N);
-  const double bytes_swap = split > 1 ? (tiles - whole) * (2.0 * split - 1.0) * bm * bn * 4.0 : 0.0;
+  const double bytes_swap = split > 1 ? (tiles - whole) * split * bm * bn * 4.0 : 0.0;       // written once, read once by the launch that adds up
   // (the store-bound shapes stream at 6.5-6.9 TB/s, measured)
-  const double t_hbm = bytes_total / (0.9 * hw.bandwidth_gbs[0] * 1e3) + bytes_swap / (0.25 * hw.bandwidth_gbs[0] * 1e3);
+  const double t_hbm = (bytes_total + bytes_swap) / (0.9 * hw.bandwidth_gbs[0] * 1e3);
   // soft roofline: the smaller of the two limits still costs a fraction (imperfect overlap)
   const bool prepass = v.pointwise && v.cstride > 1 && v.bsrc != B_NCS2;   // the input is compacted by a dependent launch of its own
   return (t_cu > t_hbm ? t_cu : t_hbm) + 0.2 * (t_cu > t_hbm ? t_hbm : t_cu) + hw.launch_us * (prepass ? 3.5 : 1.0) +
-         (split > 1 ? hw.launch_us : 0.0);
+         (split > 1 ? 2.0 * hw.launch_us + bytes_swap / (0.5 * hw.bandwidth_gbs[0] * 1e3) : 0.0);
 }
 
 double predict_instance(const GemmView& v, const gensor_hw& hw, const InstanceDesc& d, int split = 1) {
