@@ -376,6 +376,18 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   if ((int64_t)a.tiles_m * a.tiles_n * a.batch > INT32_MAX) return GENSOR_ERR_UNSUPPORTED;
   a.split = sp.split;
   a.whole = (int32_t)sp.whole;
+  // Read ahead where the launch moves more than the 256 MiB Infinity Cache holds (its operands then come from memory; from
+  // that cache they come soon enough, and the wait at the end of each wave costs 2-10 %: 96 x 1024 x 1024 x 64 with fp16
+  // output 61 -> 69 us, 48 x 768 x 768 x 64 21.1 -> 23.4), a batch is one or two k tiles deep, an XCD works through whole batches (its range of tiles is
+  // contiguous when the tile count is a multiple of 8) and the batch's workgroups cover the operands of the next with one
+  // vector a thread; only the tiles such launches end in are compiled for it (Cfg::HAS_AHEAD); dense matrices only, so that every byte of the range is an element.
+  if (v.batch > 1 && v.K <= 2 * d->bk && d->vec && sp.split == 1 && (v.bsrc == B_KC || v.bsrc == B_NC)) {
+    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
+    const int64_t wa = strideA && lda == (v.asrc == A_KC ? v.K : v.M) ? v.M * v.K * v.esize : 0;
+    const int64_t wb = strideB && ldb == (v.bsrc == B_KC ? v.K : v.N) ? v.N * v.K * v.esize : 0;
+    const int64_t moved = v.batch * (wa + wb + v.M * v.N * v.osize);
+    if (tiles * v.batch % 8 == 0 && moved > (int64_t)256 * 1024 * 1024 && wa + wb <= tiles * d->threads * 16) { a.ahead_a = wa; a.ahead_b = wb; }
+  }
   a.partials = (float*)workspace;
   if (d->units) {
     ConvPlan pl;

@@ -44,15 +44,18 @@ hipError_t allow_dynamic_lds(K kernel, int bytes, std::atomic<uint64_t>& done) {
   return hipSuccess;
 }
 
-template <typename C, bool SPLIT = false>
+template <typename C, bool SPLIT = false, bool AHEAD = false>
 hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
+  if constexpr (C::HAS_AHEAD && !SPLIT && !AHEAD) {
+    if (a.ahead_a + a.ahead_b > 0) return launch_instance<C, false, true>(a, st);
+  }
   static std::atomic<uint64_t> done{0};
-  hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT>, C::LDS_BYTES, done);
+  hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT, AHEAD>, C::LDS_BYTES, done);
   if (e != hipSuccess) return e;
   // one workgroup per whole tile and, in a split launch, a.split per tile behind them
   const unsigned tiles = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.batch;
   const unsigned grid = SPLIT ? (unsigned)a.whole + (tiles - (unsigned)a.whole) * (unsigned)a.split : tiles;
-  hipLaunchKernelGGL((contraction_kernel<C, SPLIT>), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, st, a);
+  hipLaunchKernelGGL((contraction_kernel<C, SPLIT, AHEAD>), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, st, a);
   return hipGetLastError();
 }
 
