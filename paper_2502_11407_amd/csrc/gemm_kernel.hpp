@@ -57,6 +57,7 @@ struct KernelArgs {
   int64_t lda, ldb, ldc;           // elements
   int64_t strideA, strideB, strideC;
   float alpha, beta;
+  int32_t through;                 // C is stored write-through (only where beta is 0)
   int32_t tiles_m, tiles_n, batch;
   int32_t panel;                   // tile rows per panel in the workgroup->tile map
   int64_t ahead_a, ahead_b;        // bytes of the next batch's A and B that this batch's workgroups read ahead (0: none)
@@ -1120,20 +1121,20 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(Cb + ((int64_t)m0 * args.ldc + n0) * OS), 0,
         clamp_records(((int64_t)(rows_valid - 1) * args.ldc + cols_valid) * OS), RSRC_FLAGS);
-    // C is stored with the write-through cache policy (sc1): every line goes to memory at once instead of
-    // lying dirty in the L2 until it is evicted.  Measured against write-back: 10-15 % faster on the
-    // store-bound shapes (96 x 1024 x 1024 x 64: 79 -> 70 us), 1-2 % on the 4096^3 and GPT-2 shapes, 0.5-2.5 %
+    // C is stored with the write-through cache policy (sc1) unless the host says otherwise (args.through): every line goes to
+    // memory at once instead of lying dirty in the L2 until it is evicted.  Measured against write-back: 10-15 % faster
+    // on the store-bound shapes (96 x 1024 x 1024 x 64: 79 -> 70 us), 1-2 % on the 4096^3 and GPT-2 shapes, 0.5-2.5 %
     // slower on launches of many rounds of long tiles (8192^3, 65536 x 4096 x 1024), where a write-back L2
     // drains one tile's stores under the next tile's loop.  The policy is an immediate of the store
-    // instruction; choosing it at run time (two copies of this loop behind a branch) cost every shape 1-2 %.
-    constexpr int STORE_POLICY = 16;
+    // instruction: it is chosen where the beta path is, once per block.
     // One store costs an accumulator read, the scaling, one add and the store: the column part of the offset (or
     // an out-of-range one: adding a row offset below 2^31 keeps it out of range) is selected once per block column,
     // the row part is a per-lane base plus a multiple of the row pitch that is the same for the whole wave, and
     // whether C is read (beta) is decided once per block, not per element.
     const uint32_t pitch = (uint32_t)args.ldc * OS;
-    auto store_block = [&](int bi, int bj, uint32_t lane_off, auto beta_tag) {
+    auto store_block = [&](int bi, int bj, uint32_t lane_off, auto beta_tag, auto policy_tag) {
       constexpr bool with_beta = decltype(beta_tag)::value;
+      constexpr int STORE_POLICY = decltype(policy_tag)::value;
 #pragma unroll
       for (int v = 0; v < MF::NACC; ++v) {
         const int r = (MB == 32) ? 8 * (v / 4) + (v % 4) : v;      // row inside the block, less the lane group's 4 * fgrp
@@ -1160,8 +1161,11 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
 #pragma unroll
       for (int bi = 0; bi < C::MBLK; ++bi) {
         const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + 4 * fgrp) * pitch;
-        if (beta != 0.f) store_block(bi, bj, lane_off, std::true_type{});
-        else store_block(bi, bj, lane_off, std::false_type{});
+        constexpr std::integral_constant<int, 16> write_through{};
+        constexpr std::integral_constant<int, 0> write_back{};
+        if (args.through) store_block(bi, bj, lane_off, std::false_type{}, write_through);
+        else if (beta == 0.f) store_block(bi, bj, lane_off, std::false_type{}, write_back);
+        else store_block(bi, bj, lane_off, std::true_type{}, write_back);
       }
     }
   }

@@ -368,6 +368,14 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   a.lda = lda; a.ldb = ldb; a.ldc = ldc;
   a.strideA = strideA; a.strideB = strideB; a.strideC = strideC;
   a.alpha = alpha; a.beta = beta;
+  // Write-through stores, except where rows of C that do not start on 128-byte lines make a large output: its partial lines
+  // then go to memory one by one, where a write-back L2 joins them (outputs changing from call to call: 8192 x 8200 x 128
+  // fp32 153 -> 70 us, 32 x 1000 x 1000 x 64 fp32 61 -> 36, with fp16 output 24.4 -> 20.4, 8192 x 3000 x 768 77.5 -> 66.8).
+  // Smaller ones stay with write-through (6000 x 2500 fp32, 60 MB: 33.0 against 34.8 us; 4000 x 1000: 10.8 against
+  // 11.8; 16-bit outputs of 8-30 MB: within 4 % either way), aligned rows too (48 x 768 x 768 x 64: 21.7 against 27.4).
+  const int64_t c_bytes = v.batch * v.M * v.N * v.osize;
+  const bool partial_lines = (ldc * v.osize) % 128 != 0 && c_bytes > (v.osize == 2 ? 32ll : 64ll) * 1024 * 1024;
+  a.through = beta == 0.f && !partial_lines;
   a.tiles_m = (int32_t)((v.M + d->bm - 1) / d->bm);
   a.tiles_n = (int32_t)((v.N + d->bn - 1) / d->bn);
   a.batch = (int32_t)v.batch;

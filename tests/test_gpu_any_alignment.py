@@ -86,3 +86,15 @@ def test_gemv_at_any_alignment_bit_exact(gs, dtype, M, vectors, extra):
         y = gs.to_device(y0, "f32")
         gs.gemv(dtype, dA, dx, y, 2.0, -1.0, lda=N + pad)
         assert np.array_equal(gs.to_host_f64(y), 2.0 * want - y0)
+
+
+@pytest.mark.parametrize("beta", [0.0, -1.0])
+def test_large_output_with_rows_off_the_lines_bit_exact(gs, beta):
+    """More than 32 MiB of 16-bit output whose rows do not start on 128-byte lines: stored write-back."""
+    M, N, K = 4099, 4104, 16
+    A, B = inputs.small_ints(91, (M, K), "f16", -3, 3), inputs.small_ints(92, (N, K), "f16", -3, 3)
+    C0 = inputs.small_ints(93, (M, N), "f16", -4, 4)
+    C = gs.to_device(C0, "f16")
+    gs.gemm(gs.gemm_problem("f16", M, N, K, 0, 1, 1, "f16"), gs.to_device(A, "f16"), gs.to_device(B, "f16"), C, 1.0, beta)
+    want = ops.gemm(A, B, "f16", transB=1, alpha=1.0, beta=beta, C0=C0.astype(np.float32))
+    assert np.array_equal(gs.to_host_f64(C), want)
