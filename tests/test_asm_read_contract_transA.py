@@ -25,6 +25,6 @@ def test_every_direct_staged_transA_instance_waits_for_its_reads(tmp_path):
 
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         for idx, res in ex.map(one, insts):
-            assert len(res) == 2, idx
+            assert len(res) >= 2, idx
             for violations, reads in res:
                 assert reads > 0 and not violations, "instance %d: %s" % (idx, violations[:3])
