@@ -363,7 +363,8 @@ double predict_rows(const GemmView& v, const gensor_hw& hw, int bm, int bn, int 
   const double peak_simd = (v.esize == 2 ? hw.mfma_tflops_16bit : hw.mfma_tflops_f32) * 1e6 / (double)(hw.compute_units * hw.simds_per_cu);
   // the shift and mask of a B fragment's dwords: 8 vector instructions of 4 cycles per fragment
   const double t_valu = steps * (wn / 32) * 12.0 * 4.0 / (hw.clock_ghz * 1e3) * share;
-  const double t_mfma = steps * (wm / 32) * (wn / 32) * (2.0 * 32 * 32 * 2 * epc) / peak_simd * share;
+  // (fp32: measured at 1.3-1.6 of what its MFMAs take)
+  const double t_mfma = steps * (wm / 32) * (wn / 32) * (2.0 * 32 * 32 * 2 * epc) / peak_simd * share * (v.esize == 4 ? 1.5 : 1.0);
   // staging: a round trip per batch of loads, and about a hundred vector instructions per 16-byte unit and thread
   const double threads = 64.0 * nwaves, a_units = (double)bm * (2.0 * steps), p_units = (double)pl.channels * pl.rows * std::ceil((double)v.cw / epc);
   const double a_batches = std::ceil(a_units / (6.0 * threads)), p_batches = std::ceil(p_units / (4.0 * threads));
@@ -427,10 +428,11 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double t_lds = e * kp * ((double)bm * (bn / wn) * conflict_ways(v, hw, bk, 0, vm) +
                                  (double)bn * (bm / wm) * conflict_ways(v, hw, bk, 1, vn) + (bm + bn)) / lds_bw;
   const double l2_bw = hw.l2_bandwidth_gbs * 1e3 / hw.compute_units;
-  const double gather = (v.bsrc == B_CONV && !direct) ? 16.0 : 1.0;     // element-wise loads and their index arithmetic
-  // operands off the vector boundaries: the same loads, each spread over two cache lines; the gather's filters, too, but
-  // there the gather's own element loads set the pace
-  const double scalar = vec ? 1.0 : (v.bsrc == B_CONV ? 6.0 : 2.0);
+  // element-wise loads and their index arithmetic (16-bit elements at 16 were priced 0.6-0.8 of the measured time)
+  const double gather = (v.bsrc == B_CONV && !direct) ? (e == 2 ? 24.0 : 16.0) : 1.0;
+  // operands off the vector boundaries: the same loads, each spread over two cache lines (the filters of a gather, too, but
+  // there the gather's own element loads set the pace)
+  const double scalar = vec ? 1.0 : (v.bsrc == B_CONV ? 1.2 : 2.0);
   const double t_feed = scalar * e * kp * (bm + gather * bn) / l2_bw;
   double par = resident * nwaves / hw.simds_per_cu;
   if (par > 4.0) par = 4.0;
@@ -563,6 +565,9 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
       const int cand[8] = {d.bm, d.bn, d.bk, d.wm, d.wn, d.kg, d.vm, d.vn};
       double dist = 0.0;
       for (int k = 0; k < 8; ++k) dist += std::fabs(std::log2((double)cand[k]) - std::log2((double)target[k]));
+      // convolution loaders have k orders and LDS layouts of their own, so their coordinates say little about how near they
+      // are (fewer than 17 filters: no state holds a loader's tile): the cheapest is taken
+      if (v.bsrc == B_CONV) dist = us;
       if (!have || dist < bd || (dist == bd && us < best_us)) { have = true; bd = dist; best = &d; best_us = us; }
     }
   }
