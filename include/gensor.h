@@ -78,7 +78,7 @@ typedef struct {
   int32_t vthread[2];         /* V for m and n: interleave depth of that operand's LDS tile (see above) */
   int32_t stages;             /* LDS buffers: 1, 2, or a ring of 3 (two k tiles in flight) */
   int32_t unroll;             /* MFMA k-steps unrolled per LDS stage = BK / (k per fragment) */
-  int32_t vec_bytes;          /* width of one global access: 16, or the element size (scalar path) */
+  int32_t vec_bytes;          /* 16: operands on 16-byte boundaries with rows of whole vectors; the element size: any alignment */
   int32_t direct_lds;         /* 1: global->LDS loads bypass registers */
   int32_t split_k;            /* 1..16 workgroups per tile of the last, partly filled round (GEMM/BMM; see gensor_gemm) */
   int32_t wg_remap;           /* tile rows per panel in the workgroup->tile map (L2 reuse per XCD) */
