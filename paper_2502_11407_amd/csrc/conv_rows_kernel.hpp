@@ -33,6 +33,34 @@ struct ConvRowsCfg {
   static_assert(BM % WM == 0 && BN % WN == 0 && WM % MB == 0 && WN % MB == 0, "tiles");
 };
 
+// Byte offset of an output pixel's window in the staged rows: first row counted from the stage's first, first column
+// counted from the first one in LDS.
+__host__ __device__ inline uint32_t rows_window(int row, int col, int row_pitch, int es) { return (uint32_t)(row * row_pitch + col * es); }
+
+// The chunks of a stage relative to a window, in the order channel, filter row, chunk of the row.  An odd number of chunks has one
+// more behind the last (the MFMA takes two): it has no rows of its own and is read from the last chunk's, for its value is cleared.
+// ONE_CHUNK: a filter row is one chunk.
+template <bool ONE_CHUNK>
+struct RowsWalk {
+  int sc = 0, r = 0;
+  uint32_t off = 0;
+  __host__ __device__ void advance(int R, int SC, int row_pitch, int chan_pitch) {
+    if constexpr (ONE_CHUNK) {
+      off += (uint32_t)row_pitch;
+    } else {
+      off += 16;
+      if (++sc < SC) return;
+      sc = 0;
+      off += (uint32_t)(row_pitch - 16 * SC);
+    }
+    if (++r == R) { r = 0; off += (uint32_t)(chan_pitch - R * row_pitch); }
+  }
+  static __host__ __device__ uint32_t last(int channels, int R, int SC, int row_pitch, int chan_pitch) {
+    return (uint32_t)((channels - 1) * chan_pitch + (R - 1) * row_pitch + 16 * (SC - 1));
+  }
+  __host__ __device__ uint32_t at(uint32_t last_off) const { return off < last_off ? off : last_off; }
+};
+
 // ONE_CHUNK: a filter row is one chunk (at most 8 columns, 4 for fp32), whose mask is the same throughout.
 template <typename C, bool ONE_CHUNK>
 __global__ __launch_bounds__(C::THREADS, C::MBLK * C::NBLK > 2 ? 2 : 4) void conv_rows_kernel(const KernelArgs args) {
@@ -186,7 +214,7 @@ __global__ __launch_bounds__(C::THREADS, C::MBLK * C::NBLK > 2 ? 2 : 4) void con
     const int dp = g_first % P + dg;                     // ... and from the first row of its first image
     const int di = divide(dp, args.cRec[6]), p = dp - di * P, img = g_first / P + di;
     o_at[bj] = (uint32_t)(img * args.M * PQ + p * Q + q);
-    const uint32_t at = (uint32_t)((img * Hp + p * stride - R0) * row_pitch + (q * stride - pad + XO) * ES);
+    const uint32_t at = rows_window(img * Hp + p * stride - R0, q * stride - pad + XO, row_pitch, ES);
     b_at[bj] = at & ~3u;
     b_odd[bj] = at & 2u;
   }
@@ -197,27 +225,17 @@ __global__ __launch_bounds__(C::THREADS, C::MBLK * C::NBLK > 2 ? 2 : 4) void con
   auto compute = [&](int ch) {
     const int nch = ch * R * SC;
     const int steps = (nch + 1) >> 1;
-    // where the lane's chunk of the next step lies relative to its window: chunk, filter row, channel
-    int sc = 0, r = 0;
-    uint32_t off = 0;
-    auto advance = [&]() {
-      if constexpr (ONE_CHUNK) {
-        off += (uint32_t)row_pitch;
-      } else {
-        off += 16;
-        if (++sc < SC) return;
-        sc = 0;
-        off += (uint32_t)(row_pitch - 16 * SC);
-      }
-      if (++r == R) { r = 0; off += (uint32_t)(chan_pitch - R * row_pitch); }
-    };
+    RowsWalk<ONE_CHUNK> walk;                            // where the lane's chunk of the next step lies
+    auto advance = [&]() { walk.advance(R, SC, row_pitch, chan_pitch); };
+    const uint32_t last_off = walk.last(ch, R, SC, row_pitch, chan_pitch);
     if (fgrp) advance();
     int valid[2] = {S, S};                               // elements of the filter row in the lane's chunk
     GENSOR_LDS char* arow = abase + (wave_m * C::WM + frow) * a_pitch + fgrp * 16;
     auto read = [&](int buf, int step) {
-      if constexpr (!ONE_CHUNK) valid[buf] = S - sc * EPC;
+      if constexpr (!ONE_CHUNK) valid[buf] = S - walk.sc * EPC;
 #pragma unroll
       for (int bi = 0; bi < C::MBLK; ++bi) af[buf][bi] = *(GENSOR_LDS u32x4*)(arow + bi * MB * a_pitch + step * 32);
+      const uint32_t off = walk.at(last_off);
 #pragma unroll
       for (int bj = 0; bj < C::NBLK; ++bj) {
         GENSOR_LDS uint32_t* src = (GENSOR_LDS uint32_t*)(pbase + b_at[bj] + off);

@@ -168,7 +168,8 @@ bool conv_rows_plan(int bm, int bn, const GemmView& v, ConvRowsPlan* plan, int r
   const int64_t share = 160 * 1024 / (wgs < 3 ? wgs : 3) / 16 * 16;
   auto bytes = [&](int64_t ch) {
     int64_t chunks = (ch * v.cr * sc + 1) / 2 * 2 + 1;        // an odd number of 16-byte chunks
-    // (a lane's window may reach a chunk and a dword beyond the last row: read and cleared, never used)
+    // (the last chunk of a window's row may reach 15 bytes beyond the last row, and its fifth dword four more: read and
+    // cleared, never used)
     return std::make_pair((int64_t)bm * chunks * 16, ch * rows * pl.row_pitch + (sc * 16 + 32));
   };
   auto total = [&](int64_t ch) { auto b = bytes(ch); return (b.first + b.second + 15) / 16 * 16; };
