@@ -326,6 +326,18 @@ gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_m
   return st;
 }
 
+// The kernels address a workgroup tile with 32-bit offsets.
+bool offsets_fit(const InstanceDesc& d, const GemmView& v, int64_t lda, int64_t ldb, int64_t ldc) {
+  const int64_t lim = 0x7fffffffll;
+  if (v.asrc == A_KC && (int64_t)(d.bm + 1) * lda * v.esize >= lim) return false;
+  if (v.asrc == A_MC && ((int64_t)(d.bk + 1) * lda + d.bm) * v.esize >= lim) return false;
+  // (the convolution epilogues address the output with 64-bit indices and never use ldc)
+  if (v.bsrc != B_CONV && (int64_t)(d.bm + 1) * ldc * v.osize >= lim) return false;
+  if (v.bsrc == B_KC && (int64_t)(d.bn + 1) * ldb * v.esize >= lim) return false;
+  if ((v.bsrc == B_NC || v.bsrc == B_NCS2) && ((int64_t)(d.bk + 1) * ldb + d.bn) * v.esize >= lim) return false;
+  return true;
+}
+
 gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmView& v, float alpha,
                   const void* A, int64_t lda, int64_t strideA, const void* B, int64_t ldb, int64_t strideB,
                   float beta, void* C, int64_t ldc, int64_t strideC, void* workspace, size_t workspace_bytes, void* stream) {
@@ -347,20 +359,28 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
     if (st != GENSOR_OK) return st;
     d = find_instance(s, v);
   }
+  if (d && !d->vec && (v.bsrc == B_KC || v.bsrc == B_NC) && !offsets_fit(*d, v, lda, ldb, ldc)) {
+    // Rows too far apart for this tile's offsets (a schedule does not know the leading dimensions): the smallest tile of the
+    // instances at any alignment takes about twice as long ones.
+    for (int i = 0; i < g_num_instances; ++i) {
+      const InstanceDesc& e = g_instances[i];
+      if (e.vec || e.mb != 16 || !instance_serves(e, v) || !offsets_fit(e, v, lda, ldb, ldc)) continue;
+      const int32_t panel = s->wg_remap, units = s->round_units;
+      schedule_from_instance(e, &local);
+      local.wg_remap = panel;
+      local.round_units = units;
+      s = &local;
+      d = &e;
+      break;
+    }
+  }
   if (!d) return GENSOR_ERR_NO_SCHEDULE;
   if (d->vec && !vec_ok) return GENSOR_ERR_NO_SCHEDULE;          // schedule asks for vector accesses the operands cannot give
   if (d->direct && v.bsrc != B_CONV && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
   if (s->split_k < 1 || !split_allowed(*d, v, s->split_k)) return GENSOR_ERR_NO_SCHEDULE;
   SplitPlan sp = split_plan(*d, v, s->split_k, s->round_units);
   if (sp.split > 1 && (!ws_aligned || workspace_bytes < sp.bytes)) return GENSOR_ERR_WORKSPACE;
-  // 32-bit offsets inside one workgroup tile
-  const int64_t lim = 0x7fffffffll;
-  if (v.asrc == A_KC && (int64_t)(d->bm + 1) * lda * v.esize >= lim) return GENSOR_ERR_UNSUPPORTED;
-  if (v.asrc == A_MC && ((int64_t)(d->bk + 1) * lda + d->bm) * v.esize >= lim) return GENSOR_ERR_UNSUPPORTED;
-  // (the convolution epilogues address the output with 64-bit indices and never use ldc)
-  if (v.bsrc != B_CONV && (int64_t)(d->bm + 1) * ldc * v.osize >= lim) return GENSOR_ERR_UNSUPPORTED;
-  if (v.bsrc == B_KC && (int64_t)(d->bn + 1) * ldb * v.esize >= lim) return GENSOR_ERR_UNSUPPORTED;
-  if ((v.bsrc == B_NC || v.bsrc == B_NCS2) && ((int64_t)(d->bk + 1) * ldb + d->bn) * v.esize >= lim) return GENSOR_ERR_UNSUPPORTED;
+  if (!offsets_fit(*d, v, lda, ldb, ldc)) return GENSOR_ERR_UNSUPPORTED;
 
   KernelArgs a;
   std::memset(&a, 0, sizeof(a));

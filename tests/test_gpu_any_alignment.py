@@ -98,3 +98,30 @@ def test_large_output_with_rows_off_the_lines_bit_exact(gs, beta):
     gs.gemm(gs.gemm_problem("f16", M, N, K, 0, 1, 1, "f16"), gs.to_device(A, "f16"), gs.to_device(B, "f16"), C, 1.0, beta)
     want = ops.gemm(A, B, "f16", transB=1, alpha=1.0, beta=beta, C0=C0.astype(np.float32))
     assert np.array_equal(gs.to_host_f64(C), want)
+
+
+@pytest.mark.parametrize("dtype,out,M,N,K,ta,tb,lda,ldb", [
+    ("f16", "f32", 201, 300, 1003, 1, 1, 20000001, None),
+    ("bf16", "bf16", 70, 301, 203, 0, 0, None, 20000001),
+    ("f32", "f32", 40, 131, 99, 0, 0, None, 20000001),
+    ("f16", "f32", 130, 5000001, 71, 0, 0, None, None),            # output rows of 20 MB
+])
+def test_leading_dimensions_beyond_the_larger_tiles(gs, dtype, out, M, N, K, ta, tb, lda, ldb):
+    """Rows so far apart that the 32-bit offsets inside a large tile do not reach: a smaller tile takes them."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(101)
+
+    def ints(rows, cols, ld):
+        buf = gs.empty_device(((rows - 1) * (ld or cols) + cols,), dtype)
+        view = torch.as_strided(buf, (rows, cols), (ld or cols, 1))
+        return view.copy_(torch.randint(-1, 2, (rows, cols), generator=gen, device="cuda", dtype=torch.int8))
+
+    A, B = ints(*((K, M) if ta else (M, K)), lda), ints(*((N, K) if tb else (K, N)), ldb)
+    C = gs.empty_device((M, N), out)
+    p = gs.gemm_problem(dtype, M, N, K, ta, tb, 1, out)
+    fa, b = (A.T if ta else A).float(), B.T if tb else B
+    for s in (None, gs.construct(p)):
+        C.fill_(float("nan"))
+        gs.gemm(p, A, B, C, 1.0, 0.0, s, workspace=gs.gemm_workspace(p, s) if s is not None else None)
+        for n in range(0, N, 1000000):       # sums of at most 203 ones: exact in fp32, and rounded to bf16
+            assert (C[:, n:n + 1000000].float() == fa @ b[:, n:n + 1000000].float()).all().item(), n
