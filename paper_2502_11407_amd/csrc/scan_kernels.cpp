@@ -222,12 +222,13 @@ __global__ __launch_bounds__(256) void avgpool_direct_kernel(const void* in, voi
 }
 
 // Four waves share two rows where that leaves each a trip's worth of vectors (256 vectors a row: at 250 both splits take
-// 10.7-10.9 us for 16384 rows, at 475 the shared rows 20.8 against 22.7 us, at 125 9.2 against 7.0).
+// 10.7-10.9 us for 16384 rows, at 475 the shared rows 20.8 against 22.7 us, at 125 9.2 against 7.0), and where the launch
+// can hold that many workgroups: HIP takes fewer than 2^32 threads, 2^25 rows at two a workgroup, four times that otherwise.
 template <typename T>
 hipError_t launch_gemv(const void* A, int64_t lda, const void* x, float* y, int64_t M, int64_t N, float alpha, float beta, hipStream_t st) {
   constexpr int ES = ElemSize<T>::value, EPC = 16 / ES;
   const bool stream = M * lda * ES + N * ES + M * 4 > (int64_t)256 * 1024 * 1024;
-  const bool shared = N / EPC >= 256;
+  const bool shared = N / EPC >= 256 && (M + 1) / 2 * 256 < ((int64_t)1 << 32);
   const dim3 grid((unsigned)(shared ? (M + 1) / 2 : (M + 7) / 8)), block(256);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, (const char*)A, lda, (const char*)x, y, (int)M, (int)N, alpha, beta); };
   if (shared) stream ? go(gemv_kernel<T, true, 4>) : go(gemv_kernel<T, false, 4>);
@@ -279,6 +280,7 @@ using namespace gensor;
 extern "C" gensor_status gensor_gemv(gensor_dtype in_dtype, int64_t M, int64_t N, float alpha, const void* A, int64_t lda,
                                      const void* x, float beta, float* y, void* hip_stream) {
   if (!A || !x || !y || M <= 0 || N <= 0 || lda < N) return GENSOR_ERR_INVALID_ARG;
+  // (a trip past the end of a row, 64 * SPLIT * UNROLL vectors of at most 8 elements, is counted in an int)
   if (M > INT32_MAX - 8 || N > INT32_MAX - 32768) return GENSOR_ERR_UNSUPPORTED;
   hipError_t e;
   switch (in_dtype) {

@@ -88,6 +88,23 @@ def test_gemv_at_any_alignment_bit_exact(gs, dtype, M, vectors, extra):
         assert np.array_equal(gs.to_host_f64(y), 2.0 * want - y0)
 
 
+def test_gemv_with_more_rows_than_a_launch_holds_at_two_a_workgroup(gs):
+    """2^25 rows of 256 vectors, 128 GiB."""
+    import torch
+    M, N = 2 ** 25, 2048
+    if torch.cuda.mem_get_info()[0] < 150 * 10 ** 9:
+        pytest.skip("needs 150 GB of device memory")
+    A = gs.empty_device((M, N), "f16").fill_(1.0)
+    A[M // 2], A[M - 1] = 3.0, 2.0
+    y = gs.empty_device((M,)).fill_(float("nan"))
+    gs.gemv("f16", A, torch.ones(N, dtype=torch.float16, device="cuda"), y)
+    del A
+    torch.cuda.empty_cache()
+    assert y[M // 2].item() == 3 * N and y[M - 1].item() == 2 * N
+    y[M // 2] = y[M - 1] = N
+    assert (y == N).all().item()
+
+
 @pytest.mark.parametrize("beta", [0.0, -1.0])
 def test_large_output_with_rows_off_the_lines_bit_exact(gs, beta):
     """More than 32 MiB of 16-bit output whose rows do not start on 128-byte lines: stored write-back."""
