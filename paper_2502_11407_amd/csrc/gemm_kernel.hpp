@@ -57,7 +57,7 @@ struct KernelArgs {
   int64_t lda, ldb, ldc;           // elements
   int64_t strideA, strideB, strideC;
   float alpha, beta;
-  int32_t through;                 // C is stored write-through (only where beta is 0)
+  int32_t through;                 // C is stored write-through (beside beta only with fp32 output)
   int32_t tiles_m, tiles_n, batch;
   int32_t panel;                   // tile rows per panel in the workgroup->tile map
   int64_t ahead_a, ahead_b;        // bytes of the next batch's A and B that this batch's workgroups read ahead (0: none)
@@ -1163,8 +1163,10 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + 4 * fgrp) * pitch;
         constexpr std::integral_constant<int, 16> write_through{};
         constexpr std::integral_constant<int, 0> write_back{};
-        if (args.through) store_block(bi, bj, lane_off, std::false_type{}, write_through);
+        // (without the hint the fourth form cost the store-bound launches that do not use it 0.7 %)
+        if (OS == 2 ? args.through != 0 : __builtin_expect(args.through && beta == 0.f, 1)) store_block(bi, bj, lane_off, std::false_type{}, write_through);
         else if (beta == 0.f) store_block(bi, bj, lane_off, std::false_type{}, write_back);
+        else if (OS == 4 && args.through) store_block(bi, bj, lane_off, std::true_type{}, write_through);
         else store_block(bi, bj, lane_off, std::true_type{}, write_back);
       }
     }

@@ -396,7 +396,13 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   // 11.8; 16-bit outputs of 8-30 MB: within 4 % either way), aligned rows too (48 x 768 x 768 x 64: 21.7 against 27.4).
   const int64_t c_bytes = v.batch * v.M * v.N * v.osize;
   const bool partial_lines = (ldc * v.osize) % 128 != 0 && c_bytes > (v.osize == 2 ? 32ll : 64ll) * 1024 * 1024;
-  a.through = beta == 0.f && !partial_lines;
+  // Beside beta the line has just been read, and only large fp32 outputs (or launches of a single k tile, which wait on
+  // little else) still gain from write-through.  With it and without, beta = 0.5: 96 x 1024 x 1024 x 64 269 against 277 us,
+  // 8 of them 14.7 against 15.9, 4096^3 224.6 against 227.7, 6144 x 4096 x 512 126.4 against 128.0; but 4096 x 3072 x 768
+  // 47.3 against 45.6, 4000 x 1000 x 512 21.9 against 17.7, and with 16-bit output 8192 x 3072 x 768 97.7 against 83.8,
+  // 96 x 1024 x 1024 x 64 255 against 233, 16384 x 8192 x 512 554 against 532.
+  const bool beside_beta = v.osize == 4 && (c_bytes >= 64ll * 1024 * 1024 || v.K <= d->bk);
+  a.through = !partial_lines && (beta == 0.f || beside_beta);
   a.tiles_m = (int32_t)((v.M + d->bm - 1) / d->bm);
   a.tiles_n = (int32_t)((v.N + d->bn - 1) / d->bn);
   a.batch = (int32_t)v.batch;

@@ -142,3 +142,15 @@ def test_leading_dimensions_beyond_the_larger_tiles(gs, dtype, out, M, N, K, ta,
         gs.gemm(p, A, B, C, 1.0, 0.0, s, workspace=gs.gemm_workspace(p, s) if s is not None else None)
         for n in range(0, N, 1000000):       # sums of at most 203 ones: exact in fp32, and rounded to bf16
             assert (C[:, n:n + 1000000].float() == fa @ b[:, n:n + 1000000].float()).all().item(), n
+
+
+@pytest.mark.parametrize("beta", [0.0, -1.0])
+@pytest.mark.parametrize("N", [4096, 4100], ids=["rows on the lines", "rows off the lines"])
+def test_large_fp32_output_bit_exact(gs, N, beta):
+    """64 MiB of fp32 output and more: write-through with and without beta, write-back where rows start off the 128-byte lines."""
+    M, K = 4101, 192
+    A, B = inputs.small_ints(94, (M, K), "f16", -3, 3), inputs.small_ints(95, (N, K), "f16", -3, 3)
+    C0 = inputs.small_ints(96, (M, N), "f32", -4, 4)
+    C = gs.to_device(C0, "f32")
+    gs.gemm(gs.gemm_problem("f16", M, N, K, 0, 1), gs.to_device(A, "f16"), gs.to_device(B, "f16"), C, 1.0, beta)
+    assert np.array_equal(C.cpu().numpy(), A.astype(np.float32) @ B.astype(np.float32).T + beta * C0)      # integers: exact in fp32
