@@ -208,9 +208,11 @@ struct Cfg {
   static constexpr int B_LOADS = (B_CHUNKS + THREADS - 1) / THREADS;
   // Register-staged double buffer: two register sets, i.e. two k tiles of loads in flight, where they fit beside the
   // accumulators, the fragments and the addresses into the 256 registers of a lane that two waves per SIMD leave
-  // (a set more than that would halve the resident waves)
+  // (a set more than that would halve the resident waves).  16x16 blocks compile to about half as many fragment registers again as the two
+  // steps' (128x128x64 tiles: 264-284 registers with two sets, one workgroup per CU instead of two, 8192 x 4096 x 512
+  // 60 -> 72 us, 16384 x 2048 x 192 33 -> 44).
   static constexpr int STAGE_REGS = 4 * (A_LOADS + B_LOADS * (BSRC_ == B_NCS2 ? 2 : 1));
-  static constexpr int OTHER_REGS = WM_ * WN_ / 64 + 8 * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
+  static constexpr int OTHER_REGS = WM_ * WN_ / 64 + (MB_ == 16 ? 12 : 8) * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
   static constexpr int RSETS = (!DIRECT_ && STAGES_ == 2 && KSTEPS % 2 == 0 && BSRC_ != B_CONV && 2 * STAGE_REGS + OTHER_REGS <= 256) ? 2 : 1;
   // the tile that store-bound batches of a shallow k end in also exists with the next batch read ahead
   static constexpr bool HAS_AHEAD = VEC_ && DIRECT_ && STAGES_ == 2 && ES == 2 && ElemSize<OutT_>::value == 4 && BM_ == 128 && BN_ == 128 && WAVES == 8;

@@ -1,0 +1,36 @@
+"""Register counts that rules in the kernels rely on, read from the compiler's own figures for this repository's kernels."""
+import os
+import re
+import subprocess
+import sys
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2502_11407_amd", "csrc"))
+import build as kernel_build  # noqa: E402
+import lattice  # noqa: E402
+
+
+def _counts(tmp_path, insts, launcher, extra=()):
+    """(instance, registers, spilled registers) of every kernel the launches of these instances instantiate."""
+    src, out = tmp_path / "k.hip", tmp_path / "k.s"
+    lines = ['#include "registry.hpp"', "namespace gensor {"]
+    for d in insts:
+        lines.append("typedef %s C_%d;" % (lattice.cfg_type(d), d["id"]))
+        for j, call in enumerate(launcher):
+            lines.append("hipError_t l%d_%d(const KernelArgs& a, hipStream_t st) { return %s(a, st); }" % (d["id"], j, call % ("C_%d" % d["id"])))
+    src.write_text("\n".join(lines + ["}\n"]))
+    r = subprocess.run([kernel_build.HIPCC] + kernel_build.FLAGS + list(extra) + ["-x", "hip", "--cuda-device-only", "-S", str(src), "-o", str(out)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = out.read_text()
+    regs = [int(x) for x in re.findall(r"\.vgpr_count:\s+(\d+)", text)]
+    spills = [int(x) for x in re.findall(r"\.vgpr_spill_count:\s+(\d+)", text)]
+    assert len(regs) == len(spills) >= len(insts)
+    return list(zip(re.findall(r"\.name:\s+(_ZN6gensor\S+)", text), regs, spills))
+
+
+def test_large_tiles_of_16x16_blocks_keep_two_waves_per_simd(tmp_path):
+    """Their LDS leaves two workgroups of four waves per CU; more than 256 registers would leave one."""
+    insts = [d for d in lattice.lattice() if d["dt"] == "f16" and d["mb"] == 16 and d["bm"] == 128 and d["vec"] == 1 and d["bsrc"] in ("KC", "NC")]
+    assert len(insts) >= 4
+    for name, regs, spilled in _counts(tmp_path, insts, ("launch_instance<%s>", "launch_instance<%s, true>")):
+        assert regs <= 256 and spilled == 0, (name, regs, spilled)
