@@ -29,7 +29,10 @@ struct ConvRowsCfg {
   static constexpr int ES = ElemSize<T>::value, EPC = 16 / ES;
   static constexpr int WAVES_N = BN / WN, WAVES = BM / WM * WAVES_N, THREADS = WAVES * 64;
   static constexpr int MBLK = WM / MB, NBLK = WN / MB;
-  static constexpr int A_BATCH = 6, P_BATCH = 4;       // 16-byte units a thread has in flight: filters, input rows
+  // 16-byte units a thread has in flight: filters, input rows.  Two input rows where a wave has two blocks of 16-bit operands:
+  // four spilled 13-15 of the 128 registers that two workgroups of eight such waves per CU leave (16 x 16 x 112 x 112, 64 filters
+  // 5x5: 55 -> 49 us; 8 x 40 x 28 x 28: 32 -> 28; five and three, without spills, too: 49, 29.6).
+  static constexpr int A_BATCH = 6, P_BATCH = ES == 2 && MBLK * NBLK == 2 ? 2 : 4;
   static_assert(BM % WM == 0 && BN % WN == 0 && WM % MB == 0 && WN % MB == 0, "tiles");
 };
 

@@ -34,3 +34,10 @@ def test_large_tiles_of_16x16_blocks_keep_two_waves_per_simd(tmp_path):
     assert len(insts) >= 4
     for name, regs, spilled in _counts(tmp_path, insts, ("launch_instance<%s>", "launch_instance<%s, true>")):
         assert regs <= 256 and spilled == 0, (name, regs, spilled)
+
+
+def test_row_staged_convolution_does_not_spill(tmp_path):
+    insts = [d for d in lattice.lattice() if lattice.conv_rows(d) and (d["dt"], d["out"]) in (("f16", "f32"), ("bf16", "bf16"), ("f32", "f32"))]
+    assert len(insts) == 12
+    for name, regs, spilled in _counts(tmp_path, insts, ("launch_conv_rows<%s>",), kernel_build.CONV_FLAGS):
+        assert spilled == 0, (name, regs, spilled)
