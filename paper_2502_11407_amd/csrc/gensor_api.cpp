@@ -151,12 +151,12 @@ bool conv_rows_plan(int bm, int bn, const GemmView& v, ConvRowsPlan* plan, int r
   // unless it is whole rows) and starts at any row of an image
   int64_t out_rows = px % v.Q == 0 ? px / v.Q : (px + v.Q - 2) / v.Q + 1;
   if (out_rows > v.cn * v.P) out_rows = v.cn * v.P;
-  int64_t rows = 0;
-  for (int64_t first = 0; first < v.P; ++first) {
-    const int64_t last = first + out_rows - 1 < v.cn * v.P ? first + out_rows - 1 : v.cn * v.P - 1;
-    const int64_t r = (last / v.P) * hp + (last % v.P - first) * v.cstride + v.cr;
-    if (r > rows) rows = r;
-  }
+  // (its last row is `images` images and `more` rows further on, or one image more where it starts among the last `more`
+  // rows of an image and another follows; in closed form, for the plan is made in every call and an image may have any number of rows)
+  const int64_t images = (out_rows - 1) / v.P, more = (out_rows - 1) % v.P;
+  int64_t rows = images * hp + more * v.cstride + v.cr;
+  if (more > 0 && images + 1 < v.cn && (images + 1) * hp + (more - v.P) * v.cstride + v.cr > rows)
+    rows = (images + 1) * hp + (more - v.P) * v.cstride + v.cr;
   pl.rows = (int)rows;
   const int64_t xo = (v.cpad + epc - 1) / epc * epc;
   const int64_t right = (v.cw + v.cpad + epc - 1) / epc * epc;

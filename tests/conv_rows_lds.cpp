@@ -58,6 +58,16 @@ static void check(int dtype, int64_t n, int64_t c, int64_t h, int64_t w, int64_t
     if (nche * 16 > pl.a_pitch) { std::printf("filter row %lld over pitch %d\n", (long long)nche * 16, pl.a_pitch); ++failures; }
     const int64_t written = ((int64_t)pl.channels * pl.rows - 1) * pl.row_pitch + (xo + segs * epc) * v.esize;
     if (written > input_bytes || pl.stage_bytes > 160 * 1024) { std::printf("stage of %d bytes\n", pl.stage_bytes); ++failures; }
+    // the rows a tile can touch, counted over every row it may start at
+    const int64_t hp = v.ch + 2 * v.cpad, last_row = v.cn * v.P - 1;
+    int64_t out_rows = pl.tile_px % v.Q == 0 ? pl.tile_px / v.Q : (pl.tile_px + v.Q - 2) / v.Q + 1, rows = 0;
+    if (out_rows > last_row + 1) out_rows = last_row + 1;
+    for (int64_t first = 0; first < v.P; ++first) {
+      const int64_t g = first + out_rows - 1 < last_row ? first + out_rows - 1 : last_row;
+      const int64_t r = (g / v.P) * hp + (g % v.P - first) * v.cstride + v.cr;
+      if (r > rows) rows = r;
+    }
+    if (rows != pl.rows) { std::printf("%d rows planned, %lld touched\n", pl.rows, (long long)rows); ++failures; }
     const int tail = (int)(v.cc % pl.channels ? v.cc % pl.channels : pl.channels);       // channels of the last stage
     for (int64_t n0 = 0; n0 < N; n0 += pl.tile_px) {
       for (int ch : {pl.channels, tail}) {
@@ -87,6 +97,10 @@ int main() {
     check(dt, 16, 16, 112, 112, 64, 5, 5, 1, 2);
     check(dt, 2, 6, 50, 61, 48, 7, 7, 1, 3);
     check(dt, 1, 1, 1, 1, 1, 1, 1, 1, 0);
+    check(dt, 5, 1, 4, 3, 9, 3, 3, 3, 1);            // several images to a tile, strides beyond the filter
+    check(dt, 2, 1, 4, 3, 9, 2, 2, 2, 0);
+    check(dt, 30, 2, 11, 5, 33, 4, 2, 3, 2);
+    check(dt, 1, 2, 700, 1, 8, 5, 1, 1, 2);          // one column
   }
   std::printf("%s: %d plans, %d failure(s)\n", failures ? "FAILED" : "inside", walked, failures);
   return failures || walked < 100 ? 1 : 0;
