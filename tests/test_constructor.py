@@ -447,7 +447,7 @@ def test_cost_model_limits_and_monotonicity():
     big = f(256, 256, 64, 128, 128, 16, 8, 8, direct=1)
     assert t_mfma < big < 2.5 * t_mfma                                                   # MFMA-bound, and not absurdly above it
     assert f(32, 32, 64, 16, 16, 32, 8, 8) > f(128, 128, 64, 64, 64, 16, 8, 8) > big     # small tiles re-read operands
-    assert f(128, 128, 64, 64, 64, 16, 8, 8, vec=0) > f(128, 128, 64, 64, 64, 16, 8, 8)  # element loads cost
+    assert f(128, 128, 64, 64, 64, 16, 8, 8, vec=0) > f(128, 128, 64, 64, 64, 16, 8, 8)  # rows off the vector boundaries cost
     assert f(256, 256, 128, 128, 128, 16, 16, 16) < 0                                    # LDS capacity (two stages of 128 KiB)
     assert f(256, 256, 64, 256, 256, 16, 8, 8) < 0                                       # registers (256 x 256 accumulators per wave)
     assert f(256, 256, 64, 16, 16, 32, 8, 8) < 0                                         # 256 waves per workgroup

@@ -125,7 +125,7 @@ def test_gemm_real_values_default_schedule(gs, dtype, transB):
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_gemm_alpha_beta_and_unaligned_shapes(gs, dtype):
-    M, N, K = 77, 53, 41        # nothing is a multiple of a chunk: scalar path
+    M, N, K = 77, 53, 41        # nothing is a multiple of a chunk: the any-alignment instances
     A = inputs.small_ints(3, (M, K), dtype)
     B = inputs.small_ints(4, (K, N), dtype)
     C0 = inputs.small_ints(5, (M, N), "f32")
@@ -224,7 +224,7 @@ def test_conv_patch_instances_bit_exact(gs, dtype, geom):
     (3, 40, 12, 16, 70, 1),      # the input itself is the B operand (ldb = H*W)
     (3, 40, 12, 16, 70, 2),      # stride 2, rows of whole vectors: sampled while fetched, no workspace; P*Q = 48
     (2, 16, 16, 40, 300, 2),     # the same over several m and n tiles with ragged edges; P*Q = 160
-    (2, 24, 13, 11, 33, 3),      # compacted through the workspace; P*Q = 20: scalar instances only
+    (2, 24, 13, 11, 33, 3),      # compacted through the workspace; P*Q = 20: any-alignment instances only
     (2, 16, 31, 31, 16, 2),      # compacted through the workspace; P*Q = 256, several n tiles
     (2, 8, 9, 24, 20, 2),        # could be sampled, but P*Q = 60 is no whole number of fp16 vectors: compacted
 ])
@@ -423,7 +423,7 @@ def test_gemv_bit_exact_on_integers(gs, dtype, M, N):
 
 
 def test_gemv_unaligned_operands_and_errors(gs):
-    """A view with an odd leading dimension and an offset start takes the element-load kernel."""
+    """A view with an odd leading dimension and an offset start."""
     import torch
     A = inputs.small_ints(44, (33, 77), "f16", -2, 2)
     x = inputs.small_ints(45, (77,), "f16", -2, 2)
@@ -601,7 +601,7 @@ def test_benchmark_shapes_with_output_in_the_input_type(gs, name):
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_random_gemm_shapes_with_constructed_schedules(gs, dtype):
     """Seeded random extents, layouts, batch counts and scalars, each with the schedule the constructor picks
-    for it: whatever instance that is (vector or element loads, any tile) must be bit-exact on integers."""
+    for it: whatever instance that is (aligned or at any alignment, any tile) must be bit-exact on integers."""
     rng = np.random.default_rng(20250211)
     for case in range(24):
         M, N, K = (int(x) for x in rng.integers(1, 420, size=3))
@@ -703,7 +703,7 @@ def test_split_k_bit_exact_on_integers(gs, dtype, M, N, K, tb, batch, split, til
     for s in scheds:
         print("instance", s.kernel_id, s.describe()["tile_m"], s.describe()["tile_n"], "split", split, flush=True)
         ws = gs.gemm_workspace(p, s)
-        ws.fill_(0xAB)                                  # whatever the workspace holds, counters included
+        ws.fill_(0xAB)                                  # whatever the workspace holds
         # the same workspace serves call after call: the second must not see what the first left in it
         assert np.array_equal(_run_split(gs, p, s, dtype, A2, B, ws, 2.0, -1.0, C0), want2)
         assert np.array_equal(_run_split(gs, p, s, dtype, A, B, ws, 2.0, -1.0, C0), want)
@@ -779,7 +779,7 @@ def test_deep_k_shapes_full_size_sampled(gs, index):
 
 @pytest.mark.gpu
 def test_operators_captured_in_a_graph_replay_like_eager_calls(gs):
-    """Every operator launch (the split-k pair of counter clear + kernel included) can be recorded into a HIP
+    """Every operator launch (the split-k pair of kernel and reduction included) can be recorded into a HIP
     graph: each replay, with eager work and synchronisations in between and fresh inputs written into the
     captured buffers, gives what the eager call gives."""
     import torch
@@ -796,7 +796,7 @@ def test_operators_captured_in_a_graph_replay_like_eager_calls(gs):
     cws = gs.conv_workspace(pc)
 
     def launch_all():
-        gs.gemm(p, dA, dB, dC, 1.0, 0.0, s, workspace=ws)          # split-k: counter clear + kernel
+        gs.gemm(p, dA, dB, dC, 1.0, 0.0, s, workspace=ws)          # split-k: kernel + reduction
         gs.gemm(p, dA, dB, dC1, 1.0, 0.0, None)                    # schedule looked up per shape
         gs.conv2d(pc, dI, dW, dO, None, cws)
         gs.gemv("f16", dA, dx, dy)

@@ -1,4 +1,4 @@
-"""The allocation-free GEMM entry point (gensor_gemm_static_scratch: split-k counters and partial tiles in a device
+"""The allocation-free GEMM entry point (gensor_gemm_static_scratch: split-k partial tiles in a device
 array of the library itself) against gensor_gemm with a caller-owned workspace: same kernels, same summation
 order, so the outputs must be identical bit for bit; and against the oracle at the stated tolerance."""
 import numpy as np
