@@ -247,7 +247,8 @@ size_t gensor_workspace_bytes(const gensor_schedule* s, const gensor_problem* p)
  * carried in fp32.  A memory-bound streaming kernel with a fixed internal schedule (no
  * gensor_schedule): 16-byte vector loads whatever the alignment of A, x and lda.  Enqueued on
  * hip_stream; nothing is allocated.
- * INVALID_ARG for null pointers, non-positive extents or lda < N.
+ * INVALID_ARG for null pointers, non-positive extents or lda < N; UNSUPPORTED for more rows than a
+ * launch holds (M > 2^27 - 8) or N > INT32_MAX - 32768.
  */
 gensor_status gensor_gemv(gensor_dtype in_dtype, int64_t M, int64_t N, float alpha,
                           const void* A, int64_t lda, const void* x, float beta, float* y,

@@ -280,8 +280,9 @@ using namespace gensor;
 extern "C" gensor_status gensor_gemv(gensor_dtype in_dtype, int64_t M, int64_t N, float alpha, const void* A, int64_t lda,
                                      const void* x, float beta, float* y, void* hip_stream) {
   if (!A || !x || !y || M <= 0 || N <= 0 || lda < N) return GENSOR_ERR_INVALID_ARG;
-  // (a trip past the end of a row, 64 * SPLIT * UNROLL vectors of at most 8 elements, is counted in an int)
-  if (M > INT32_MAX - 8 || N > INT32_MAX - 32768) return GENSOR_ERR_UNSUPPORTED;
+  // HIP takes fewer than 2^32 threads, 256 for eight rows; a trip past the end of a row, 64 * SPLIT * UNROLL vectors of at most
+  // 8 elements, is counted in an int
+  if (M > ((int64_t)1 << 27) - 8 || N > INT32_MAX - 32768) return GENSOR_ERR_UNSUPPORTED;
   hipError_t e;
   switch (in_dtype) {
     case GENSOR_F32: e = launch_gemv<f32_t>(A, lda, x, y, M, N, alpha, beta, (hipStream_t)hip_stream); break;

@@ -57,3 +57,11 @@ def test_host_side_argument_checks_without_a_gpu():
     assert gs.lib.gensor_conv2d(None, ctypes.byref(conv), addr, addr, addr, None, 0, None) == 1
     assert gs.status_string(3).startswith("no feasible schedule")
     assert gs.instance_schedule(0, gs.gemm_problem("f32", 8, 8, 8)) is None
+
+
+def test_gemv_refuses_more_rows_than_a_launch_holds():
+    from paper_2502_11407_amd import binding as gs
+    buf = ctypes.create_string_buffer(64)
+    addr = ctypes.addressof(buf)
+    for rows in (2 ** 27 - 7, 2 ** 31 - 9):                       # refused on the host, before anything is launched
+        assert gs.lib.gensor_gemv(1, rows, 8, 1.0, addr, 8, addr, 0.0, addr, None) == 2
