@@ -7,7 +7,7 @@ This is a MEASUREMENT fixture, not oracle output: it is what pins the library's 
 instance it ranks first, and how its ranking correlates with the hardware) to something that shares no code
 with it.  tests/test_cost_model_measured.py reads it on the CPU.
 
-Run on the GPU machine from the repository root, after building:
+Run on an MI355X from the repository root, after building:
     python tests/golden/make_instance_times.py
 Protocol per (shape, instance): launches that settle the shader clock (15 ms), then the median of 3
 event-bracketed batches of at least 10 launches (about 3 ms each).  Instances the cost model prices above

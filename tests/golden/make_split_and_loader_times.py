@@ -4,8 +4,8 @@ contraction is split along k (every instance and split factor) and of the convol
 element gather), on one MI355X.  A measurement fixture like instance_times.json, for the parts of the cost model that file
 does not reach; tests/test_cost_model_splits_and_loaders.py reads it on the CPU.
 
-Run on the GPU machine from the repository root, after building:
-    python tests/golden/make_split_and_loader_times.py
+Run on an MI355X from the repository root, after building (the file to write may be named):
+    python tests/golden/make_split_and_loader_times.py [path]
 Protocol per schedule: three sets of operands in turn, 5 ms of launches to settle the clock, then the least of 3 event-bracketed
 batches of at least 10 launches.  Schedules the model prices above SKIP_GEMM or SKIP_CONV times its cheapest are not timed.
 """
@@ -96,10 +96,9 @@ def main():
         best = min(rows, key=lambda q: q[2])
         print(shape, "%d schedules, best instance %d split %d %.1f us" % (len(rows), *best), flush=True)
     text = json.dumps(out).replace('{"shape"', '\n{"shape"')
-    os.makedirs(os.path.join(ROOT, "gpurun_out"), exist_ok=True)
-    for path in (os.path.join(ROOT, "tests", "golden"), os.path.join(ROOT, "gpurun_out")):
-        with open(os.path.join(path, "split_and_loader_times.json"), "w") as f:
-            f.write(text + "\n")
+    path = sys.argv[1] if len(sys.argv) > 1 else os.path.join(ROOT, "tests", "golden", "split_and_loader_times.json")
+    with open(path, "w") as f:
+        f.write(text + "\n")
 
 
 if __name__ == "__main__":
