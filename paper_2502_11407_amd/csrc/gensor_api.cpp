@@ -403,6 +403,7 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   // 96 x 1024 x 1024 x 64 255 against 233, 16384 x 8192 x 512 554 against 532.
   const bool beside_beta = v.osize == 4 && (c_bytes >= 64ll * 1024 * 1024 || v.K <= d->bk);
   a.through = !partial_lines && (beta == 0.f || beside_beta);
+  a.paired = v.osize == 2 && beta == 0.f && v.N % 2 == 0 && ldc % 2 == 0 && strideC % 2 == 0 && (reinterpret_cast<uintptr_t>(C) & 3u) == 0;
   a.tiles_m = (int32_t)((v.M + d->bm - 1) / d->bm);
   a.tiles_n = (int32_t)((v.N + d->bn - 1) / d->bn);
   a.batch = (int32_t)v.batch;
