@@ -68,7 +68,7 @@ def generate():
         kg = (64 // d["mb"]) * (16 // es)
         a_bytes = d["bm"] * d["bk"] * es if d["asrc"] == "KC" else d["bk"] * (d["bm"] * es + (0 if d["direct"] else lattice.pad_m(d)))
         b_bytes = d["bn"] * d["bk"] * es if (d["bsrc"] == "KC" or d["direct"]) else d["bk"] * (d["bn"] * es + lattice.pad_n(d))
-        lds = 0 if d["units"] or lattice.conv_rows(d) else (a_bytes + b_bytes) * d["stages"]
+        lds = 0 if d["units"] or lattice.conv_rows(d) else (a_bytes + b_bytes) * d["stages"] + (b_bytes if lattice.alternate(d) else 0)
         threads = (d["bm"] // d["wm"]) * (d["bn"] // d["wn"]) * 64
         reg.append("  {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, launch_%d, %s}," % (
             d["id"], lattice.DT[d["dt"]], lattice.DT[d["out"]], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"],

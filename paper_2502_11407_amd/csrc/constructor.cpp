@@ -396,7 +396,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double tiles = tiles_m * tiles_n * (double)v.batch;
   const int nwaves = (bm / wm) * (bn / wn);
   if (nwaves > hw.max_waves_per_wg) return -1.0;
-  const int lds = stages * e * bk * (bm + bn);
+  // the tiles whose wave groups alternate (Cfg::ALTERNATE): B has a third stage
+  const bool alternate = direct && stages == 2 && e == 2 && mb == 16 && bm == 256 && bn == 256 && bk == 64;
+  const int lds = stages * e * bk * (bm + bn) + (alternate ? e * bk * bn : 0);
   if (lds > hw.lds_bytes_per_cu) return -1.0;
   const int regs = wm * wn / 64 + 2 * (wm + wn) * kg * e / 256 + (direct ? 0 : (e * bk * (bm + bn)) / (nwaves * 64 * 4)) + 32;
   if (regs > hw.regs_per_lane) return -1.0;
@@ -440,12 +442,15 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (direct && v.bsrc == B_KC) overlap += 0.05;      // measured: what direct staging pays for k-contiguous operands
   if (direct && v.bsrc == B_NC) overlap += 0.03;      // ... and for an n-contiguous B
   if (direct && v.bsrc == B_KC && stages == 2 && wm * wn >= 128 * 128 && bk == 4 * kg) overlap += 0.24;   // the two-steps-ahead schedule of the one-wave-per-SIMD tiles (k-contiguous operands: measured)
+  // (the alternating groups: one multiplies while the other waits, 94 % of the MFMA rate on all-zero operands, and no boundary
+  // of a k tile is exposed; 4096^3 105 us against 124 of the next tile, 3648 x 2624 x 1856 38 against 41)
+  if (alternate) overlap = 1.3;
   double t_main = t_mfma;
   if (t_lds > t_main) t_main = t_lds;
   if (t_feed > t_main) t_main = t_feed;
   // every k tile boundary (barrier, refill of the fragment pipeline) exposes a share of the memory latency
   // (a ring of three and more stages keeps more tiles in flight)
-  const double t_ktile = 0.3 * hw.latency_ns[0] * 1e-3;
+  const double t_ktile = alternate ? 0.0 : 0.3 * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;
     // (a ring fills stages - 1 tiles before its first product: those boundaries are paid in full, measured as no gain
@@ -475,6 +480,8 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // beyond four waves per SIMD nothing more is hidden
   double hide = resident * nwaves / hw.simds_per_cu;
   if (hide > 4.0) hide = 4.0;
+  // (the alternating groups reach their stores within a slot of each other: 8 us a tile beside 1.4 a k tile, 8192 x 4096 x 512 and x 1024)
+  if (alternate) hide = 1.3;
   // a part stores its partial tile
   const double t_swap = bm * bn * 4.0 / (1.2 * hbm_bw_cu);
   const double t_cu = cu_whole * (t_main + t_epi / hide) + cu_part * (t_part + t_swap / hide) + t_fill;
@@ -499,7 +506,7 @@ const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
 bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok) {
   if (!instance_serves(d, v)) return false;
   if (d.vec && !vec_ok) return false;
-  if (d.direct && v.bsrc != B_CONV && v.K % d.bk != 0) return false;
+  if (d.direct && !d.alternate() && v.bsrc != B_CONV && v.K % d.bk != 0) return false;
   return true;
 }
 

@@ -116,6 +116,13 @@ template <typename T> __device__ inline uint32_t pack_out(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, p);
 }
 
+// 16 bytes a lane to lds + 16 * lane.  (The host's pass knows no 16-byte form of the builtin, and would drop the kernel.)
+__device__ inline void load_to_lds(__amdgpu_buffer_rsrc_t r, GENSOR_LDS char* lds, uint32_t offset) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (GENSOR_LDS void*)lds, 16, offset, 0, 0, 0);
+#endif
+}
+
 // ---------------------------------------------------------------- MFMA wrappers
 // (the bits travel through a by-value argument: a bit cast applied directly to a vector
 // element expression reads element 0 whatever the index)
@@ -209,7 +216,9 @@ struct Cfg {
   static constexpr int A_BYTES = (ASRC == A_KC) ? BM * PITCH_K : BK * PITCH_M;
   static constexpr int B_BYTES = (BSRC == B_KC) ? BN * PITCH_K : BK * PITCH_N;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int LDS_BYTES = STAGE_BYTES * STAGES;
+  // Two groups of four waves that take turns at reading and multiplying (the loop says how); B has a third stage.
+  static constexpr bool ALTERNATE = DIRECT_ && STAGES_ == 2 && MB_ == 16 && ES == 2 && BM_ == 256 && BN_ == 256 && BK_ == 64 && WM_ == 128 && WN_ == 64;
+  static constexpr int LDS_BYTES = STAGE_BYTES * STAGES + (ALTERNATE ? B_BYTES : 0);
   static constexpr int A_CHUNKS = (ASRC == A_KC) ? BM * CPR : BK * (BM * ES / 16);
   static constexpr int B_CHUNKS = (BSRC == B_KC) ? BN * CPR : BK * (BN * ES / 16);
   static constexpr int A_LOADS = (A_CHUNKS + THREADS - 1) / THREADS;
@@ -849,7 +858,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   // of tile kt, so that the barrier and the LDS latency are covered by matrix work.
   const int nk = (Kx + BK - 1) / BK;
   constexpr bool PIPE = (C::KSTEPS % 2 == 0) && C::STAGES == 2;
-  if constexpr (C::STAGES <= 2) {
+  if constexpr (C::STAGES <= 2 && !C::ALTERNATE) {
     fetch_a(0, 0);
     fetch_b(0, 0);
     if constexpr (C::RSETS == 2) {
@@ -860,7 +869,231 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     wait_deposits();
     __syncthreads();
   }
-  if constexpr (DEEP) {
+  if constexpr (C::ALTERNATE) {
+    // Large tiles run into the chip's power limit, which 16x16x32 products reach at 1957 TFLOP/s and 32x32x16 ones at 1705
+    // (registers only, uniform operands), but only from two waves per SIMD (one: 1784).  So: eight waves of 16x16 blocks, and so
+    // that the two waves of a SIMD do not wait for the LDS together, the four waves of the upper half of the tile (group
+    // 0) and the four of the lower half (group 1) alternate.  Time is cut into slots by barriers.  In slot 2t group 0
+    // multiplies k tile t, all of whose fragments it holds, while group 1 reads its fragments of tile t; in slot 2t+1 group
+    // 1 multiplies and group 0 reads tile t+1.  A multiplying wave issues nothing but MFMAs, in an order in which each one
+    // shares an operand with the one before (2 % more under the power limit).  The direct loads go out between the
+    // fragment reads, 32 a slot; a slot of 48 followed by one of 16 took 1220 cycles instead of 1080, loads behind the reads 1440.
+    //   A(t), in stage t % 2: group g reads only its own half.  In slot 2t group 1 requests the upper half of A(t+2) (group 0 read
+    //   that of A(t) in slot 2t-1), in slot 2t+1 group 0 the lower half (group 1 read it in slot 2t).
+    //   B(t), in stage t % 3: both read it, the later in slot 2t.  Group 1 requests half of B(t+2) in slot 2t, group 0 the other half
+    //   of B(t+3) in slot 2t+1.
+    // Every request has at least two slots before the barrier behind which it is read.  Each wave waits for its own
+    // requests in front of that barrier; they land in issue order, so the waits are counts.
+    // 4096^3 f16 118 -> 104 us (all-zero operands 79 -> 70), 8192^3 911 -> 800 (771 -> 575), against four 128x128 waves of 32x32 blocks.
+    // Raising the wave priority while multiplying starves the readers (108 us on zeros); MFMAs behind the barrier of their
+    // slot, to cover it, delay the next slot's reads (81 us).
+    static_assert(C::KSTEPS == 2 && C::A_BYTES == 32768 && C::B_BYTES == 32768, "two k steps; 32 KiB an operand");
+    constexpr int NB = C::MBLK * C::NBLK;
+    const int group = wave >> 2, w4 = wave & 3;
+    auto stage_a = [&](int t) { return lds + (t & 1) * C::A_BYTES; };
+    auto stage_b = [&](int t3) { return lds + 2 * C::A_BYTES + t3 * C::B_BYTES; };
+    // This wave's requests: four 1 KiB runs of one half of each operand's tile.  (Chunks 512 apart have the same swizzle.)
+    // An m-contiguous A is kept as two halves [k][128 rows]: a run has to be contiguous in the LDS and in one half.
+    const int half_a = 1 - group, half_b = group;
+    uint32_t va[2], vb[2], step_a, step_b;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int q = (i * 4 + w4) * 64 + lane;                  // chunk inside the half
+      if constexpr (C::ASRC == A_KC) {
+        const int row = half_a * 128 + q / C::CPR;
+        va[i] = (uint32_t)((row * (int)args.lda + swizzled_chunk(row, q % C::CPR, C::RPP, C::VM) * EPC) * ES);
+        step_a = (uint32_t)((512 / C::CPR) * (int)args.lda * ES);
+      } else {
+        const int krow = q / 16, ch = (q % 16) ^ (nc_swizzle(krow, C::VM) >> 4);
+        va[i] = (uint32_t)((krow * (int)args.lda + half_a * 128 + ch * EPC) * ES);
+        step_a = (uint32_t)((512 / 16) * (int)args.lda * ES);
+      }
+      const int q2 = half_b * 1024 + q;
+      if constexpr (C::BSRC == B_KC) {
+        const int row = q2 / C::CPR;
+        vb[i] = (uint32_t)((row * (int)args.ldb + swizzled_chunk(row, q2 % C::CPR, C::RPP, C::VN) * EPC) * ES);
+        step_b = (uint32_t)((512 / C::CPR) * (int)args.ldb * ES);
+      } else {
+        const int krow = q2 / 32, ch = (q2 % 32) ^ (nc_swizzle(krow, C::VN) >> 4);
+        vb[i] = (uint32_t)((krow * (int)args.ldb + ch * EPC) * ES);
+        step_b = (uint32_t)((512 / 32) * (int)args.ldb * ES);
+      }
+    }
+    // K need not be a multiple of BK: k rows beyond it lie beyond the descriptor; a chunk of a k-contiguous row that does
+    // would alias the next row and is sent out of range (an offset at OOB stays there when a step is added).
+    const int k_a = (int)((lane & 7) ^ (((w4 * 8 + (lane >> 3)) / C::RPP) % C::VM)) * EPC;
+    const int k_b = (int)((lane & 7) ^ (((w4 * 8 + (lane >> 3)) / C::RPP) % C::VN)) * EPC;
+    struct Offsets { uint32_t at[2]; };
+    auto offsets_a = [&](int t) {
+      if constexpr (C::ASRC != A_KC) return Offsets{{va[0], va[1]}};
+      const bool in = k_a < Kx - t * BK;
+      return Offsets{{in ? va[0] : OOB, in ? va[1] : OOB}};
+    };
+    auto offsets_b = [&](int t) {
+      if constexpr (C::BSRC != B_KC) return Offsets{{vb[0], vb[1]}};
+      const bool in = k_b < Kx - t * BK;
+      return Offsets{{in ? vb[0] : OOB, in ? vb[1] : OOB}};
+    };
+    auto load_a = [&](const __amdgpu_buffer_rsrc_t& r, const Offsets& o, GENSOR_LDS char* stage, int i) {
+      load_to_lds(r, stage + (half_a * 16 + i * 4 + w4) * 1024, o.at[i & 1] + (uint32_t)(i >> 1) * step_a);
+    };
+    auto load_b = [&](const __amdgpu_buffer_rsrc_t& r, const Offsets& o, GENSOR_LDS char* stage, int i) {
+      load_to_lds(r, stage + (half_b * 16 + i * 4 + w4) * 1024, o.at[i & 1] + (uint32_t)(i >> 1) * step_b);
+    };
+    auto request_a = [&](int t) {
+      const __amdgpu_buffer_rsrc_t r = rsrc_a(t * BK);
+      const Offsets o = offsets_a(t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_a(r, o, stage_a(t), i);
+    };
+    auto request_b = [&](int t, int t3) {
+      const __amdgpu_buffer_rsrc_t r = rsrc_b(t * BK);
+      const Offsets o = offsets_b(t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_b(r, o, stage_b(t3), i);
+    };
+    auto pin = [&]() { __builtin_amdgcn_sched_barrier(0); };
+    auto end_slot = [&]() { pin(); __builtin_amdgcn_s_barrier(); pin(); };
+    // at most n of this wave's requests outstanding
+    auto landed = [&](auto n_tag) {
+      constexpr int n = decltype(n_tag)::value;
+      pin();
+      __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
+    };
+    // Where this lane reads inside a stage.  A tile's rows are 128 (k-contiguous), 256 (m-contiguous: half a tile) or 512
+    // bytes and blocks and k steps differ in bits that the swizzle only XORs, so every read's address is one exclusive or
+    // away from the lane's first and one immediate offset.
+    auto lane_k = [&](int row, int v) { return (uint32_t)(row * C::PITCH_K + swizzled_chunk(row, fgrp, C::RPP, v) * 16); };
+    auto lane_tr = [&](int pitch, int first_byte, int v) {
+      const int g = lane >> 4, s = lane & 15, krow = g * 8 + (s >> 2);
+      return (uint32_t)(krow * pitch + ((first_byte + (s & 3) * 8) ^ nc_swizzle(krow, v)));
+    };
+    uint32_t lane_a = ASM_A ? wave_m * (C::A_BYTES / 2) + lane_tr(256, 0, C::VM) : lane_k(block_row(0) + frow, C::VM);
+    uint32_t lane_b = ASM_B ? lane_tr(BN * ES, block_col(0) * ES, C::VN) : lane_k(block_col(0) + frow, C::VN);
+    auto read_tr = [&](uint32_t at, auto pitch_tag, auto ks_tag, u32x2& lo, u32x2& hi) {
+      constexpr int pitch = decltype(pitch_tag)::value, k = decltype(ks_tag)::value * C::KG;
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(k * pitch));
+      asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"((k + 4) * pitch));
+    };
+    auto read_k = [&](GENSOR_LDS char* at, auto off_tag, u32x4& frag) {
+      constexpr int off = decltype(off_tag)::value;
+      if constexpr (ASM_TR) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(frag) : "v"((uint32_t)(uintptr_t)at), "n"(off));
+      else frag = *(GENSOR_LDS u32x4*)(at + off);
+    };
+    // fragments of one block of one k step
+    auto read_a = [&](GENSOR_LDS char* stage, auto ks_tag, auto bi_tag) {
+      constexpr int ks = decltype(ks_tag)::value, bi = decltype(bi_tag)::value;
+      if constexpr (ASM_A) read_tr((uint32_t)(uintptr_t)(stage + (lane_a ^ (bi * MB * ES))), std::integral_constant<int, 256>{}, ks_tag, fal[ks][bi], fah[ks][bi]);
+      else read_k(stage + (lane_a ^ (ks * 64)), std::integral_constant<int, bi * MB * C::PITCH_K>{}, fa[ks][bi]);
+    };
+    auto read_b = [&](GENSOR_LDS char* stage, auto ks_tag, auto bj_tag) {
+      constexpr int ks = decltype(ks_tag)::value, bj = decltype(bj_tag)::value;
+      if constexpr (ASM_B) read_tr((uint32_t)(uintptr_t)(stage + (lane_b ^ (bj * MB * ES))), std::integral_constant<int, BN * ES>{}, ks_tag, fbl[ks][bj], fbh[ks][bj]);
+      else read_k(stage + (lane_b ^ (ks * 64)), std::integral_constant<int, bj * MB * C::PITCH_K>{}, fb[ks][bj]);
+    };
+    // A reading slot: the fragments of a tile, with up to four requests of each operand between them (`ra`, `rb`: the tiles
+    // requested), then the wait for all but the youngest `left` requests and the barrier.
+    auto read_slot = [&](int t, int t3, auto ra_tag, int ra, auto rb_tag, int rb, int rb3, auto left_tag) {
+      constexpr bool want_a = decltype(ra_tag)::value, want_b = decltype(rb_tag)::value;
+      const __amdgpu_buffer_rsrc_t qa = rsrc_a(want_a ? ra * BK : 0), qb = rsrc_b(want_b ? rb * BK : 0);
+      const Offsets oa = offsets_a(ra), ob = offsets_b(rb);
+      GENSOR_LDS char* ta = stage_a(t);
+      GENSOR_LDS char* tb = stage_b(t3);
+      asm volatile("" : "+v"(lane_a), "+v"(lane_b));           // (kept from computing all addresses once: they do not fit the registers)
+      constexpr int ITEMS = C::MBLK + C::NBLK;
+      static_for<2 * ITEMS>([&](auto j_tag) {
+        constexpr int j = decltype(j_tag)::value, e = j % ITEMS;
+        constexpr std::integral_constant<int, j / ITEMS> ks{};
+        if constexpr (e < C::NBLK) read_b(tb, ks, std::integral_constant<int, e>{});
+        else read_a(ta, ks, std::integral_constant<int, e - C::NBLK>{});
+        if constexpr (j % 3 == 2) {
+          constexpr int l = j / 3;
+          pin();
+          if constexpr (l < 4 && want_a) load_a(qa, oa, stage_a(ra), l);
+          if constexpr (l >= 4 && want_b) load_b(qb, ob, stage_b(rb3), l - 4);
+          pin();
+        }
+      });
+      landed(left_tag);
+      __builtin_amdgcn_s_waitcnt(0xC07F);                      // the fragments are here: their stage may be overwritten
+      end_slot();
+    };
+    auto multiply = [&]() {
+      settle(0, std::integral_constant<int, 0>{});
+      settle(1, std::integral_constant<int, 0>{});
+#pragma unroll
+      for (int x = 0; x < 2 * NB; ++x) {
+        const int ks = x / NB, bi = x % NB / C::NBLK, j = x % C::NBLK, bj = (bi & 1) ? C::NBLK - 1 - j : j;
+        MF::run(fa[ks][bi], fb[ks][bj], acc[bi][bj]);
+      }
+      pin();
+    };
+    auto third = [&](int t3, int by) { return t3 + by >= 3 ? t3 + by - 3 : t3 + by; };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr std::integral_constant<int, 0> all{};
+    constexpr std::integral_constant<int, 4> but4{};
+    constexpr std::integral_constant<int, 8> but8{};
+    constexpr std::integral_constant<int, 12> but12{};
+    int t = 0, t3 = 0;                                         // k tile, and t % 3
+    request_a(0);
+    request_b(0, 0);
+    if (group == 0) {
+      if (nk > 1) {
+        request_b(1, 1);
+        landed(but4);
+      } else {
+        landed(all);
+      }
+      end_slot();
+      if (nk > 2) read_slot(0, 0, yes, 1, yes, 2, 2, but12);
+      else if (nk > 1) read_slot(0, 0, yes, 1, no, 0, 0, but4);
+      else read_slot(0, 0, no, 0, no, 0, 0, all);
+      for (; t + 3 < nk; ++t, t3 = third(t3, 1)) {
+        multiply();
+        landed(but8);
+        end_slot();
+        read_slot(t + 1, third(t3, 1), yes, t + 2, yes, t + 3, t3, but12);
+      }
+      if (t + 2 < nk) {
+        multiply();
+        landed(but8);
+        end_slot();
+        read_slot(t + 1, third(t3, 1), yes, t + 2, no, 0, 0, but8);
+        ++t;
+        t3 = third(t3, 1);
+      }
+      if (t + 1 < nk) {
+        multiply();
+        landed(all);
+        end_slot();
+        read_slot(t + 1, third(t3, 1), no, 0, no, 0, 0, all);
+      }
+      multiply();
+      end_slot();
+      end_slot();
+    } else {
+      if (nk > 1) {
+        request_a(1);
+        request_b(1, 1);
+        landed(but8);
+      } else {
+        landed(all);
+      }
+      end_slot();
+      end_slot();
+      for (; t + 2 < nk; ++t, t3 = third(t3, 1)) {
+        read_slot(t, t3, yes, t + 2, yes, t + 2, third(t3, 2), but8);
+        multiply();
+        end_slot();
+      }
+      for (; t < nk; ++t, t3 = third(t3, 1)) {
+        read_slot(t, t3, no, 0, no, 0, 0, all);
+        multiply();
+        end_slot();
+      }
+    }
+  } else if constexpr (DEEP) {
     // By the barrier in front of step 2 every wave has read (and received) steps 2 and 3 of this
     // tile, so its stage is free: the loads of tile kt+2 go out right behind the barrier, over
     // steps 2 and 3 and between their MFMAs, a whole k tile before they are needed.
@@ -1164,14 +1397,15 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         }
       }
     };
-    // 16-bit output in whole cache lines: 64 columns of a row are 128 bytes, but a block's row is 64, a lane holds one
+    // 16-bit output in whole cache lines: 64 columns of a row are 128 bytes, but a block's row is 32 or 64, a lane holds one
     // column, and an element store moves two bytes a lane.  So a lane packs rows r and r + 1 of its column, trades with its
-    // neighbour for the column pair of one of the two rows, and a lane swap brings the two blocks side by side together: a store
+    // neighbour for the column pair of one of the two rows, and lane swaps bring the blocks side by side together: a store
     // then writes two whole lines, and half as many are issued.  It pays where a CU holds one workgroup, whose stores nothing
-    // hides: pointwise 32 x 256 x 56 x 56 -> 512 stride 2, fp16, 19.2 -> 18.0 us.  Smaller wave tiles, whose stores run
+    // hides: pointwise 32 x 256 x 56 x 56 -> 512 stride 2, fp16, 19.2 -> 18.0 us; 8192 x 3072 x 768 bf16 on 16x16 blocks 49.6 -> 41.8.
+    // Smaller wave tiles, whose stores run
     // under other waves' products, lose 1-3 % to the packing (96 x 1024 x 1024 x 64 fp16 57.9 -> 59.9, 8192 x 768 x 3072 40.4 ->
     // 40.9) and keep the element stores.
-    constexpr bool PAIRS = OS == 2 && MB == 32 && C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0;
+    constexpr bool PAIRS = OS == 2 && C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0;
     if (PAIRS && args.paired) {
       if constexpr (PAIRS) {
         const uint32_t pick = (lane & 1) ? 0x03020706u : 0x05040100u;      // odd lanes: the second row
@@ -1194,10 +1428,48 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
             const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + (lane & 1)) * pitch;
 #pragma unroll
             for (int v = 0; v < MF::NACC; v += 2) {
-              const int r = 8 * (v / 4) + (v % 4);                         // rows r and r + 1 of the lower lanes, r + 4 and r + 5 of the upper
-              const auto q = __builtin_amdgcn_permlane32_swap(pair_of(bi, bj, v), pair_of(bi, bj + 1, v), false, false);
-              put(q[0], lane_off + (uint32_t)r * pitch);
-              put(q[1], lane_off + (uint32_t)(r + 4) * pitch);
+              const int r = (MB == 32) ? 8 * (v / 4) + (v % 4) : v;        // rows r and r + 1 of lane group 0; groups are four rows apart
+              if constexpr (MB == 32) {
+                const auto q = __builtin_amdgcn_permlane32_swap(pair_of(bi, bj, v), pair_of(bi, bj + 1, v), false, false);
+                put(q[0], lane_off + (uint32_t)r * pitch);
+                put(q[1], lane_off + (uint32_t)(r + 4) * pitch);
+              } else {
+                const auto a = __builtin_amdgcn_permlane16_swap(pair_of(bi, bj, v), pair_of(bi, bj + 1, v), false, false);
+                const auto b = __builtin_amdgcn_permlane16_swap(pair_of(bi, bj + 2, v), pair_of(bi, bj + 3, v), false, false);
+                const auto c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+                const auto d = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+                put(c[0], lane_off + (uint32_t)r * pitch);
+                put(d[0], lane_off + (uint32_t)(r + 4) * pitch);
+                put(c[1], lane_off + (uint32_t)(r + 8) * pitch);
+                put(d[1], lane_off + (uint32_t)(r + 12) * pitch);
+              }
+            }
+          }
+        }
+      }
+      return;
+    }
+    // fp32 output of 16x16 blocks: their rows are half lines, so two blocks side by side trade lane rows first and a store
+    // writes two whole lines
+    constexpr bool ROWS = C::ALTERNATE && OS == 4;
+    if (ROWS && beta == 0.f) {
+      if constexpr (ROWS) {
+        auto put = [&](uint32_t x, uint32_t off) {
+          if (args.through) __builtin_amdgcn_raw_buffer_store_b32(x, rc, off, 0, 16);
+          else __builtin_amdgcn_raw_buffer_store_b32(x, rc, off, 0, 0);
+        };
+#pragma unroll
+        for (int bj = 0; bj < C::NBLK; bj += 2) {
+          const int col = block_col(bj) + (lane & 31);
+          const uint32_t col_off = col < cols_valid ? (uint32_t)(col * OS) : OOB;
+#pragma unroll
+          for (int bi = 0; bi < C::MBLK; ++bi) {
+            const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + 8 * (lane >> 5)) * pitch;
+#pragma unroll
+            for (int v = 0; v < MF::NACC; ++v) {
+              const auto q = __builtin_amdgcn_permlane16_swap(as_u32(alpha * acc[bi][bj][v]), as_u32(alpha * acc[bi][bj + 1][v]), false, false);
+              put(q[0], lane_off + (uint32_t)v * pitch);
+              put(q[1], lane_off + (uint32_t)(v + 4) * pitch);
             }
           }
         }

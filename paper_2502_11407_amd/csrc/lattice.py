@@ -37,6 +37,11 @@ def conv_rows(d):
     return d["bsrc"] == "CONV" and d["direct"] == 1 and d["vec"] == 0
 
 
+def alternate(d):
+    """Two groups of waves that take turns at reading and multiplying (the kernel's ALTERNATE)."""
+    return d["direct"] == 1 and d["stages"] == 2 and d["mb"] == 16 and (d["bm"], d["bn"], d["bk"]) == (256, 256, 64)
+
+
 def _pad(v, row_bytes):
     if v == 1:
         return 0
@@ -222,6 +227,12 @@ def lattice():
             for (bm, bn) in ((128, 256), (256, 128)):
                 out.append(_inst(dt, dt, bm, bn, 64, 64, 64, 32, bsrc=bsrc, stages=3, direct=1))
         out.append(_inst(dt, dt, 256, 256, 64, 128, 64, 32, bsrc="NC", direct=1))
+    # 256x256 tiles of eight waves of 16x16 blocks whose two halves alternate
+    for dt in ("f16", "bf16"):
+        for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+            for odt in ("f32", dt):
+                if odt == "f32" or asrc == "KC":
+                    out.append(_inst(dt, odt, 256, 256, 64, 128, 64, 16, bsrc=bsrc, direct=1, asrc=asrc))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],

@@ -21,6 +21,8 @@ struct InstanceDesc {
   int vec, stages, direct;
   int lds_bytes, threads, kg;           // kg: k consumed per fragment read (lds_bytes 0: set per problem)
   int units;                            // patch-staged convolution: transpose units per thread
+  // 256x256 tiles whose wave groups alternate (Cfg::ALTERNATE); directly staged, they still take any K
+  bool alternate() const { return direct && stages == 2 && mb == 16 && bm == 256 && bn == 256 && bk == 64; }
   bool conv_rows() const { return bsrc == B_CONV && direct && !vec; }      // the row-staged convolution
   hipError_t (*launch)(const KernelArgs&, hipStream_t);
   hipError_t (*launch_split)(const KernelArgs&, hipStream_t);   // the same instance with split tiles; null if not compiled
