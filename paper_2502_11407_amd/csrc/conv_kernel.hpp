@@ -110,7 +110,7 @@ __global__ __launch_bounds__(C::THREADS) void conv_patch_kernel(const KernelArgs
   // workgroup -> (filter tile, pixel tile): contiguous tile ranges per XCD, panels of tile rows
   const int total = args.tiles_m * args.tiles_n;
   int wg = blockIdx.x;
-  if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);
+  wg = xcd_contiguous(wg, total);
   int tile_m, tile_n;
   {
     const int panel = args.panel;

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(C::THREADS, C::MBLK * C::NBLK > 2 ? 2 : 4) void con
 
   const int total = args.tiles_m * args.tiles_n;
   int wg = blockIdx.x;
-  if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);      // a contiguous range of tiles per XCD
+  wg = xcd_contiguous(wg, total);      // a contiguous range of tiles per XCD
   int tile_m, tile_n;
   tile_of(args, wg, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * args.cTilePx;

@@ -267,6 +267,15 @@ __device__ inline __attribute__((always_inline)) void static_for(F&& f) {      /
   }
 }
 
+// Workgroup ids are dealt round-robin to the 8 XCDs.  Number `id` of `count` so that each XCD holds a contiguous range (the
+// first count % 8 of them one more).  Counts that are not a multiple of 8 were left scattered once, so that every XCD fetched all
+// operands: 39 x 669 x 669 x 64 fp16 18.0 -> 15.4 us, 91 x 364 x 364 x 128 bf16 18.6 -> 15.7, split 672 x 344 x 16832 in parts of
+// other counts 1.2 times faster; a pointwise layer of 27 x 128 x 28 x 28 -> 416 12.9 -> 10.5.
+__device__ inline int xcd_contiguous(int id, int count) {
+  const int xcd = id & 7;
+  return xcd * (count >> 3) + min(xcd, count & 7) + (id >> 3);
+}
+
 // tile number inside a batch -> tile coordinates: panels of `panel` tile rows, walked column by column
 __device__ inline void tile_of(const KernelArgs& args, int t, int& tile_m, int& tile_n) {
   const int panel = args.panel;
@@ -306,17 +315,16 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   int wg = blockIdx.x;
   int kpart = 0, kparts = 1;                // this workgroup's share of a split tile
   if constexpr (!SPLIT) {
-    if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);
+    wg = xcd_contiguous(wg, total);
   } else if (wg < args.whole) {
-    if ((args.whole & 7) == 0) wg = (wg & 7) * (args.whole >> 3) + (wg >> 3);
+    wg = xcd_contiguous(wg, args.whole);
   } else {
     // the split tiles come last in launch order, part by part: an XCD then holds neighbouring tiles over one range of
     // k and its L2 fetches each operand's range once for all of them.  Tile by tile it fetched the slabs of its few tiles
     // over the whole of k: 512 x 512 x 32768 in 16 parts read its operands three times over, 38.7 against 29-30 us.
     kparts = args.split;
     const int tiles = total - args.whole, units = tiles * kparts;
-    int u = wg - args.whole;
-    if ((units & 7) == 0) u = (u & 7) * (units >> 3) + (u >> 3);
+    const int u = xcd_contiguous(wg - args.whole, units);
     kpart = u / tiles;
     wg = args.whole + u - kpart * tiles;
   }
