@@ -110,7 +110,7 @@ __global__ __launch_bounds__(C::THREADS) void conv_patch_kernel(const KernelArgs
   // workgroup -> (filter tile, pixel tile): contiguous tile ranges per XCD, panels of tile rows
   const int total = args.tiles_m * args.tiles_n;
   int wg = blockIdx.x;
-  wg = xcd_contiguous(wg, total);
+  if ((total & 7) == 0) wg = xcd_contiguous(wg, total);      // (other counts: no gain from a contiguous range here)
   int tile_m, tile_n;
   {
     const int panel = args.panel;
