@@ -63,6 +63,7 @@ enum { GENSOR_DIM_M = 0, GENSOR_DIM_N = 1, GENSOR_DIM_K = 2 };
  * Loop dimensions are those of the GEMM view: m, n (spatial) and k (reduction); for
  * Conv2d m = filters k, n = (image, out row, out col), k = (channel, filter row, filter col).
  * tile[d][0] = T_2: workgroup tile staged in LDS       (BM, BN, BK)
+ *   (256x256x64 tiles of 16x16 blocks may be cut 192 columns wide by a launch where that takes no more rounds)
  * tile[d][1] = T_1: wavefront tile held in registers   (WM, WN, and the MFMA k depth)
  * tile[d][2] = T_0: extent per virtual thread = tile[d][1] / vthread[d]
  * vthread[d]: virtual threads of Section IV-A / Eq. 3 on this hardware: the rows that one quarter

@@ -392,12 +392,13 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const int e = v.esize, eo = v.osize;
   const int g = e == 2 ? 16 : 8;
   const int mb = kg == g ? 32 : 16;
+  // the tiles whose wave groups alternate (Cfg::ALTERNATE): B has a third stage, and 192 columns may be what a launch cuts
+  const bool alternate = direct && stages == 2 && e == 2 && mb == 16 && bm == 256 && bn == 256 && bk == 64;
+  if (alternate && split == 1 && narrow_tiles(v, hw.compute_units)) { bn = 192; wm = 64; wn = 96; }
   const double tiles_m = std::ceil((double)v.M / bm), tiles_n = std::ceil((double)v.N / bn);
   const double tiles = tiles_m * tiles_n * (double)v.batch;
   const int nwaves = (bm / wm) * (bn / wn);
   if (nwaves > hw.max_waves_per_wg) return -1.0;
-  // the tiles whose wave groups alternate (Cfg::ALTERNATE): B has a third stage
-  const bool alternate = direct && stages == 2 && e == 2 && mb == 16 && bm == 256 && bn == 256 && bk == 64;
   const int lds = stages * e * bk * (bm + bn) + (alternate ? e * bk * bn : 0);
   if (lds > hw.lds_bytes_per_cu) return -1.0;
   const int regs = wm * wn / 64 + 2 * (wm + wn) * kg * e / 256 + (direct ? 0 : (e * bk * (bm + bn)) / (nwaves * 64 * 4)) + 32;
@@ -444,7 +445,8 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (direct && v.bsrc == B_KC && stages == 2 && wm * wn >= 128 * 128 && bk == 4 * kg) overlap += 0.24;   // the two-steps-ahead schedule of the one-wave-per-SIMD tiles (k-contiguous operands: measured)
   // (the alternating groups: one multiplies while the other waits, 94 % of the MFMA rate on all-zero operands, and no boundary
   // of a k tile is exposed; 4096^3 105 us against 124 of the next tile, 3648 x 2624 x 1856 38 against 41)
-  if (alternate) overlap = 1.3;
+  // (192 columns: a k tile takes 0.80 of the time of a wide one's, not 0.75)
+  if (alternate) overlap = bn == 192 ? 1.22 : 1.3;
   double t_main = t_mfma;
   if (t_lds > t_main) t_main = t_lds;
   if (t_feed > t_main) t_main = t_feed;

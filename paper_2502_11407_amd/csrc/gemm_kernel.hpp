@@ -59,6 +59,7 @@ struct KernelArgs {
   float alpha, beta;
   int32_t through;                 // C is stored write-through (beside beta only with fp32 output)
   int32_t paired;                  // 16-bit C without beta whose columns 2j and 2j + 1 are one aligned dword
+  int32_t narrow;                  // tiles of 192 instead of 256 columns (instances whose wave groups alternate; the launch selects them)
   int32_t tiles_m, tiles_n, batch;
   int32_t panel;                   // tile rows per panel in the workgroup->tile map
   int64_t ahead_a, ahead_b;        // bytes of the next batch's A and B that this batch's workgroups read ahead (0: none)
@@ -217,7 +218,9 @@ struct Cfg {
   static constexpr int B_BYTES = (BSRC == B_KC) ? BN * PITCH_K : BK * PITCH_N;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   // Two groups of four waves that take turns at reading and multiplying (the loop says how); B has a third stage.
-  static constexpr bool ALTERNATE = DIRECT_ && STAGES_ == 2 && MB_ == 16 && ES == 2 && BM_ == 256 && BN_ == 256 && BK_ == 64 && WM_ == 128 && WN_ == 64;
+  static constexpr bool ALTERNATE = DIRECT_ && STAGES_ == 2 && MB_ == 16 && ES == 2 && BM_ == 256 && BK_ == 64 &&
+                                    ((BN_ == 256 && WM_ == 128 && WN_ == 64) || (BN_ == 192 && WM_ == 64 && WN_ == 96));
+  static constexpr bool HAS_NARROW = ALTERNATE && BN_ == 256;
   static constexpr int LDS_BYTES = STAGE_BYTES * STAGES + (ALTERNATE ? B_BYTES : 0);
   static constexpr int A_CHUNKS = (ASRC == A_KC) ? BM * CPR : BK * (BM * ES / 16);
   static constexpr int B_CHUNKS = (BSRC == B_KC) ? BN * CPR : BK * (BN * ES / 16);
@@ -251,6 +254,13 @@ struct Cfg {
                 "rings of three and more stages are filled by direct loads");
   static_assert(STAGES <= 2 || (A_LOADS + B_LOADS) * (STAGES - 2) <= 63, "the load counter holds 63");
 };
+
+// The 192-column form of an instance whose wave groups alternate: three quarters of the work a tile for the shapes whose 256-column
+// tiles end in a partly filled round (8192 x 3072 x 768: 384 tiles of 256 columns are one and a half rounds, 512 of 192 two full ones;
+// 42.2 -> 38.8 us, 2880 x 3648 x 2048 50.2 -> 45.1, 3264 x 2560 x 3264 64.5 -> 60.0).  The LDS sets its pace: 864 cycles of reads and
+// deposits beside 768 of products a slot.
+template <typename C>
+using NarrowCfg = Cfg<typename C::T, typename C::OutT, 256, 192, 64, 64, 96, 16, C::VM, C::VN, C::BSRC, true, 2, true, C::ASRC>;
 
 __device__ inline int swizzled_chunk(int row, int chunk, int rpp, int v) { return chunk ^ ((row / rpp) % v); }
 // Byte XOR applied inside an unpadded n-contiguous row of k row `krow`: of the four rows a
@@ -895,19 +905,33 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     // 4096^3 f16 118 -> 104 us (all-zero operands 79 -> 70), 8192^3 911 -> 800 (771 -> 575), against four 128x128 waves of 32x32 blocks.
     // Raising the wave priority while multiplying starves the readers (108 us on zeros); MFMAs behind the barrier of their
     // slot, to cover it, delay the next slot's reads (81 us).
-    static_assert(C::KSTEPS == 2 && C::A_BYTES == 32768 && C::B_BYTES == 32768, "two k steps; 32 KiB an operand");
+    // Tiles of 192 columns (NarrowCfg): a group's four waves are two by two of 64x96 instead of four of 128x64 side by side, which
+    // reads 160 rows a wave and k tile where 128x48 waves would read 176.
+    static_assert(C::KSTEPS == 2 && C::A_BYTES == 32768 && C::B_BYTES == BN * 128, "two k steps; 32 KiB of A, 128 bytes of B a column");
+    constexpr int WM2 = C::WAVES_M / 2;                        // rows of waves in a group
+    constexpr int NA = 4, NBR = BN / 64;                       // a wave's requests of each operand: 1 KiB runs of one half of its tile
     constexpr int NB = C::MBLK * C::NBLK;
     const int group = wave >> 2, w4 = wave & 3;
     auto stage_a = [&](int t) { return lds + (t & 1) * C::A_BYTES; };
     auto stage_b = [&](int t3) { return lds + 2 * C::A_BYTES + t3 * C::B_BYTES; };
-    // This wave's requests: four 1 KiB runs of one half of each operand's tile.  (Chunks 512 apart have the same swizzle.)
+    // This wave's requests: 1 KiB runs of one half of each operand's tile.  (Chunks 512 apart have the same swizzle, but for the
+    // rows of 24 chunks of an n-contiguous B.)
+    // Rows of an n-contiguous B are whole 128-byte groups; of four k rows read together the pitch of an odd number of groups
+    // already spreads two over the banks, and only the other bit is left to the swizzle, which stays inside a group.
+    auto swizzle_b = [&](int krow) -> int {
+      if constexpr (BN * ES % 256 == 0) return nc_swizzle(krow, C::VN);
+      else return C::VN >= 4 ? ((krow >> 1 & 1) << 6) ^ ((krow >> 3 & 1) << 5) : 0;
+    };
     // An m-contiguous A is kept as two halves [k][128 rows]: a run has to be contiguous in the LDS and in one half.
     const int half_a = 1 - group, half_b = group;
-    uint32_t va[2], vb[2], step_a, step_b;
+    constexpr bool ROWS_24 = C::BSRC != B_KC && NBR == 3;
+    constexpr int VB = ROWS_24 ? 3 : 2;
+    uint32_t va[2], vb[VB], step_a, step_b = 0;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < VB; ++i) {
       const int q = (i * 4 + w4) * 64 + lane;                  // chunk inside the half
-      if constexpr (C::ASRC == A_KC) {
+      if (i >= 2) {
+      } else if constexpr (C::ASRC == A_KC) {
         const int row = half_a * 128 + q / C::CPR;
         va[i] = (uint32_t)((row * (int)args.lda + swizzled_chunk(row, q % C::CPR, C::RPP, C::VM) * EPC) * ES);
         step_a = (uint32_t)((512 / C::CPR) * (int)args.lda * ES);
@@ -916,49 +940,50 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         va[i] = (uint32_t)((krow * (int)args.lda + half_a * 128 + ch * EPC) * ES);
         step_a = (uint32_t)((512 / 16) * (int)args.lda * ES);
       }
-      const int q2 = half_b * 1024 + q;
+      const int q2 = half_b * (NBR * 256) + q;
       if constexpr (C::BSRC == B_KC) {
         const int row = q2 / C::CPR;
         vb[i] = (uint32_t)((row * (int)args.ldb + swizzled_chunk(row, q2 % C::CPR, C::RPP, C::VN) * EPC) * ES);
         step_b = (uint32_t)((512 / C::CPR) * (int)args.ldb * ES);
       } else {
-        const int krow = q2 / 32, ch = (q2 % 32) ^ (nc_swizzle(krow, C::VN) >> 4);
+        constexpr int CPRN = BN * ES / 16;
+        const int krow = q2 / CPRN, ch = (q2 % CPRN) ^ (swizzle_b(krow) >> 4);
         vb[i] = (uint32_t)((krow * (int)args.ldb + ch * EPC) * ES);
-        step_b = (uint32_t)((512 / 32) * (int)args.ldb * ES);
+        if constexpr (!ROWS_24) step_b = (uint32_t)((512 / CPRN) * (int)args.ldb * ES);
       }
     }
     // K need not be a multiple of BK: k rows beyond it lie beyond the descriptor; a chunk of a k-contiguous row that does
     // would alias the next row and is sent out of range (an offset at OOB stays there when a step is added).
     const int k_a = (int)((lane & 7) ^ (((w4 * 8 + (lane >> 3)) / C::RPP) % C::VM)) * EPC;
     const int k_b = (int)((lane & 7) ^ (((w4 * 8 + (lane >> 3)) / C::RPP) % C::VN)) * EPC;
-    struct Offsets { uint32_t at[2]; };
+    struct Offsets { uint32_t at[3]; };
     auto offsets_a = [&](int t) {
-      if constexpr (C::ASRC != A_KC) return Offsets{{va[0], va[1]}};
+      if constexpr (C::ASRC != A_KC) return Offsets{{va[0], va[1], 0}};
       const bool in = k_a < Kx - t * BK;
-      return Offsets{{in ? va[0] : OOB, in ? va[1] : OOB}};
+      return Offsets{{in ? va[0] : OOB, in ? va[1] : OOB, 0}};
     };
     auto offsets_b = [&](int t) {
-      if constexpr (C::BSRC != B_KC) return Offsets{{vb[0], vb[1]}};
+      if constexpr (C::BSRC != B_KC) return Offsets{{vb[0], vb[1], vb[VB - 1]}};
       const bool in = k_b < Kx - t * BK;
-      return Offsets{{in ? vb[0] : OOB, in ? vb[1] : OOB}};
+      return Offsets{{in ? vb[0] : OOB, in ? vb[1] : OOB, 0}};
     };
     auto load_a = [&](const __amdgpu_buffer_rsrc_t& r, const Offsets& o, GENSOR_LDS char* stage, int i) {
       load_to_lds(r, stage + (half_a * 16 + i * 4 + w4) * 1024, o.at[i & 1] + (uint32_t)(i >> 1) * step_a);
     };
     auto load_b = [&](const __amdgpu_buffer_rsrc_t& r, const Offsets& o, GENSOR_LDS char* stage, int i) {
-      load_to_lds(r, stage + (half_b * 16 + i * 4 + w4) * 1024, o.at[i & 1] + (uint32_t)(i >> 1) * step_b);
+      load_to_lds(r, stage + (half_b * (NBR * 4) + i * 4 + w4) * 1024, ROWS_24 ? o.at[i] : o.at[i & 1] + (uint32_t)(i >> 1) * step_b);
     };
     auto request_a = [&](int t) {
       const __amdgpu_buffer_rsrc_t r = rsrc_a(t * BK);
       const Offsets o = offsets_a(t);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_a(r, o, stage_a(t), i);
+      for (int i = 0; i < NA; ++i) load_a(r, o, stage_a(t), i);
     };
     auto request_b = [&](int t, int t3) {
       const __amdgpu_buffer_rsrc_t r = rsrc_b(t * BK);
       const Offsets o = offsets_b(t);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_b(r, o, stage_b(t3), i);
+      for (int i = 0; i < NBR; ++i) load_b(r, o, stage_b(t3), i);
     };
     auto pin = [&]() { __builtin_amdgcn_sched_barrier(0); };
     auto end_slot = [&]() { pin(); __builtin_amdgcn_s_barrier(); pin(); };
@@ -968,16 +993,20 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       pin();
       __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
     };
-    // Where this lane reads inside a stage.  A tile's rows are 128 (k-contiguous), 256 (m-contiguous: half a tile) or 512
+    // Where this lane reads inside a stage.  A tile's rows are 128 (k-contiguous), 256 (m-contiguous: half a tile), 384 or 512
     // bytes and blocks and k steps differ in bits that the swizzle only XORs, so every read's address is one exclusive or
     // away from the lane's first and one immediate offset.
     auto lane_k = [&](int row, int v) { return (uint32_t)(row * C::PITCH_K + swizzled_chunk(row, fgrp, C::RPP, v) * 16); };
-    auto lane_tr = [&](int pitch, int first_byte, int v) {
-      const int g = lane >> 4, s = lane & 15, krow = g * 8 + (s >> 2);
-      return (uint32_t)(krow * pitch + ((first_byte + (s & 3) * 8) ^ nc_swizzle(krow, v)));
-    };
-    uint32_t lane_a = ASM_A ? wave_m * (C::A_BYTES / 2) + lane_tr(256, 0, C::VM) : lane_k(block_row(0) + frow, C::VM);
-    uint32_t lane_b = ASM_B ? lane_tr(BN * ES, block_col(0) * ES, C::VN) : lane_k(block_col(0) + frow, C::VN);
+    const int tr_row = (lane >> 4) * 8 + ((lane & 15) >> 2);
+    auto lane_tr = [&](int pitch, int first_byte, int swizzle) { return (uint32_t)(tr_row * pitch + ((first_byte + (lane & 3) * 8) ^ swizzle)); };
+    uint32_t lane_a = ASM_A ? group * (C::A_BYTES / 2) + lane_tr(256, wave_m % WM2 * C::WM * ES, nc_swizzle(tr_row, C::VM))
+                            : lane_k(block_row(0) + frow, C::VM);
+    // (a wave's 96 columns start on half a 128-byte group: one address for each two blocks)
+    constexpr int LB = ASM_B && C::WN % 64 != 0 ? C::NBLK / 2 : 1;
+    uint32_t lane_b[LB];
+#pragma unroll
+    for (int p = 0; p < LB; ++p)
+      lane_b[p] = ASM_B ? lane_tr(BN * ES, block_col(2 * p) * ES, swizzle_b(tr_row)) : lane_k(block_col(0) + frow, C::VN);
     auto read_tr = [&](uint32_t at, auto pitch_tag, auto ks_tag, u32x2& lo, u32x2& hi) {
       constexpr int pitch = decltype(pitch_tag)::value, k = decltype(ks_tag)::value * C::KG;
       asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(at), "n"(k * pitch));
@@ -996,10 +1025,10 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     };
     auto read_b = [&](GENSOR_LDS char* stage, auto ks_tag, auto bj_tag) {
       constexpr int ks = decltype(ks_tag)::value, bj = decltype(bj_tag)::value;
-      if constexpr (ASM_B) read_tr((uint32_t)(uintptr_t)(stage + (lane_b ^ (bj * MB * ES))), std::integral_constant<int, BN * ES>{}, ks_tag, fbl[ks][bj], fbh[ks][bj]);
-      else read_k(stage + (lane_b ^ (ks * 64)), std::integral_constant<int, bj * MB * C::PITCH_K>{}, fb[ks][bj]);
+      if constexpr (ASM_B) read_tr((uint32_t)(uintptr_t)(stage + (lane_b[LB > 1 ? bj / 2 : 0] ^ ((LB > 1 ? bj % 2 : bj) * MB * ES))), std::integral_constant<int, BN * ES>{}, ks_tag, fbl[ks][bj], fbh[ks][bj]);
+      else read_k(stage + (lane_b[0] ^ (ks * 64)), std::integral_constant<int, bj * MB * C::PITCH_K>{}, fb[ks][bj]);
     };
-    // A reading slot: the fragments of a tile, with up to four requests of each operand between them (`ra`, `rb`: the tiles
+    // A reading slot: the fragments of a tile, with this wave's requests of each operand between them (`ra`, `rb`: the tiles
     // requested), then the wait for all but the youngest `left` requests and the barrier.
     auto read_slot = [&](int t, int t3, auto ra_tag, int ra, auto rb_tag, int rb, int rb3, auto left_tag) {
       constexpr bool want_a = decltype(ra_tag)::value, want_b = decltype(rb_tag)::value;
@@ -1007,18 +1036,18 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       const Offsets oa = offsets_a(ra), ob = offsets_b(rb);
       GENSOR_LDS char* ta = stage_a(t);
       GENSOR_LDS char* tb = stage_b(t3);
-      asm volatile("" : "+v"(lane_a), "+v"(lane_b));           // (kept from computing all addresses once: they do not fit the registers)
+      asm volatile("" : "+v"(lane_a), "+v"(lane_b[0]));        // (kept from computing all addresses once: they do not fit the registers)
       constexpr int ITEMS = C::MBLK + C::NBLK;
       static_for<2 * ITEMS>([&](auto j_tag) {
         constexpr int j = decltype(j_tag)::value, e = j % ITEMS;
         constexpr std::integral_constant<int, j / ITEMS> ks{};
         if constexpr (e < C::NBLK) read_b(tb, ks, std::integral_constant<int, e>{});
         else read_a(ta, ks, std::integral_constant<int, e - C::NBLK>{});
-        if constexpr (j % 3 == 2) {
-          constexpr int l = j / 3;
+        constexpr int l = (j + 1) * (NA + NBR) / (2 * ITEMS) - 1;          // the request behind this read
+        if constexpr ((j + 1) * (NA + NBR) / (2 * ITEMS) > j * (NA + NBR) / (2 * ITEMS)) {
           pin();
-          if constexpr (l < 4 && want_a) load_a(qa, oa, stage_a(ra), l);
-          if constexpr (l >= 4 && want_b) load_b(qb, ob, stage_b(rb3), l - 4);
+          if constexpr (l < NA && want_a) load_a(qa, oa, stage_a(ra), l);
+          if constexpr (l >= NA && want_b) load_b(qb, ob, stage_b(rb3), l - NA);
           pin();
         }
       });
@@ -1040,34 +1069,35 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
     constexpr std::integral_constant<int, 0> all{};
-    constexpr std::integral_constant<int, 4> but4{};
-    constexpr std::integral_constant<int, 8> but8{};
-    constexpr std::integral_constant<int, 12> but12{};
+    constexpr std::integral_constant<int, NA> but_a{};         // all but the requests of one tile of A, of B, of both, and of another B
+    constexpr std::integral_constant<int, NBR> but_b{};
+    constexpr std::integral_constant<int, NA + NBR> but_ab{};
+    constexpr std::integral_constant<int, NA + 2 * NBR> but_ab2{};
     int t = 0, t3 = 0;                                         // k tile, and t % 3
     request_a(0);
     request_b(0, 0);
     if (group == 0) {
       if (nk > 1) {
         request_b(1, 1);
-        landed(but4);
+        landed(but_b);
       } else {
         landed(all);
       }
       end_slot();
-      if (nk > 2) read_slot(0, 0, yes, 1, yes, 2, 2, but12);
-      else if (nk > 1) read_slot(0, 0, yes, 1, no, 0, 0, but4);
+      if (nk > 2) read_slot(0, 0, yes, 1, yes, 2, 2, but_ab2);
+      else if (nk > 1) read_slot(0, 0, yes, 1, no, 0, 0, but_a);
       else read_slot(0, 0, no, 0, no, 0, 0, all);
       for (; t + 3 < nk; ++t, t3 = third(t3, 1)) {
         multiply();
-        landed(but8);
+        landed(but_ab);
         end_slot();
-        read_slot(t + 1, third(t3, 1), yes, t + 2, yes, t + 3, t3, but12);
+        read_slot(t + 1, third(t3, 1), yes, t + 2, yes, t + 3, t3, but_ab2);
       }
       if (t + 2 < nk) {
         multiply();
-        landed(but8);
+        landed(but_ab);
         end_slot();
-        read_slot(t + 1, third(t3, 1), yes, t + 2, no, 0, 0, but8);
+        read_slot(t + 1, third(t3, 1), yes, t + 2, no, 0, 0, but_ab);
         ++t;
         t3 = third(t3, 1);
       }
@@ -1084,14 +1114,14 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       if (nk > 1) {
         request_a(1);
         request_b(1, 1);
-        landed(but8);
+        landed(but_ab);
       } else {
         landed(all);
       }
       end_slot();
       end_slot();
       for (; t + 2 < nk; ++t, t3 = third(t3, 1)) {
-        read_slot(t, t3, yes, t + 2, yes, t + 2, third(t3, 2), but8);
+        read_slot(t, t3, yes, t + 2, yes, t + 2, third(t3, 2), but_ab);
         multiply();
         end_slot();
       }
@@ -1413,7 +1443,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     // Smaller wave tiles, whose stores run
     // under other waves' products, lose 1-3 % to the packing (96 x 1024 x 1024 x 64 fp16 57.9 -> 59.9, 8192 x 768 x 3072 40.4 ->
     // 40.9) and keep the element stores.
-    constexpr bool PAIRS = OS == 2 && C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0;
+    // (Waves of 96 columns, three pairs of 16x16 blocks: half lines.)
+    constexpr bool PAIRS = OS == 2 && (C::ALTERNATE || (C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0));
+    constexpr bool HALF_LINES = C::WN % 64 != 0;
     if (PAIRS && args.paired) {
       if constexpr (PAIRS) {
         const uint32_t pick = (lane & 1) ? 0x03020706u : 0x05040100u;      // odd lanes: the second row
@@ -1426,19 +1458,23 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           if (args.through) __builtin_amdgcn_raw_buffer_store_b32(x, rc, off, 0, 16);
           else __builtin_amdgcn_raw_buffer_store_b32(x, rc, off, 0, 0);
         };
-        constexpr int GB = 64 / MB;                                        // blocks in 64 columns
+        constexpr int GB = (HALF_LINES ? 32 : 64) / MB;                    // blocks in 64 (32) columns
 #pragma unroll
         for (int bj = 0; bj < C::NBLK; bj += GB) {
-          const int col = block_col(bj) + (lane / MB) * MB + (lane % MB & ~1);
+          const int col = block_col(bj) + (lane % (GB * MB) & ~1);
           const uint32_t col_off = col < cols_valid ? (uint32_t)(col * OS) : OOB;
 #pragma unroll
           for (int bi = 0; bi < C::MBLK; ++bi) {
-            const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + (lane & 1)) * pitch;
+            const uint32_t lane_off = col_off + (uint32_t)(block_row(bi) + (lane & 1) + (HALF_LINES ? 8 * (lane >> 5) : 0)) * pitch;
 #pragma unroll
             for (int v = 0; v < MF::NACC; v += 2) {
               const int r = (MB == 32) ? 8 * (v / 4) + (v % 4) : v;        // rows r and r + 1 of lane group 0; groups are four rows apart
               if constexpr (MB == 32) {
                 const auto q = __builtin_amdgcn_permlane32_swap(pair_of(bi, bj, v), pair_of(bi, bj + 1, v), false, false);
+                put(q[0], lane_off + (uint32_t)r * pitch);
+                put(q[1], lane_off + (uint32_t)(r + 4) * pitch);
+              } else if constexpr (HALF_LINES) {
+                const auto q = __builtin_amdgcn_permlane16_swap(pair_of(bi, bj, v), pair_of(bi, bj + 1, v), false, false);
                 put(q[0], lane_off + (uint32_t)r * pitch);
                 put(q[1], lane_off + (uint32_t)(r + 4) * pitch);
               } else {

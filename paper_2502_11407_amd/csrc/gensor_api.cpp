@@ -405,13 +405,15 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   a.through = !partial_lines && (beta == 0.f || beside_beta);
   a.paired = v.osize == 2 && beta == 0.f && v.N % 2 == 0 && ldc % 2 == 0 && strideC % 2 == 0 && (reinterpret_cast<uintptr_t>(C) & 3u) == 0;
   a.tiles_m = (int32_t)((v.M + d->bm - 1) / d->bm);
-  a.tiles_n = (int32_t)((v.N + d->bn - 1) / d->bn);
+  a.narrow = d->alternate() && sp.split == 1 && narrow_tiles(v, s->round_units > 0 ? s->round_units : gensor_hw_mi355x()->compute_units);
+  const int bn = a.narrow ? 192 : d->bn;
+  a.tiles_n = (int32_t)((v.N + bn - 1) / bn);
   a.batch = (int32_t)v.batch;
   a.panel = s->wg_remap > 0 ? s->wg_remap : 1;
   if (a.panel > a.tiles_m) a.panel = a.tiles_m;
   if ((int64_t)a.tiles_m * a.tiles_n * a.batch > INT32_MAX) return GENSOR_ERR_UNSUPPORTED;
   a.split = sp.split;
-  a.whole = (int32_t)sp.whole;
+  a.whole = sp.split == 1 ? a.tiles_m * a.tiles_n * a.batch : (int32_t)sp.whole;
   // Read ahead where the launch moves more than the 256 MiB Infinity Cache holds (its operands then come from memory; from
   // that cache they come soon enough, and the wait at the end of each wave costs 2-10 %: 96 x 1024 x 1024 x 64 with fp16
   // output 61 -> 69 us, 48 x 768 x 768 x 64 21.1 -> 23.4), a batch is one or two k tiles deep, an XCD works through whole batches (its range of tiles is

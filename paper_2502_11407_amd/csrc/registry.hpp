@@ -51,6 +51,9 @@ hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
   if constexpr (C::HAS_AHEAD && !SPLIT && !AHEAD) {
     if (a.ahead_a + a.ahead_b > 0) return launch_instance<C, false, true>(a, st);
   }
+  if constexpr (C::HAS_NARROW && !SPLIT) {
+    if (a.narrow) return launch_instance<NarrowCfg<C>>(a, st);
+  }
   static std::atomic<uint64_t> done{0};
   hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT, AHEAD>, C::LDS_BYTES, done);
   if (e != hipSuccess) return e;
