@@ -443,6 +443,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (direct && v.bsrc == B_KC) overlap += 0.05;      // measured: what direct staging pays for k-contiguous operands
   if (direct && v.bsrc == B_NC) overlap += 0.03;      // ... and for an n-contiguous B
   if (direct && v.bsrc == B_KC && stages == 2 && wm * wn >= 128 * 128 && bk == 4 * kg) overlap += 0.24;   // the two-steps-ahead schedule of the one-wave-per-SIMD tiles (k-contiguous operands: measured)
+  // (three k tiles in flight: whole tiles were priced 7-20 % above the measured time without; parts of split ones were not, against
+  // the smaller tiles that share their units: 128 x 264 x 28672 in 16 parts 18.9 us against 16.4)
+  if (stages >= 4 && split == 1 && v.K > 3 * bk) overlap += 0.12;
   // (the alternating groups: one multiplies while the other waits, 94 % of the MFMA rate on all-zero operands, and no boundary
   // of a k tile is exposed; 4096^3 105 us against 124 of the next tile, 3648 x 2624 x 1856 38 against 41)
   // (192 columns: a k tile takes 0.80 of the time of a wide one's, not 0.75)
@@ -452,7 +455,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (t_feed > t_main) t_main = t_feed;
   // every k tile boundary (barrier, refill of the fragment pipeline) exposes a share of the memory latency
   // (a ring of three and more stages keeps more tiles in flight)
-  const double t_ktile = alternate ? 0.0 : 0.3 * hw.latency_ns[0] * 1e-3;
+  // (small register-staged tiles keep two k tiles of loads in flight, too: Cfg::RSETS)
+  const bool two_sets = !direct && vec && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && bm * bn <= 128 * 64;
+  const double t_ktile = alternate ? 0.0 : (two_sets ? 0.15 : 0.3) * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;
     // (a ring fills stages - 1 tiles before its first product: those boundaries are paid in full, measured as no gain
@@ -493,7 +498,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double t_hbm = (bytes_total + bytes_swap) / (0.9 * hw.bandwidth_gbs[0] * 1e3);
   // soft roofline: the smaller of the two limits still costs a fraction (imperfect overlap)
   const bool prepass = v.pointwise && v.cstride > 1 && v.bsrc != B_NCS2;   // the input is compacted by a dependent launch of its own
-  return (t_cu > t_hbm ? t_cu : t_hbm) + 0.2 * (t_cu > t_hbm ? t_hbm : t_cu) + hw.launch_us * (prepass ? 3.5 : 1.0) +
+  // (a ring of four that never fills keeps a second workgroup's stages for nothing: 96 x 1024 x 1024 x 64 76 us against 63)
+  const double unfilled = stages >= 4 && nk < stages ? 1.1 : 1.0;
+  return unfilled * ((t_cu > t_hbm ? t_cu : t_hbm) + 0.2 * (t_cu > t_hbm ? t_hbm : t_cu)) + hw.launch_us * (prepass ? 3.5 : 1.0) +
          (split > 1 ? 2.0 * hw.launch_us + bytes_swap / (0.5 * hw.bandwidth_gbs[0] * 1e3) : 0.0);
 }
 

@@ -233,6 +233,18 @@ def lattice():
             for odt in ("f32", dt):
                 if odt == "f32" or asrc == "KC":
                     out.append(_inst(dt, odt, 256, 256, 64, 128, 64, 16, bsrc=bsrc, direct=1, asrc=asrc))
+    # rings of four stages for the 128x128 tiles of eight 64x32 waves: launches of about one tile per compute unit, where one
+    # k tile in flight does not cover the latency (1280 x 1792 x 2048 f16 20.5 -> 17.1 us, 1536 x 2304 x 3072 32.5 -> 27.9,
+    # 1856 x 1280 x 3264 30.8 -> 25.6, 1024 x 3072 x 768 row-major B 11.9 -> 10.0, 3072 x 768 x 4096 transA 34.0 -> 32.3).  Five stages
+    # are within 3 % either way; 64x64 waves are 6-13 % slower.
+    for dt in ("f16", "bf16"):
+        for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+            for odt in ("f32", dt):
+                if odt == "f32" or asrc == "KC":
+                    out.append(_inst(dt, odt, 128, 128, 64, 64, 32, 32, bsrc=bsrc, stages=4, direct=1, asrc=asrc))
+        # (the walks reach the eight-wave state less often where both operands are k-contiguous and k is deep)
+        for odt in ("f32", dt):
+            out.append(_inst(dt, odt, 128, 128, 64, 64, 64, 32, stages=4, direct=1))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],
