@@ -385,6 +385,7 @@ double predict_rows(const GemmView& v, const gensor_hw& hw, int bm, int bn, int 
 // partial tiles in device memory and a dependent launch adds them up.  Infeasible if there is nothing to split.
 double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, int wm, int wn, int kg,
                int vm, int vn, int vec, int stages, int direct, int split) {
+  if (hw.compute_units < 1) return -1.0;              // rounds of tiles are whole-number divisions by it
   if (v.bsrc == B_CONV && direct && !vec) return split == 1 ? predict_rows(v, hw, bm, bn, wm, wn) : -1.0;
   if (v.bsrc == B_CONV && direct) return split == 1 ? predict_patch(v, hw, bm, bn, bk, wm, wn, kg, stages) : -1.0;
   if (split < 1 || (split > 1 && v.bsrc != B_KC && v.bsrc != B_NC)) return -1.0;

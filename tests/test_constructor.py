@@ -476,3 +476,28 @@ def test_construct_rejects_bad_problems():
     with pytest.raises(gs.GensorError) as e:
         gs.construct(gs.gemm_problem("f16", 64, 64, 64, 0, 0, 1, "bf16"))      # output neither fp32 nor the input type
     assert e.value.status == 2
+
+
+def test_hardware_without_compute_units_is_infeasible_not_fatal():
+    """A description with no compute units has no schedule and no price: an error code, not a division that ends the process (so
+    the calls run in a process of their own)."""
+    import os
+    import subprocess
+    import sys
+    code = """
+import ctypes as C
+from paper_2502_11407_amd import binding as gs
+hw = gs.Hw.from_buffer_copy(gs.hw_mi355x())
+for units in (0, -1):
+    hw.compute_units = units
+    for p in (gs.gemm_problem("f16", 4096, 4096, 4096, 0, 1), gs.conv_problem("f16", 16, 64, 56, 56, 64, 3, 3, 1, 1)):
+        s = gs.Schedule()
+        assert gs.lib.gensor_construct(C.byref(p), C.byref(hw), None, 0, C.byref(s)) == 3, units
+        for i in range(gs.num_instances()):
+            t = gs.instance_schedule(i, p)
+            assert t is None or gs.predict_us(t, p, hw) < 0, (units, i)
+print("done")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "done" in r.stdout, (r.returncode, r.stderr[-2000:])
