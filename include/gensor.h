@@ -168,6 +168,9 @@ gensor_status gensor_instance_schedule(int32_t id, const gensor_problem* p, gens
  * elements (lda >= K, or M if transA: A is then stored [K][M]; ldb >= N, or K if transB: B stored
  * [N][K]; ldc >= N).
  * s == NULL: a schedule is constructed for `p` (seed 0) and remembered per shape.
+ * Tiles are addressed with 32-bit offsets and a schedule does not know the leading dimensions: where the rows of its tile are
+ * too far apart (a tile of BM rows reaches leading dimensions of 2^31 / (BM + 1) bytes), the call runs a schedule of tiles that
+ * reach instead, which needs no more than `workspace`; UNSUPPORTED if there is none.
  *
  * Split-k (s->split_k > 1).  Tiles are dealt to the compute units in rounds of
  * s->round_units.  The tiles of the last round, if it is not full (every

@@ -513,8 +513,9 @@ double predict_instance(const GemmView& v, const gensor_hw& hw, const InstanceDe
 // split factors the ranking tries on every candidate instance
 const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
-bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok) {
+bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok, const LeadingDims* ld) {
   if (!instance_serves(d, v)) return false;
+  if (ld && !offsets_fit(d, v, *ld)) return false;
   if (d.vec && !vec_ok) return false;
   if (d.direct && !d.alternate() && v.bsrc != B_CONV && v.K % d.bk != 0) return false;
   return true;
@@ -523,7 +524,7 @@ bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok) {
 }  // namespace
 
 gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, const gensor_construct_opts* opts,
-                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out) {
+                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld) {
   if (!p || !out) return GENSOR_ERR_INVALID_ARG;
   const auto t0 = std::chrono::steady_clock::now();
   GemmView v;
@@ -557,7 +558,7 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
       const InstanceDesc& d = g_instances[i];
       if (d.bm != e.tile[0][0] || d.bn != e.tile[1][0] || d.wm != e.tile[0][1] || d.wn != e.tile[1][1]) continue;
       if (!d.units && !d.conv_rows() && (d.bk != e.tile[2][0] || d.kg != e.tile[2][1] || d.vm != e.v[0] || d.vn != e.v[1])) continue;
-      if (!usable(d, v, vec_ok)) continue;
+      if (!usable(d, v, vec_ok, ld)) continue;
       for (int split : kSplits) {
         if (split > 1 && c.opts.no_split_k) break;
         const double us = predict_instance(v, c.hw, d, split);
@@ -576,7 +577,7 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
     double bd = 0.0;
     for (int i = 0; i < g_num_instances; ++i) {
       const InstanceDesc& d = g_instances[i];
-      if (!usable(d, v, vec_ok)) continue;
+      if (!usable(d, v, vec_ok, ld)) continue;
       const double us = predict_instance(v, c.hw, d);
       if (us <= 0) continue;
       const int cand[8] = {d.bm, d.bn, d.bk, d.wm, d.wn, d.kg, d.vm, d.vn};

@@ -2,10 +2,10 @@
 // kernel instance a schedule names, and the launch.  No device memory is allocated here.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <tuple>
 #include <utility>
 
 #include "../../include/gensor.h"
@@ -212,6 +212,17 @@ const InstanceDesc* find_instance(const gensor_schedule* s, const GemmView& v) {
   return nullptr;
 }
 
+bool offsets_fit(const InstanceDesc& d, const GemmView& v, const LeadingDims& ld) {
+  const int64_t lim = 0x7fffffffll;
+  if (v.asrc == A_KC && (int64_t)(d.bm + 1) * ld.a * v.esize >= lim) return false;
+  if (v.asrc == A_MC && ((int64_t)(d.bk + 1) * ld.a + d.bm) * v.esize >= lim) return false;
+  // (the convolution epilogues address the output with 64-bit indices and never use ldc)
+  if (v.bsrc != B_CONV && (int64_t)(d.bm + 1) * ld.c * v.osize >= lim) return false;
+  if (v.bsrc == B_KC && (int64_t)(d.bn + 1) * ld.b * v.esize >= lim) return false;
+  if ((v.bsrc == B_NC || v.bsrc == B_NCS2) && ((int64_t)(d.bk + 1) * ld.b + d.bn) * v.esize >= lim) return false;
+  return true;
+}
+
 // Can the 16-byte vector path be used?  (k-contiguous operands need K and their leading
 // dimension to be whole chunks; the n-contiguous operand needs N and ldb to be.)
 bool vector_ok(const GemmView& v, const void* A, int64_t lda, int64_t strideA, const void* B, int64_t ldb, int64_t strideB) {
@@ -301,41 +312,29 @@ extern "C" size_t gensor_workspace_bytes(const gensor_schedule* s, const gensor_
 // ------------------------------------------------------------------------------------
 namespace {
 std::mutex g_memo_mutex;
-std::map<std::tuple<int, int, int, int, int, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t>, gensor_schedule> g_memo;
+std::map<std::array<int64_t, 17>, gensor_schedule> g_memo;
 const size_t kMemoLimit = 4096;      // shapes remembered; a full memo is emptied (a shape seen again is constructed again)
 
-gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_mode, bool no_split, gensor_schedule* out) {
-  auto key = std::make_tuple((int)p->op, (int)p->in_dtype, (int)p->out_dtype, (int)p->transB + 2 * (int)p->transA,
-                             (vec_ok ? 1 : 0) + (no_split ? 2 : 0) + 4 * view_mode,
-                             p->op == GENSOR_OP_CONV2D ? p->n : p->batch, p->op == GENSOR_OP_CONV2D ? p->c : p->M,
-                             p->op == GENSOR_OP_CONV2D ? p->h : p->N, p->op == GENSOR_OP_CONV2D ? p->w : p->K,
-                             p->op == GENSOR_OP_CONV2D ? p->k : 0, p->op == GENSOR_OP_CONV2D ? p->r : 0,
-                             p->op == GENSOR_OP_CONV2D ? p->s : 0,
-                             p->op == GENSOR_OP_CONV2D ? p->stride : 0, p->op == GENSOR_OP_CONV2D ? p->pad : 0);
+gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_mode, bool no_split, gensor_schedule* out,
+                                const LeadingDims* ld = nullptr) {
+  const bool conv = p->op == GENSOR_OP_CONV2D;
+  const std::array<int64_t, 17> key = {p->op, p->in_dtype, p->out_dtype, p->transB + 2 * p->transA,
+                                       (vec_ok ? 1 : 0) + (no_split ? 2 : 0) + 4 * view_mode,
+                                       conv ? p->n : p->batch, conv ? p->c : p->M, conv ? p->h : p->N, conv ? p->w : p->K,
+                                       conv ? p->k : 0, conv ? p->r : 0, conv ? p->s : 0, conv ? p->stride : 0, conv ? p->pad : 0,
+                                       ld ? ld->a : 0, ld ? ld->b : 0, ld ? ld->c : 0};
   std::lock_guard<std::mutex> lock(g_memo_mutex);
   auto it = g_memo.find(key);
   if (it != g_memo.end()) { *out = it->second; return GENSOR_OK; }
   gensor_construct_opts opts;
   std::memset(&opts, 0, sizeof(opts));
   opts.no_split_k = no_split ? 1 : 0;
-  gensor_status st = construct_internal(p, nullptr, &opts, 0, vec_ok, view_mode, out);
+  gensor_status st = construct_internal(p, nullptr, &opts, 0, vec_ok, view_mode, out, ld);
   if (st == GENSOR_OK) {
     if (g_memo.size() >= kMemoLimit) g_memo.clear();
     g_memo[key] = *out;
   }
   return st;
-}
-
-// The kernels address a workgroup tile with 32-bit offsets.
-bool offsets_fit(const InstanceDesc& d, const GemmView& v, int64_t lda, int64_t ldb, int64_t ldc) {
-  const int64_t lim = 0x7fffffffll;
-  if (v.asrc == A_KC && (int64_t)(d.bm + 1) * lda * v.esize >= lim) return false;
-  if (v.asrc == A_MC && ((int64_t)(d.bk + 1) * lda + d.bm) * v.esize >= lim) return false;
-  // (the convolution epilogues address the output with 64-bit indices and never use ldc)
-  if (v.bsrc != B_CONV && (int64_t)(d.bm + 1) * ldc * v.osize >= lim) return false;
-  if (v.bsrc == B_KC && (int64_t)(d.bn + 1) * ldb * v.esize >= lim) return false;
-  if ((v.bsrc == B_NC || v.bsrc == B_NCS2) && ((int64_t)(d.bk + 1) * ldb + d.bn) * v.esize >= lim) return false;
-  return true;
 }
 
 gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmView& v, float alpha,
@@ -344,6 +343,7 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   const bool vec_ok = vector_ok(v, A, lda, strideA, B, ldb, strideB);
   const bool ws_aligned = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
   gensor_schedule local;
+  const LeadingDims ld = {lda, ldb, ldc};
   const bool constructed = !s;
   const int mode = !v.pointwise ? VIEW_GENERAL : (v.cstride > 1 && v.bsrc == B_NC ? VIEW_PREPASS : VIEW_DEFAULT);
   if (!s) {
@@ -359,12 +359,12 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
     if (st != GENSOR_OK) return st;
     d = find_instance(s, v);
   }
-  if (d && !d->vec && (v.bsrc == B_KC || v.bsrc == B_NC) && !offsets_fit(*d, v, lda, ldb, ldc)) {
+  if (d && !d->vec && (v.bsrc == B_KC || v.bsrc == B_NC) && !offsets_fit(*d, v, ld)) {
     // Rows too far apart for this tile's offsets (a schedule does not know the leading dimensions): the smallest tile of the
     // instances at any alignment takes about twice as long ones.
     for (int i = 0; i < g_num_instances; ++i) {
       const InstanceDesc& e = g_instances[i];
-      if (e.vec || e.mb != 16 || !instance_serves(e, v) || !offsets_fit(e, v, lda, ldb, ldc)) continue;
+      if (e.vec || e.mb != 16 || !instance_serves(e, v) || !offsets_fit(e, v, ld)) continue;
       const int32_t panel = s->wg_remap, units = s->round_units;
       schedule_from_instance(e, &local);
       local.wg_remap = panel;
@@ -380,7 +380,21 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   if (s->split_k < 1 || !split_allowed(*d, v, s->split_k)) return GENSOR_ERR_NO_SCHEDULE;
   SplitPlan sp = split_plan(*d, v, s->split_k, s->round_units);
   if (sp.split > 1 && (!ws_aligned || workspace_bytes < sp.bytes)) return GENSOR_ERR_WORKSPACE;
-  if (!offsets_fit(*d, v, lda, ldb, ldc)) return GENSOR_ERR_UNSUPPORTED;
+  if (!offsets_fit(*d, v, ld)) {
+    // The same for aligned operands: what would be constructed of the tiles that reach, for the room there is.  (256-row tiles reach
+    // half as far as 128-row ones, and which of them a shape gets is the cost model's choice: rows that ran must not depend on it.)
+    const int32_t panel = s->wg_remap;
+    if (!d->vec || memoised_schedule(p, vec_ok, mode, !ws_aligned, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
+    d = find_instance(&local, v);
+    if (d && local.split_k > 1 && workspace_bytes < split_plan(*d, v, local.split_k, local.round_units).bytes) {
+      if (memoised_schedule(p, vec_ok, mode, true, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
+      d = find_instance(&local, v);
+    }
+    if (!d) return GENSOR_ERR_UNSUPPORTED;
+    local.wg_remap = panel;
+    s = &local;
+    sp = split_plan(*d, v, s->split_k, s->round_units);
+  }
 
   KernelArgs a;
   std::memset(&a, 0, sizeof(a));

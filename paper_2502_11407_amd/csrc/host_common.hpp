@@ -84,9 +84,13 @@ inline bool narrow_tiles(const GemmView& v, int64_t compute_units) {
   return narrow <= wide;
 }
 
-// gensor_construct with two more inputs: whether the operands allow 16-byte vector accesses
-// and the view (ViewMode) a pointwise convolution is taken in.
+// The kernels address a workgroup tile with 32-bit offsets: can instance d, with leading dimensions `ld`?
+struct LeadingDims { int64_t a, b, c; };
+bool offsets_fit(const InstanceDesc& d, const GemmView& v, const LeadingDims& ld);
+
+// gensor_construct with more inputs: whether the operands allow 16-byte vector accesses, the view (ViewMode) a
+// pointwise convolution is taken in, and, where only tiles whose offsets reach are wanted, the leading dimensions.
 gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, const gensor_construct_opts* opts,
-                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out);
+                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld = nullptr);
 
 }  // namespace gensor

@@ -67,3 +67,28 @@ def test_alpha_beta_and_batches(gs):
     gs.bmm(p, A, B, C, 0.5, 2.0, s)
     for b in range(batch):
         assert torch.equal(C[b], 0.5 * (A[b].float() @ B[b].float()) + 2.0 * C0[b]), b
+
+
+@pytest.mark.parametrize("operand", ["A", "B", "C"])
+def test_rows_too_long_for_256_row_tiles(gs, operand):
+    """Leading dimensions that the offsets of a 256-row tile do not reach and those of a 128-row one do, in the schedule of an
+    instance of 256 rows and with none named: a tile that reaches takes the call."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(7)
+    M, N, K, far = 300, 280, 72, {"A": 6000000, "B": 6000000, "C": 3000000}[operand]
+
+    def rows(r, c, ld, dtype):
+        return torch.as_strided(gs.empty_device(((r - 1) * ld + c,), dtype), (r, c), (ld, 1))
+
+    ints = lambda r, c: torch.randint(-1, 2, (r, c), generator=g, device="cuda", dtype=torch.int8)
+    A = rows(M, K, far if operand == "A" else K, "f16").copy_(ints(M, K))
+    B = rows(N, K, far if operand == "B" else K, "f16").copy_(ints(N, K))
+    C = rows(M, N + 8, far if operand == "C" else N + 8, "f32")
+    p = gs.gemm_problem("f16", M, N, K, 0, 1)
+    wide = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+            if s is not None and s.direct_lds and s.stages == 2 and s.tile[2][1] == 32 and (s.tile[0][0], s.tile[1][0]) == (256, 256)]
+    assert len(wide) == 1
+    for s in (wide[0], None):
+        C.fill_(7.0)
+        gs.gemm(p, A, B, C, 1.0, 0.0, s)
+        assert torch.equal(C[:, :N], A.float() @ B.float().T.contiguous()) and bool((C[:, N:] == 7.0).all())

@@ -1,0 +1,53 @@
+"""What the entry points dispatch a call to, and what they refuse, on the library's host code alone (tests/stub_library.py)."""
+import pytest
+
+from stub_library import ACCEPTED, Stub
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    return Stub(tmp_path_factory.mktemp("stub"))
+
+
+# (dtype, out, M, N, K, transA, transB, lda, ldb, ldc): rows too far apart for the 32-bit offsets of the 256-row tiles that are
+# constructed for these shapes, and within those of 128 rows
+LONG_ROWS = [
+    ("f16", "f32", 3287, 2816, 704, 0, 1, 6000000, None, None),
+    ("f16", "f32", 3287, 2816, 704, 0, 1, None, None, 3000000),
+    ("f16", "f32", 3156, 3072, 768, 0, 1, None, 6000000, None),
+    ("bf16", "bf16", 8192, 3072, 768, 0, 1, None, 6000000, None),
+    ("bf16", "bf16", 8192, 3072, 768, 0, 0, None, None, 6000000),
+    ("f16", "f32", 4096, 4096, 4096, 0, 0, 6000000, None, None),
+    ("f16", "f32", 768, 3072, 8192, 1, 0, None, None, 3000000),
+]
+
+
+@pytest.mark.parametrize("case", LONG_ROWS)
+def test_rows_too_long_for_the_constructed_tile_find_another(stub, case):
+    dtype, out, M, N, K, ta, tb, lda, ldb, ldc = case
+    p = stub.gs.gemm_problem(dtype, M, N, K, ta, tb, 1, out)
+    s = stub.construct(p)
+    es, os_ = 2, 4 if out == "f32" else 2
+    need = stub.workspace_bytes(p, s)
+    for schedule, room in ((s, need), (None, 0), (None, 1 << 30)):
+        st, launch = stub.call(p, schedule, lda, ldb, ldc, room)
+        assert st == ACCEPTED and launch, (case, schedule is not None, st)
+        t = stub.gs.instance_schedule(launch["id"], p)
+        assert t.vec_bytes == 16                                       # aligned operands keep aligned accesses
+        bm, bn, bk = t.tile[0][0], t.tile[1][0], t.tile[2][0]
+        a = (bk + 1) * (lda or M) + bm if ta else (bm + 1) * (lda or K)
+        b = (bn + 1) * (ldb or K) if tb else (bk + 1) * (ldb or N) + bn
+        assert max(a * es, b * es, (bm + 1) * (ldc or N) * os_) < 2 ** 31 - 1, (bm, bn, bk)
+
+
+def test_rows_too_long_for_every_tile_stay_refused(stub):
+    p = stub.gs.gemm_problem("f16", 3287, 2816, 704, 0, 1)
+    for lda in (200000000, 2 ** 31, 2 ** 40):                          # (17 rows of 200 million 16-bit elements: beyond 2^31 bytes)
+        for s in (stub.construct(p), None):
+            st, launch = stub.call(p, s, lda=lda, room=1 << 30)
+            assert st == 2 and launch is None, (lda, st)
+    # a split schedule without its workspace is refused for that first, whatever the rows
+    q = stub.gs.gemm_problem("f16", 512, 512, 32768, 0, 1)
+    s = stub.construct(q)
+    assert s.split_k > 1
+    assert stub.call(q, s, lda=60000000)[0] == 4
