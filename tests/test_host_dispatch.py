@@ -51,3 +51,27 @@ def test_rows_too_long_for_every_tile_stay_refused(stub):
     s = stub.construct(q)
     assert s.split_k > 1
     assert stub.call(q, s, lda=60000000)[0] == 4
+
+
+# weight gradients (transA) whose constructed split fitted the static scratch while 256-row tiles were no choice, at least twice
+# the bytes of it when they are
+@pytest.mark.parametrize("M,N,K", [(768, 3072, 8192), (768, 3072, 5616), (3328, 832, 4568), (3840, 960, 3784), (3584, 896, 4504), (2520, 544, 10488)])
+def test_constructed_splits_stay_within_the_static_scratch(stub, M, N, K):
+    from paper_2502_11407_amd.binding import STATIC_SCRATCH_BYTES
+    p = stub.gs.gemm_problem("f16", M, N, K, 1, 0)
+    s = stub.construct(p)
+    assert s.split_k > 1 and 0 < stub.workspace_bytes(p, s) <= STATIC_SCRATCH_BYTES
+    assert stub.call(p, s, static=True)[0] == ACCEPTED
+    assert stub.call(p, s, room=STATIC_SCRATCH_BYTES)[0] == ACCEPTED
+    # and a call that names none splits in a workspace of that size
+    st, launch = stub.call(p, None, room=STATIC_SCRATCH_BYTES)
+    assert st == ACCEPTED and launch["split"] > 1 and (launch["id"], launch["split"]) == (s.kernel_id, s.split_k)
+
+
+def test_splits_beyond_the_static_scratch_where_no_other_fits_either(stub):
+    """960 x 3840 x 7992 transA: every tile's best split needs more than the static scratch, so the alternating ones may, too."""
+    from paper_2502_11407_amd.binding import STATIC_SCRATCH_BYTES
+    p = stub.gs.gemm_problem("f16", 960, 3840, 7992, 1, 0)
+    s = stub.construct(p)
+    assert s.split_k > 1 and stub.workspace_bytes(p, s) > STATIC_SCRATCH_BYTES
+    assert stub.call(p, s, static=True) == (4, None)
