@@ -182,8 +182,8 @@ gensor_status gensor_instance_schedule(int32_t id, const gensor_problem* p, gens
  * aligned, at least gensor_workspace_bytes(s, p) bytes (WORKSPACE otherwise), for the partial tiles.  It is scratch: nothing is kept in it between calls, and
  * two calls that overlap in time must not share it.  If the tile count is a whole number of
  * rounds nothing is split and no workspace is needed (gensor_workspace_bytes returns 0).
- * With s == NULL split-k schedules are ranked only when a workspace is passed, and one too
- * small for the ranking's choice selects the best unsplit schedule instead.
+ * With s == NULL the best schedule that needs no more than the workspace passed is taken (no
+ * workspace: the best unsplit one).
  * Schedules with split_k == 1 use no workspace (pass NULL, 0).
  */
 gensor_status gensor_gemm(const gensor_schedule* s, const gensor_problem* p, float alpha,
@@ -198,8 +198,8 @@ gensor_status gensor_gemm(const gensor_schedule* s, const gensor_problem* p, flo
  * of GENSOR_STATIC_SCRATCH_BYTES that is part of the library's code object (every GPU the library
  * runs on holds its own copy until the process ends).  The call allocates and frees nothing.
  * A schedule whose gensor_workspace_bytes(s, p) exceeds GENSOR_STATIC_SCRATCH_BYTES is refused with
- * GENSOR_ERR_WORKSPACE and nothing is launched; with s == NULL split-k schedules are ranked and one
- * that does not fit falls back to the best unsplit schedule, as in gensor_gemm.  Every call on one
+ * GENSOR_ERR_WORKSPACE and nothing is launched; with s == NULL the best schedule that fits is taken,
+ * as in gensor_gemm.  Every call on one
  * GPU shares that GPU's array, which keeps the last call's contents: calls that overlap in time on one GPU -- different streams, or graphs replayed
  * concurrently -- race on it and must be serialised by the caller.
  */

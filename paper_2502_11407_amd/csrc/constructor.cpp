@@ -521,10 +521,33 @@ bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok, const Leading
   return true;
 }
 
+struct Choice {
+  const InstanceDesc* d;
+  int split;
+  double us;
+  size_t bytes;            // workspace
+};
+
+// Adds a choice to a list ordered by price (equal prices: the lower instance id, then fewer parts, whatever order the states were
+// kept in) and strictly falling workspace.
+void keep_choice(std::vector<Choice>* list, const Choice& x) {
+  auto before = [](const Choice& a, const Choice& b) {
+    return a.us != b.us ? a.us < b.us : a.d->id != b.d->id ? a.d->id < b.d->id : a.split < b.split;
+  };
+  size_t at = 0;
+  while (at < list->size() && before((*list)[at], x)) ++at;
+  if (at > 0 && (*list)[at - 1].bytes <= x.bytes) return;
+  size_t end = at;
+  while (end < list->size() && (*list)[end].bytes >= x.bytes) ++end;
+  list->erase(list->begin() + at, list->begin() + end);
+  list->insert(list->begin() + at, x);
+}
+
 }  // namespace
 
 gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, const gensor_construct_opts* opts,
-                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld) {
+                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld,
+                                 std::vector<RankedSchedule>* ranked) {
   if (!p || !out) return GENSOR_ERR_INVALID_ARG;
   const auto t0 = std::chrono::steady_clock::now();
   GemmView v;
@@ -541,12 +564,9 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
   }
   // rank the distinct kept states; best exact instance wins, else the instance nearest to the best state
   std::set<Etir> seen;
-  const InstanceDesc* best = nullptr;
-  double best_us = 0.0;
-  int best_split = 1;
-  const InstanceDesc* large = nullptr;       // the same of alternating tiles whose parts need more than the static scratch
-  double large_us = 0.0;
-  int large_split = 1;
+  // What is kept of the priced choices: those that no better ranked one undercuts in workspace.  (`large`: alternating tiles whose
+  // parts need more than the static scratch, see below.)
+  std::vector<Choice> best, large;
   int scored = 0;
   const Etir* best_state = nullptr;
   double best_state_us = 0.0;
@@ -566,13 +586,8 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
         if (split > 1 && c.opts.no_split_k) break;
         const double us = predict_instance(v, c.hw, d, split);
         if (us <= 0) continue;
-        const bool beyond = split > 1 && d.alternate() && split_plan(d, v, split, c.hw.compute_units).bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES;
-        // (equal prices: the lower instance id, whatever order the states were kept in)
-        auto take = [&](const InstanceDesc*& at, double& at_us, int& at_split) {
-          if (!at || us < at_us || (us == at_us && d.id < at->id)) { at = &d; at_us = us; at_split = split; }
-        };
-        if (beyond) take(large, large_us, large_split);
-        else take(best, best_us, best_split);
+        const Choice choice = {&d, split, us, split > 1 ? split_plan(d, v, split, c.hw.compute_units).bytes : 0};
+        keep_choice(&(d.alternate() && choice.bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES ? large : best), choice);
       }
     }
     const double us0 = predict(v, c.hw, e.tile[0][0], e.tile[1][0], e.tile[2][0], e.tile[0][1], e.tile[1][1], e.tile[2][1],
@@ -582,16 +597,14 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
   // The partial tiles of the alternating 256x256 instances take twice the room of the 256x128 ones' for 0-5 % of the time (768 x 3072 x
   // 8192 transA in six parts of 57 MB 51.6 us against 51.9 in three of 28; inputs that change 51.4 against 54.3).  A shape that
   // otherwise fits the static scratch keeps fitting it: callers with that much room could not run the schedule at all.
-  if (large && (!best || (large_us < best_us && split_plan(*best, v, best_split, c.hw.compute_units).bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))) {
-    best = large;
-    best_us = large_us;
-    best_split = large_split;
-  }
-  if (!best && best_state) {
+  if (!large.empty() && (best.empty() || best[0].bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))
+    for (const Choice& x : large) keep_choice(&best, x);
+  if (best.empty() && best_state) {
     const int target[8] = {best_state->tile[0][0], best_state->tile[1][0], best_state->tile[2][0], best_state->tile[0][1],
                            best_state->tile[1][1], best_state->tile[2][1], best_state->v[0], best_state->v[1]};
     bool have = false;
     double bd = 0.0;
+    Choice nearest = {nullptr, 1, 0.0, 0};
     for (int i = 0; i < g_num_instances; ++i) {
       const InstanceDesc& d = g_instances[i];
       if (!usable(d, v, vec_ok, ld)) continue;
@@ -603,19 +616,30 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
       // convolution loaders have k orders and LDS layouts of their own, so their coordinates say little about how near they
       // are (fewer than 17 filters: no state holds a loader's tile): the cheapest is taken
       if (v.bsrc == B_CONV) dist = us;
-      if (!have || dist < bd || (dist == bd && us < best_us)) { have = true; bd = dist; best = &d; best_us = us; }
+      if (!have || dist < bd || (dist == bd && us < nearest.us)) { have = true; bd = dist; nearest.d = &d; nearest.us = us; }
+    }
+    if (have) best.push_back(nearest);
+  }
+  if (best.empty()) return GENSOR_ERR_NO_SCHEDULE;
+  auto describe = [&](const Choice& x, gensor_schedule* s) {
+    schedule_from_instance(*x.d, s);
+    s->split_k = x.split;
+    s->round_units = c.hw.compute_units;
+    s->predicted_us = x.us;
+    s->iterations = max_steps;
+    s->chains = c.opts.chains;
+    s->states_scored = scored;
+    s->seed = seed;
+    s->construct_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  };
+  describe(best[0], out);
+  if (ranked) {
+    ranked->resize(best.size());
+    for (size_t i = 0; i < best.size(); ++i) {
+      describe(best[i], &(*ranked)[i].schedule);
+      (*ranked)[i].bytes = best[i].bytes;
     }
   }
-  if (!best) return GENSOR_ERR_NO_SCHEDULE;
-  schedule_from_instance(*best, out);
-  out->split_k = best_split;
-  out->round_units = c.hw.compute_units;
-  out->predicted_us = best_us;
-  out->iterations = max_steps;
-  out->chains = c.opts.chains;
-  out->states_scored = scored;
-  out->seed = seed;
-  out->construct_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return GENSOR_OK;
 }
 

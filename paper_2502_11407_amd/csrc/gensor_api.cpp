@@ -308,33 +308,33 @@ extern "C" size_t gensor_workspace_bytes(const gensor_schedule* s, const gensor_
 }
 
 // ------------------------------------------------------------------------------------
-// schedule == NULL: construct once per (problem, alignment class) and remember it.
+// schedule == NULL: construct once per (problem, alignment class) and remember what the ranking found for any workspace.
 // ------------------------------------------------------------------------------------
 namespace {
 std::mutex g_memo_mutex;
-std::map<std::array<int64_t, 17>, gensor_schedule> g_memo;
+std::map<std::array<int64_t, 17>, std::vector<RankedSchedule>> g_memo;
 const size_t kMemoLimit = 4096;      // shapes remembered; a full memo is emptied (a shape seen again is constructed again)
 
-gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_mode, bool no_split, gensor_schedule* out,
+// The best schedule that needs at most `room` bytes of workspace.
+gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_mode, size_t room, gensor_schedule* out,
                                 const LeadingDims* ld = nullptr) {
   const bool conv = p->op == GENSOR_OP_CONV2D;
-  const std::array<int64_t, 17> key = {p->op, p->in_dtype, p->out_dtype, p->transB + 2 * p->transA,
-                                       (vec_ok ? 1 : 0) + (no_split ? 2 : 0) + 4 * view_mode,
+  const std::array<int64_t, 17> key = {p->op, p->in_dtype, p->out_dtype, p->transB + 2 * p->transA, (vec_ok ? 1 : 0) + 2 * view_mode,
                                        conv ? p->n : p->batch, conv ? p->c : p->M, conv ? p->h : p->N, conv ? p->w : p->K,
                                        conv ? p->k : 0, conv ? p->r : 0, conv ? p->s : 0, conv ? p->stride : 0, conv ? p->pad : 0,
                                        ld ? ld->a : 0, ld ? ld->b : 0, ld ? ld->c : 0};
   std::lock_guard<std::mutex> lock(g_memo_mutex);
   auto it = g_memo.find(key);
-  if (it != g_memo.end()) { *out = it->second; return GENSOR_OK; }
-  gensor_construct_opts opts;
-  std::memset(&opts, 0, sizeof(opts));
-  opts.no_split_k = no_split ? 1 : 0;
-  gensor_status st = construct_internal(p, nullptr, &opts, 0, vec_ok, view_mode, out, ld);
-  if (st == GENSOR_OK) {
+  if (it == g_memo.end()) {
+    std::vector<RankedSchedule> ranked;
+    gensor_status st = construct_internal(p, nullptr, nullptr, 0, vec_ok, view_mode, out, ld, &ranked);
+    if (st != GENSOR_OK) return st;
     if (g_memo.size() >= kMemoLimit) g_memo.clear();
-    g_memo[key] = *out;
+    it = g_memo.emplace(key, std::move(ranked)).first;
   }
-  return st;
+  for (const RankedSchedule& r : it->second)
+    if (r.bytes <= room) { *out = r.schedule; return GENSOR_OK; }
+  return GENSOR_ERR_NO_SCHEDULE;
 }
 
 gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmView& v, float alpha,
@@ -344,21 +344,14 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   const bool ws_aligned = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
   gensor_schedule local;
   const LeadingDims ld = {lda, ldb, ldc};
-  const bool constructed = !s;
+  const size_t room = ws_aligned ? workspace_bytes : 0;
   const int mode = !v.pointwise ? VIEW_GENERAL : (v.cstride > 1 && v.bsrc == B_NC ? VIEW_PREPASS : VIEW_DEFAULT);
   if (!s) {
-    // split-k schedules are ranked only for a caller that brought a workspace
-    gensor_status st = memoised_schedule(p, vec_ok, mode, !ws_aligned, &local);
+    gensor_status st = memoised_schedule(p, vec_ok, mode, room, &local);
     if (st != GENSOR_OK) return st;
     s = &local;
   }
   const InstanceDesc* d = find_instance(s, v);
-  if (constructed && d && s->split_k > 1 && workspace_bytes < split_plan(*d, v, s->split_k, s->round_units).bytes) {
-    // the workspace is too small for the split the ranking chose: the best unsplit schedule instead
-    gensor_status st = memoised_schedule(p, vec_ok, mode, true, &local);
-    if (st != GENSOR_OK) return st;
-    d = find_instance(s, v);
-  }
   if (d && !d->vec && (v.bsrc == B_KC || v.bsrc == B_NC) && !offsets_fit(*d, v, ld)) {
     // Rows too far apart for this tile's offsets (a schedule does not know the leading dimensions): the smallest tile of the
     // instances at any alignment takes about twice as long ones.
@@ -379,17 +372,13 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   if (d->direct && !d->alternate() && v.bsrc != B_CONV && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
   if (s->split_k < 1 || !split_allowed(*d, v, s->split_k)) return GENSOR_ERR_NO_SCHEDULE;
   SplitPlan sp = split_plan(*d, v, s->split_k, s->round_units);
-  if (sp.split > 1 && (!ws_aligned || workspace_bytes < sp.bytes)) return GENSOR_ERR_WORKSPACE;
+  if (sp.split > 1 && room < sp.bytes) return GENSOR_ERR_WORKSPACE;
   if (!offsets_fit(*d, v, ld)) {
     // The same for aligned operands: what would be constructed of the tiles that reach, for the room there is.  (256-row tiles reach
     // half as far as 128-row ones, and which of them a shape gets is the cost model's choice: rows that ran must not depend on it.)
     const int32_t panel = s->wg_remap;
-    if (!d->vec || memoised_schedule(p, vec_ok, mode, !ws_aligned, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
+    if (!d->vec || memoised_schedule(p, vec_ok, mode, room, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
     d = find_instance(&local, v);
-    if (d && local.split_k > 1 && workspace_bytes < split_plan(*d, v, local.split_k, local.round_units).bytes) {
-      if (memoised_schedule(p, vec_ok, mode, true, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
-      d = find_instance(&local, v);
-    }
     if (!d) return GENSOR_ERR_UNSUPPORTED;
     local.wg_remap = panel;
     s = &local;

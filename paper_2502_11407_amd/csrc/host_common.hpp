@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/gensor.h"
 #include "registry.hpp"
 
@@ -90,7 +92,10 @@ bool offsets_fit(const InstanceDesc& d, const GemmView& v, const LeadingDims& ld
 
 // gensor_construct with more inputs: whether the operands allow 16-byte vector accesses, the view (ViewMode) a
 // pointwise convolution is taken in, and, where only tiles whose offsets reach are wanted, the leading dimensions.
+// `ranked`: beside the best schedule, the best ones for less workspace than it needs, in order, down to one that needs none.
+struct RankedSchedule { gensor_schedule schedule; size_t bytes; };
 gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, const gensor_construct_opts* opts,
-                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld = nullptr);
+                                 uint64_t seed, bool vec_ok, int view_mode, gensor_schedule* out, const LeadingDims* ld = nullptr,
+                                 std::vector<RankedSchedule>* ranked = nullptr);
 
 }  // namespace gensor

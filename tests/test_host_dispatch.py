@@ -75,3 +75,27 @@ def test_splits_beyond_the_static_scratch_where_no_other_fits_either(stub):
     s = stub.construct(p)
     assert s.split_k > 1 and stub.workspace_bytes(p, s) > STATIC_SCRATCH_BYTES
     assert stub.call(p, s, static=True) == (4, None)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,ta,tb", [("f16", 768, 3072, 8192, 1, 0), ("bf16", 1024, 1024, 8192, 0, 1), ("f16", 512, 512, 32768, 0, 1),
+                                               ("f16", 1096, 1568, 11552, 0, 0), ("f16", 2304, 576, 7944, 1, 0)])
+def test_unnamed_schedules_split_as_far_as_the_workspace_goes(stub, dtype, M, N, K, ta, tb):
+    """A workspace too small for the constructed split gets the cheapest one that fits it, not an unsplit schedule."""
+    p = stub.gs.gemm_problem(dtype, M, N, K, ta, tb)
+    s = stub.construct(p)
+    full, seen = stub.workspace_bytes(p, s), []
+    assert s.split_k > 1
+    for room in (1 << 30, full, full - 1, full // 2, full // 4, full // 8, 1 << 19, 256, 0):
+        st, launch = stub.call(p, None, room=room)
+        assert st == ACCEPTED
+        t = stub.gs.instance_schedule(launch["id"], p)
+        t.split_k = launch["split"]
+        assert stub.workspace_bytes(p, t) <= room
+        if room >= full:
+            assert (launch["id"], launch["split"]) == (s.kernel_id, s.split_k)
+        seen.append((stub.gs.predict_us(t, p), launch["split"]))
+    assert [us for us, _ in seen] == sorted(us for us, _ in seen)          # less room is never priced faster
+    assert seen[-1][1] == 1 and any(split > 1 for _, split in seen[2:6])
+    # the unsplit one is what a ranking without splits returns
+    o = stub.gs.ConstructOpts(0, 0, 0, 0, 0, 0, 1, 0)
+    assert seen[-1][0] == stub.gs.construct(p, opts=o).predicted_us
