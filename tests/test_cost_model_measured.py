@@ -135,3 +135,22 @@ def test_virtual_threads_measured_and_priced_alike(data):
                 assert row["us"] > 1.03 * full["us"], (name, idx, j)
                 assert gs.predict_us(gs.instance_schedule(int(idx), p), p) > gs.predict_us(gs.instance_schedule(int(j), p), p), (name, idx, j)
     assert seen >= 6
+
+
+@pytest.mark.parametrize("dtype,M,N,K,us_128,us_64", [
+    ("f16", 768, 3072, 1080, 13.9, 14.7), ("f16", 3328, 832, 2272, 25.6, 27.2), ("f16", 3328, 832, 1936, 22.5, 24.1),
+    ("f16", 3072, 768, 1592, 18.6, 19.6), ("f16", 768, 3072, 752, 10.6, 11.1), ("bf16", 768, 3072, 1064, 13.6, 14.1),
+])
+def test_whole_tiles_with_an_m_contiguous_a_are_ranked_as_measured(dtype, M, N, K, us_128, us_64):
+    """Register-staged 128x128 and 64x64 tiles, both with two k tiles of loads in flight (measured on inputs that change from call to
+    call): the model prices them in the measured order and the larger one is what is constructed."""
+    from paper_2502_11407_amd import binding as gs
+    p = gs.gemm_problem(dtype, M, N, K, 1, 0)
+    price = {}
+    for i in range(gs.num_instances()):
+        s = gs.instance_schedule(i, p)
+        if s is not None and not s.direct_lds and s.stages == 2 and s.vec_bytes == 16 and s.tile[0][0] == s.tile[1][0] and s.vthread[0] == s.vthread[1] == 4:
+            price[s.tile[0][0]] = min(price.get(s.tile[0][0], 1e9), gs.predict_us(s, p))
+    assert us_128 < us_64 and price[128] < price[64]
+    s = gs.construct(p)
+    assert (s.tile[0][0], s.tile[1][0], s.split_k) == (128, 128, 1)
