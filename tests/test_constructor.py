@@ -297,6 +297,8 @@ def _views():
         # A stored [k][m]
         (gs.gemm_problem("f16", 2048, 1024, 512, 1, 0), oc.View(2048, 1024, 512, 1, 2, 4, 1, asrc=1)),
         (gs.gemm_problem("f32", 200, 136, 72, 1, 1), oc.View(200, 136, 72, 1, 4, 4, 0, asrc=1)),
+        # a k tail: of the directly staged instances only those whose wave groups alternate take it
+        (gs.gemm_problem("f16", 4096, 4096, 1000, 0, 1), oc.View(4096, 4096, 1000, 1, 2, 4, 0)),
     ]
 
 
@@ -345,12 +347,13 @@ def _coords(s):
 
 def _usable(p, view, s):
     """What gensor_construct assumes of the operands: aligned and dense, so vector accesses work exactly when the
-    contiguous extents are whole vectors; direct staging takes whole k tiles."""
+    contiguous extents are whole vectors; direct staging takes whole k tiles, but where the wave groups alternate."""
     epc = 16 // view.e
     vec_ok = view.bsrc == 2 or ((view.M if view.asrc else view.K) % epc == 0 and (view.K if view.bsrc == 0 else view.N) % epc == 0)
     if s.vec_bytes == 16 and not vec_ok:
         return False
-    if s.direct_lds and view.bsrc != 2 and view.K % s.tile[2][0] != 0:
+    alternating = s.stages == 2 and _coords(s)[:3] + (s.tile[2][1],) == (256, 256, 64, 32)
+    if s.direct_lds and view.bsrc != 2 and view.K % s.tile[2][0] != 0 and not alternating:
         return False
     return True
 

@@ -49,8 +49,9 @@ def test_every_element(gs, dtype, out, ta, tb):
         assert torch.equal(C[:M], want) and bool(torch.isnan(C[M]).all()), (s.kernel_id, M, N, K)
 
 
-def test_wide_tiles_where_narrow_ones_need_another_round(gs):
-    """16 x 16 wide tiles are one round, 16 x 22 narrow ones two: the launch keeps the wide ones, and both agree with the product."""
+def test_products_on_either_side_of_the_rule(gs):
+    """16 x 16 wide tiles are one round and 16 x 22 narrow ones two; 16 x 12 and 16 x 16 are one each.  (Which width a launch takes is
+    checked in test_host_dispatch.py, on the host code.)"""
     import torch
     g = torch.Generator(device="cuda").manual_seed(16)
     for N in (4096, 3072):

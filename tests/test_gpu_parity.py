@@ -22,6 +22,11 @@ def gs():
     return binding
 
 
+def _alternating(s):
+    """256x256 tiles whose wave groups alternate: directly staged, and still at any K."""
+    return s.direct_lds and s.stages == 2 and (s.tile[0][0], s.tile[1][0], s.tile[2][0], s.tile[2][1]) == (256, 256, 64, 32)
+
+
 def _round_up(x, m):
     return (x + m - 1) // m * m
 
@@ -248,7 +253,7 @@ def test_pointwise_conv_is_a_batched_gemm(gs, dtype, geom):
         sch = gs.instance_schedule(idx, p)
         if sch is None or (sch.vec_bytes == 16 and pq % (16 // esize)):
             continue
-        if sch.direct_lds and c % sch.tile[2][0]:
+        if sch.direct_lds and c % sch.tile[2][0] and not _alternating(sch):
             continue                                            # direct staging takes whole k tiles only
         assert gs.workspace_bytes(p, sch) == need
         print(f"pointwise conv instance {idx} tile {sch.tile[0][0]}x{sch.tile[1][0]}x{sch.tile[2][0]} geom {geom} {dtype}", flush=True)
@@ -658,7 +663,7 @@ def _split_schedules(gs, p, split, want_tiles):
         s = gs.instance_schedule(idx, p)
         if s is None or (s.tile[0][0], s.tile[1][0]) not in want_tiles:
             continue
-        if s.direct_lds and p.K % s.tile[2][0]:
+        if s.direct_lds and p.K % s.tile[2][0] and not _alternating(s):
             continue                                   # direct staging takes whole k tiles only
         s.split_k = split
         if gs.workspace_bytes(p, s) > 0:

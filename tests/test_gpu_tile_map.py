@@ -33,25 +33,37 @@ def test_gemm_tile_map_every_element(gs, name):
     wl, s0 = _pick(gs, name)
     bm, bn, bk = s0.tile[0][0], s0.tile[1][0], s0.tile[2][0]
     K = 2 * bk if bm * bn < 256 * 256 else bk          # (the map does not depend on k; the oracle's cost does)
-    # (tile rows, tile columns, batch, ragged): 270 tiles (not a multiple of 8), 18 = 4 panels of 4 rows + 2; 256 tiles
-    # (a multiple of 8); three batches of 90; two batches of 64
-    for tm, tn, batch, ragged in ((18, 15, 1, True), (16, 16, 1, False), (10, 9, 3, True), (8, 8, 2, False)):
-        M = tm * bm - (17 if ragged else 0)
-        N = tn * bn - (8 if ragged else 0)
-        p = gs.gemm_problem(wl.dtype, M, N, K, 0, wl.transB, batch)
-        s = gs.instance_schedule(s0.kernel_id, p)
-        assert s is not None and s.wg_remap == 4 and tm > s.wg_remap
-        print(f"{name}: instance {s.kernel_id} tile {bm}x{bn}x{bk}: {tm}x{tn} tiles x {batch} batch(es), M={M} N={N} K={K}", flush=True)
-        shp = lambda r, c: (batch, r, c) if batch > 1 else (r, c)
-        A = inputs.small_ints(500 + tm, shp(M, K), wl.dtype, -3, 3)
-        B = inputs.small_ints(600 + tn, shp(N, K) if wl.transB else shp(K, N), wl.dtype, -3, 3)
-        dC = torch.full(shp(M, N), float("nan"), dtype=torch.float32, device="cuda")
-        (gs.bmm if batch > 1 else gs.gemm)(p, gs.to_device(A, wl.dtype), gs.to_device(B, wl.dtype), dC, 1.0, 0.0, s)
-        torch.cuda.synchronize()
-        got = gs.to_host_f64(dC)
-        want = np.stack([ops.gemm(A[b], B[b], wl.dtype, transB=wl.transB) for b in range(batch)]) if batch > 1 \
-            else ops.gemm(A, B, wl.dtype, transB=wl.transB)
-        assert np.array_equal(got, want), f"{name} {tm}x{tn}x{batch}: {np.count_nonzero(got != want)} elements differ"
+    # the instances whose wave groups alternate cut C 256 or 192 columns wide, as rounds of `units` compute units take it: as many units
+    # as wide tiles leave the narrow ones a second round, and a million leave one of either
+    alternating = s0.direct_lds and s0.stages == 2 and (bm, bn, bk, s0.tile[2][1]) == (256, 256, 64, 32)
+    ran = 0
+    for width in (256, 192) if alternating else (bn,):
+        # (tile rows, tile columns, batch, ragged): 270 tiles (not a multiple of 8), 18 = 4 panels of 4 rows + 2; 256 tiles
+        # (a multiple of 8); three batches of 90; two batches of 64
+        for tm, tn, batch, ragged in ((18, 15, 1, True), (16, 16, 1, False), (10, 9, 3, True), (8, 8, 2, False)):
+            M = tm * bm - (17 if ragged else 0)
+            N = tn * width - (8 if ragged else 0)
+            p = gs.gemm_problem(wl.dtype, M, N, K, 0, wl.transB, batch)
+            s = gs.instance_schedule(s0.kernel_id, p)
+            assert s is not None and s.wg_remap == 4 and tm > s.wg_remap
+            tiles = tm * tn * batch
+            assert (tiles % 8 == 0) == (not ragged)
+            if alternating:
+                s.round_units = tiles if width == 256 else 1000000
+                assert tm * -(-N // 192) * batch > (tiles if width == 256 else 0)
+            print(f"{name}: instance {s.kernel_id} tile {bm}x{width}x{bk}: {tm}x{tn} tiles x {batch} batch(es), M={M} N={N} K={K}", flush=True)
+            shp = lambda r, c: (batch, r, c) if batch > 1 else (r, c)
+            A = inputs.small_ints(500 + tm, shp(M, K), wl.dtype, -3, 3)
+            B = inputs.small_ints(600 + tn, shp(N, K) if wl.transB else shp(K, N), wl.dtype, -3, 3)
+            dC = torch.full(shp(M, N), float("nan"), dtype=torch.float32, device="cuda")
+            (gs.bmm if batch > 1 else gs.gemm)(p, gs.to_device(A, wl.dtype), gs.to_device(B, wl.dtype), dC, 1.0, 0.0, s)
+            torch.cuda.synchronize()
+            got = gs.to_host_f64(dC)
+            want = np.stack([ops.gemm(A[b], B[b], wl.dtype, transB=wl.transB) for b in range(batch)]) if batch > 1 \
+                else ops.gemm(A, B, wl.dtype, transB=wl.transB)
+            assert np.array_equal(got, want), f"{name} {tm}x{tn}x{batch}: {np.count_nonzero(got != want)} elements differ"
+            ran += 1
+    assert ran == (8 if alternating else 4)
 
 
 def _conv_tile_px(bn, N, Q, tiles_m, cus=256):

@@ -99,3 +99,39 @@ def test_unnamed_schedules_split_as_far_as_the_workspace_goes(stub, dtype, M, N,
     # the unsplit one is what a ranking without splits returns
     o = stub.gs.ConstructOpts(0, 0, 0, 0, 0, 0, 1, 0)
     assert seen[-1][0] == stub.gs.construct(p, opts=o).predicted_us
+
+
+def _alternating(stub, p):
+    s = [s for s in (stub.gs.instance_schedule(i, p) for i in range(stub.gs.num_instances()))
+         if s is not None and s.direct_lds and s.stages == 2 and (s.tile[0][0], s.tile[1][0], s.tile[2][0], s.tile[2][1]) == (256, 256, 64, 32)]
+    assert len(s) == 1
+    return s[0]
+
+
+# (M, N, batch, units of a round (0: the 256 of the chip), columns): both sides of the line, rounds wide / narrow counted by hand
+@pytest.mark.parametrize("M,N,batch,units,columns", [
+    (8192, 3072, 1, 0, 192),       # 32 x 12 = 384 / 32 x 16 = 512 tiles: 2 / 2
+    (8192, 4096, 1, 0, 256),       # 512 / 704: 2 / 3
+    (4096, 4096, 1, 0, 256),       # 256 / 352: 1 / 2
+    (4096, 3072, 1, 0, 192),       # 192 / 256: 1 / 1, full
+    (4097, 3072, 1, 0, 256),       # 204 / 272: 1 / 2
+    (264, 8, 1, 0, 192), (264, 192, 1, 1, 192), (264, 192, 1, 2, 192),         # one column of either
+    (256 * 128, 193, 1, 0, 192),   # 128 / 256: 1 / 1
+    (256 * 128 + 1, 193, 1, 0, 256),
+    (300, 712, 3, 18, 256),        # 18 / 24
+    (300, 712, 3, 23, 256), (300, 712, 3, 24, 192), (300, 712, 3, 12, 192),        # 1 / 2, 1 / 1, 2 / 2
+])
+def test_width_of_alternating_tiles(stub, M, N, batch, units, columns):
+    p = stub.gs.gemm_problem("f16", M, N, 136, 0, 1, batch)
+    s = _alternating(stub, p)
+    s.round_units = units
+    st, launch = stub.call(p, s)
+    rows, cols = -(-M // 256), -(-N // columns)
+    assert st == ACCEPTED and launch["narrow"] == (columns == 192)
+    assert (launch["tiles_m"], launch["tiles_n"], launch["whole"], launch["split"]) == (rows, cols, rows * cols * batch, 1)
+    # parts of split tiles are always 256 columns wide
+    s.split_k, s.round_units = 2, 4096
+    need = stub.workspace_bytes(p, s)
+    assert need == rows * -(-N // 256) * batch * 2 * 256 * 256 * 4
+    st, launch = stub.call(p, s, room=need)
+    assert st == ACCEPTED and launch["split_launch"] and not launch["narrow"] and launch["tiles_n"] == -(-N // 256)

@@ -3,6 +3,7 @@ import os
 import re
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 sys.path.insert(0, os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2502_11407_amd", "csrc"))
 import build as kernel_build  # noqa: E402
@@ -34,6 +35,24 @@ def test_large_tiles_of_16x16_blocks_keep_two_waves_per_simd(tmp_path):
     assert len(insts) >= 4
     for name, regs, spilled in _counts(tmp_path, insts, ("launch_instance<%s>", "launch_instance<%s, true>")):
         assert regs <= 256 and spilled == 0, (name, regs, spilled)
+
+
+def test_alternating_groups_keep_two_waves_per_simd(tmp_path):
+    """256x256 tiles of eight waves, 254-256 registers a lane: one more would leave one wave per SIMD, or spill.  The launch of a whole
+    tile instantiates the 192-column form, too."""
+    insts = [d for d in lattice.lattice() if lattice.alternate(d)]
+    assert len(insts) == 12
+
+    def one(d):
+        folder = tmp_path / str(d["id"])
+        folder.mkdir()
+        return _counts(folder, [d], ("launch_instance<%s>", "launch_instance<%s, true>"))
+
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        for kernels in ex.map(one, insts):
+            assert len(kernels) == 3                       # wide, narrow, split
+            for name, regs, spilled in kernels:
+                assert regs <= 256 and spilled == 0, (name, regs, spilled)
 
 
 def test_row_staged_convolution_does_not_spill(tmp_path):
