@@ -447,10 +447,12 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // (three k tiles in flight: whole tiles were priced 7-20 % above the measured time without; parts of split ones were not, against
   // the smaller tiles that share their units: 128 x 264 x 28672 in 16 parts 18.9 us against 16.4)
   if (stages >= 4 && split == 1 && v.K > 3 * bk) overlap += 0.12;
-  // (the alternating groups: one multiplies while the other waits, 94 % of the MFMA rate on all-zero operands, and no boundary
+  // (the alternating groups: one multiplies while the other waits, 94-97 % of the MFMA rate on all-zero operands, so no boundary
   // of a k tile is exposed; 4096^3 105 us against 124 of the next tile, 3648 x 2624 x 1856 38 against 41)
-  // (192 columns: a k tile takes 0.80 of the time of a wide one's, not 0.75)
-  if (alternate) overlap = bn == 192 ? 1.22 : 1.3;
+  // (192 columns: a k tile takes 0.81 of the time of a wide one's with k-contiguous operands and 0.85-0.9 with transposing reads,
+  // not 0.75; at 1.22 for both, tall products of few tiles took them at a loss: 8192 x 768 x 3072 with fp16 output, 128 tiles,
+  // 46.5 us against 41.7 of the 256x128 ring, 7169 x 960 x 3840 71.0 against 61.6)
+  if (alternate) overlap = bn != 192 ? 1.3 : (v.bsrc == B_NC || v.asrc == A_MC) ? 1.08 : 1.19;
   double t_main = t_mfma;
   if (t_lds > t_main) t_main = t_lds;
   if (t_feed > t_main) t_main = t_feed;

@@ -154,3 +154,16 @@ def test_whole_tiles_with_an_m_contiguous_a_are_ranked_as_measured(dtype, M, N, 
     assert us_128 < us_64 and price[128] < price[64]
     s = gs.construct(p)
     assert (s.tile[0][0], s.tile[1][0], s.split_k) == (128, 128, 1)
+
+
+@pytest.mark.parametrize("dtype,out,M,N,K,tb,us_ring,us_narrow", [
+    ("f16", "f16", 8192, 768, 3072, 0, 45.7, 51.7), ("bf16", "bf16", 8192, 1024, 4096, 0, 65.6, 73.8), ("bf16", "bf16", 7169, 960, 3840, 1, 59.2, 68.6),
+    ("f16", "f16", 7169, 960, 3840, 0, 63.7, 72.3),
+])
+def test_tall_products_of_few_tiles_stay_on_the_rings_of_three(dtype, out, M, N, K, tb, us_ring, us_narrow):
+    """Tall products whose alternating 192-column tiles fill half the chip (measured on inputs that change from call to call): the
+    256x128 (128x256) rings are faster, priced so, and constructed."""
+    from paper_2502_11407_amd import binding as gs
+    p = gs.gemm_problem(dtype, M, N, K, 0, tb, 1, out)
+    s = gs.construct(p)
+    assert us_ring < us_narrow and s.split_k == 1 and s.stages == 3 and sorted((s.tile[0][0], s.tile[1][0])) == [128, 256]
