@@ -461,7 +461,7 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // (small register-staged tiles keep two k tiles of loads in flight, too: Cfg::RSETS; and whole tiles of 128x128 with an m-contiguous
   // A, without which the 64x64 ones were taken for 3-7 % more: 768 x 3072 x 1080 14.7 us against 13.9, 3328 x 832 x 2272 27.2 against 25.6)
   const bool small = bm * bn <= 128 * 64 || (v.asrc == A_MC && split == 1 && bm * bn <= 128 * 128);
-  const bool two_sets = !direct && vec && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small;
+  const bool two_sets = !direct && vec && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
   const double t_ktile = alternate ? 0.0 : (two_sets ? 0.15 : 0.3) * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;

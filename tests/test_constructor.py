@@ -481,6 +481,17 @@ def test_construct_rejects_bad_problems():
     assert e.value.status == 2
 
 
+def test_states_of_one_k_step_are_not_priced_with_two_register_sets():
+    """k tiles of a single step keep one register set (the kernels' rule).  Priced with two, tiles of 64x32x32 led the states that the
+    walks of a literal T0 = 1 end in, and the instance nearest to them took 95 us on the up projection, 303's neighbourhood 58."""
+    from paper_2502_11407_amd import binding as gs
+    literal = gs.ConstructOpts(1.0, 2.0 ** -100, 0, 0, 0, 0)
+    for M, N, K in ((8192, 3072, 768), (2048, 2048, 2048)):
+        p = gs.gemm_problem("f16", M, N, K, 0, 0)
+        s = gs.construct(p, opts=literal)
+        assert s.predicted_us < 2.0 * gs.construct(p).predicted_us, (s.kernel_id, s.predicted_us)
+
+
 def test_hardware_without_compute_units_is_infeasible_not_fatal():
     """A description with no compute units has no schedule and no price: an error code, not a division that ends the process (so
     the calls run in a process of their own)."""
