@@ -34,11 +34,10 @@ PEAK_TFLOPS = {"f16": 2516.6, "bf16": 2516.6, "f32": 157.3}   # dense MFMA, MI35
 HBM_GBS = 8000.0
 # HBM-side bytes per launch of the headline kernel.  Not measured in this run (hardware counters need the
 # profiler): the figures of the FETCH_SIZE / WRITE_SIZE counter passes recorded in TRAFFIC_SOURCE, each scaled by
-# the same counter's reading for a 256 MiB device copy; keyed by (tile, wave tile, direct) of the instance they
-# were measured on.  Any other instance reports null.
+# the same counter's reading for a 256 MiB device copy; keyed by (tile, wave tile, k of a fragment, direct) of the
+# instance they were measured on.  Any other instance reports null.
 TRAFFIC_SOURCE = "profiles/gemm_f16_4096_kernel_trace.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE passes, copy-calibrated)"
-MEASURED_TRAFFIC_BYTES = {((256, 256, 64), (128, 128), 1): 268.9e6, ((256, 256, 64), (128, 64), 1): 269.4e6,
-                          ((256, 256, 64), (64, 128), 1): 269.4e6}
+MEASURED_TRAFFIC_BYTES = {((256, 256, 64), (128, 64, 32), 1): 268.7e6}
 
 
 def _algorithmic_bytes(w, gs_inputs, out_dtype="f32"):
@@ -515,7 +514,7 @@ def main():
     peak = PEAK_TFLOPS[w.dtype]
     sd = head.sched.describe()
     traffic = MEASURED_TRAFFIC_BYTES.get(((sd["tile_m"][0], sd["tile_n"][0], sd["tile_k"][0]),
-                                          (sd["tile_m"][1], sd["tile_n"][1]), sd["direct_lds"]))
+                                          (sd["tile_m"][1], sd["tile_n"][1], sd["tile_k"][1]), sd["direct_lds"]))
     _progress("headline %.1f us over %d launches (kernel %d)" % (ms * 1e3, args.steps, head.sched.kernel_id))
     line = {
         "metric": "TFLOP/s and % of MFMA peak per operator on 1 MI355X; construction time (s)",

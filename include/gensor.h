@@ -77,7 +77,7 @@ typedef struct {
   int32_t kernel_id;          /* index of the compiled instance; filled by gensor_construct */
   int32_t tile[3][3];
   int32_t vthread[2];         /* V for m and n: interleave depth of that operand's LDS tile (see above) */
-  int32_t stages;             /* LDS buffers: 1, 2, or a ring of 3 (two k tiles in flight) */
+  int32_t stages;             /* LDS buffers: 1, 2, or a ring of 3 or 4 (two or three k tiles in flight) */
   int32_t unroll;             /* MFMA k-steps unrolled per LDS stage = BK / (k per fragment) */
   int32_t vec_bytes;          /* 16: operands on 16-byte boundaries with rows of whole vectors; the element size: any alignment */
   int32_t direct_lds;         /* 1: global->LDS loads bypass registers */
@@ -88,8 +88,9 @@ typedef struct {
   int32_t iterations;         /* walk steps per chain */
   int32_t chains;             /* independent walks */
   int32_t states_scored;      /* complete states handed to the cost model */
-  int32_t round_units;        /* compute units a round of tiles is dealt over when split_k > 1: those of the hw the
-                                 schedule was constructed for (0: gensor_hw_mi355x()->compute_units) */
+  int32_t round_units;        /* compute units a round of tiles is dealt over: those of the hw the schedule was constructed for (0:
+                                 gensor_hw_mi355x()->compute_units).  Decides which tiles split_k > 1 splits, the columns (256 or
+                                 192) of the tiles named at tile[] above, and the pixel tiles of a staged convolution */
   uint64_t seed;
 } gensor_schedule;
 

@@ -419,8 +419,8 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   a.whole = sp.split == 1 ? a.tiles_m * a.tiles_n * a.batch : (int32_t)sp.whole;
   // Read ahead where the launch moves more than the 256 MiB Infinity Cache holds (its operands then come from memory; from
   // that cache they come soon enough, and the wait at the end of each wave costs 2-10 %: 96 x 1024 x 1024 x 64 with fp16
-  // output 61 -> 69 us, 48 x 768 x 768 x 64 21.1 -> 23.4), a batch is one or two k tiles deep, an XCD works through whole batches (its range of tiles is
-  // contiguous when the tile count is a multiple of 8) and the batch's workgroups cover the operands of the next with one
+  // output 61 -> 69 us, 48 x 768 x 768 x 64 21.1 -> 23.4), a batch is one or two k tiles deep, every XCD works through as many tiles (their count is
+  // a multiple of 8; its range of them is contiguous) and the batch's workgroups cover the operands of the next with one
   // vector a thread; only the tiles such launches end in are compiled for it (Cfg::HAS_AHEAD); dense matrices only, so that every byte of the range is an element.
   if (v.batch > 1 && v.K <= 2 * d->bk && d->vec && sp.split == 1 && (v.bsrc == B_KC || v.bsrc == B_NC)) {
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;

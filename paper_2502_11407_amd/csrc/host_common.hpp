@@ -76,7 +76,7 @@ SplitPlan split_plan(const InstanceDesc& d, const GemmView& v, int split, int ro
 bool split_allowed(const InstanceDesc& d, const GemmView& v, int split);
 
 // Does a launch of an instance whose wave groups alternate, with nothing split, cut C into tiles of 192 instead of 256 columns?
-// A round of them takes 0.8 to 0.95 of a round of the wide ones, so: where they need no more rounds.  Wide and narrow, us, with
+// A round of them takes 0.8 to 0.98 of a round of the wide ones, so: where they need no more rounds.  Wide and narrow, us, with
 // rounds: 8192 x 3072 x 768 bf16 2/2 42.2 -> 38.8 (column-major B 42.1 -> 36.3), 2048 x 3072 x 4096 f16 1/1 73.6 -> 58.5, 4096 x 2560
 // x 3072 1/1 62.6 -> 61.4; but 8192 x 4096 x 1024 bf16 2/3 57.3 -> 64.4, 4096^3 1/2 104.5 -> 135.7, 4096 x 4032 x 1024 1/2 34.8 -> 44.0.
 inline bool narrow_tiles(const GemmView& v, int64_t compute_units) {

@@ -236,13 +236,15 @@ def lattice():
     # rings of four stages for the 128x128 tiles of eight 64x32 waves: launches of about one tile per compute unit, where one
     # k tile in flight does not cover the latency (1280 x 1792 x 2048 f16 20.5 -> 17.1 us, 1536 x 2304 x 3072 32.5 -> 27.9,
     # 1856 x 1280 x 3264 30.8 -> 25.6, 1024 x 3072 x 768 row-major B 11.9 -> 10.0, 3072 x 768 x 4096 transA 34.0 -> 32.3).  Five stages
-    # are within 3 % either way; 64x64 waves are 6-13 % slower.
+    # are within 3 % either way.  Four 64x64 waves are 6-15 % slower on whole tiles (1216 x 2880 x 3456 f16 35.7 against 32.4 us, 4093 x 512 x
+    # 2048 18.4 against 16.7) and within 8 % either way on parts (376 x 528 x 32512 in 16 26.9 both, 392 x 448 x 26688 in 16 22.5 against 24.3).
     for dt in ("f16", "bf16"):
         for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
             for odt in ("f32", dt):
                 if odt == "f32" or asrc == "KC":
                     out.append(_inst(dt, odt, 128, 128, 64, 64, 32, 32, bsrc=bsrc, stages=4, direct=1, asrc=asrc))
-        # (the walks reach the eight-wave state less often where both operands are k-contiguous and k is deep)
+        # They are compiled where both operands are k-contiguous: there the walks reach the eight-wave state less often, and what such
+        # shapes took without them is slower still (1216 x 2880 x 3456 37.6, 4093 x 512 x 2048 21.7, 392 x 448 x 26688 28.0)
         for odt in ("f32", dt):
             out.append(_inst(dt, odt, 128, 128, 64, 64, 64, 32, stages=4, direct=1))
     for i, d in enumerate(out):

@@ -8,8 +8,9 @@ import pytest
 from test_cost_model_measured import _spearman
 
 FIXTURE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "split_and_loader_times.json")
-# measured when the fixture was written: splits worst 8 %, mean 3 %; loaders worst 17 % (the image layer), mean 2 %; boxes differ by up to 5 %
-REGRET_BAR, MEAN_REGRET_BAR = 0.22, 0.06
+# today: splits worst 10.4 %, mean 3.1 %; loaders worst 7.7 % but for the image layer (three channels, 7x7) at 19.9 %, mean 2.1 %; boxes
+# differ by up to 5 %
+REGRET_BAR, IMAGE_LAYER_BAR, MEAN_REGRET_BAR = 0.12, 0.22, 0.05
 
 
 @pytest.fixture(scope="module")
@@ -78,7 +79,8 @@ def test_cheapest_loader_is_close_to_the_measured_best(shapes):
         print(sh, "cheapest", pick[0], pick[2], "regret %.1f %%" % (100 * regrets[-1]))
     assert {(1, True), (1, False)} <= kinds and any(not d for d, _ in kinds)
     print("worst %.3f mean %.3f" % (max(regrets), sum(regrets) / len(regrets)))
-    assert max(regrets) <= REGRET_BAR and sum(regrets) / len(regrets) <= MEAN_REGRET_BAR
+    bars = [IMAGE_LAYER_BAR if (sh[2], sh[6]) == (3, 7) else REGRET_BAR for sh, _, _ in _conv(shapes)]
+    assert bars.count(IMAGE_LAYER_BAR) == 1 and all(r <= b for r, b in zip(regrets, bars)) and sum(regrets) / len(regrets) <= MEAN_REGRET_BAR
 
 
 def test_loader_prices_scale_like_the_hardware(shapes):
