@@ -287,6 +287,10 @@ __device__ inline int xcd_contiguous(int id, int count) {
   return xcd * (count >> 3) + min(xcd, count & 7) + (id >> 3);
 }
 
+// Do k tiles kt .. kt + n - 1 of bk rows, and `beyond` more rows, lie inside K?  (Nothing here exceeds K + n * bk in magnitude as long as
+// tile kt starts inside it: K may be anything up to INT32_MAX.)
+__host__ __device__ constexpr bool tiles_inside(int kt, int n, int bk, int beyond, int K) { return kt * bk <= K - (n * bk + beyond); }
+
 // tile number inside a batch -> tile coordinates: panels of `panel` tile rows, walked column by column
 __device__ inline void tile_of(const KernelArgs& args, int t, int& tile_m, int& tile_n) {
   const int panel = args.panel;
@@ -1286,7 +1290,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     // (parts of fp32 tiles are a few k tiles long and lose 3 % to the larger kernel: 467 x 263 x 479 in six parts 10.9 -> 11.4 us)
     if constexpr (LOOSE_A && LOOSE_B && !(ES == 4 && SPLIT)) {
       constexpr int BEYOND = C::ASRC == A_KC && C::BSRC == B_KC ? 0 : EPC - 1;
-      for (; (kt + 4) * BK + BEYOND <= Kx; kt += 2) {
+      for (; tiles_inside(kt, 4, BK, BEYOND, Kx); kt += 2) {
         k_tile(kt, std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{});
         k_tile(kt + 1, std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{});
       }
