@@ -122,9 +122,14 @@ def test_large_output_with_rows_off_the_lines_bit_exact(gs, beta):
     ("bf16", "bf16", 70, 301, 203, 0, 0, None, 20000001),
     ("f32", "f32", 40, 131, 99, 0, 0, None, 20000001),
     ("f16", "f32", 130, 5000001, 71, 0, 0, None, None),            # output rows of 20 MB
+    ("f16", "f32", 48, 304, 64, 0, 1, 20000000, None),             # aligned operands
+    ("bf16", "bf16", 72, 304, 40, 0, 0, None, 20000000),
+    ("f16", "f32", 304, 72, 40, 1, 1, 20000000, None),
+    ("f32", "f32", 130, 600, 96, 0, 1, 12000000, None),
 ])
 def test_leading_dimensions_beyond_the_larger_tiles(gs, dtype, out, M, N, K, ta, tb, lda, ldb):
-    """Rows so far apart that the 32-bit offsets inside a large tile do not reach: a smaller tile takes them."""
+    """Rows so far apart that the 32-bit offsets inside a large tile do not reach: a smaller tile takes them (operands on and off the
+    vector boundaries)."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(101)
 
