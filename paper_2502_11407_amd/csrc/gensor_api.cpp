@@ -315,6 +315,16 @@ std::mutex g_memo_mutex;
 std::map<std::array<int64_t, 17>, std::vector<RankedSchedule>> g_memo;
 const size_t kMemoLimit = 4096;      // shapes remembered; a full memo is emptied (a shape seen again is constructed again)
 
+// The largest leading dimension that the same tiles reach: tiles of 2^n rows (or k rows, with `beside` elements more in one) tell no
+// two of them apart, so one construction serves all.
+int64_t same_reach(int64_t ld, int esize, int64_t beside) {
+  for (int rows = 256; rows >= 16; rows /= 2) {
+    const int64_t most = ((0x7fffffffll - 1) / esize - beside) / (rows + 1);
+    if (ld <= most) return most;
+  }
+  return ld;
+}
+
 // The best schedule that needs at most `room` bytes of workspace.
 gensor_status memoised_schedule(const gensor_problem* p, bool vec_ok, int view_mode, size_t room, gensor_schedule* out,
                                 const LeadingDims* ld = nullptr) {
@@ -377,7 +387,8 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
     // The same for aligned operands: what would be constructed of the tiles that reach, for the room there is.  (256-row tiles reach
     // half as far as 128-row ones, and which of them a shape gets is the cost model's choice: rows that ran must not depend on it.)
     const int32_t panel = s->wg_remap;
-    if (!d->vec || memoised_schedule(p, vec_ok, mode, room, &local, &ld) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
+    const LeadingDims far = {same_reach(lda, v.esize, v.asrc == A_MC ? 256 : 0), same_reach(ldb, v.esize, v.bsrc == B_KC ? 0 : 256), same_reach(ldc, v.osize, 0)};
+    if (!d->vec || memoised_schedule(p, vec_ok, mode, room, &local, &far) != GENSOR_OK) return GENSOR_ERR_UNSUPPORTED;
     d = find_instance(&local, v);
     if (!d) return GENSOR_ERR_UNSUPPORTED;
     local.wg_remap = panel;

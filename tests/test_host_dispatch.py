@@ -40,6 +40,18 @@ def test_rows_too_long_for_the_constructed_tile_find_another(stub, case):
         assert max(a * es, b * es, (bm + 1) * (ldc or N) * os_) < 2 ** 31 - 1, (bm, bn, bk)
 
 
+def test_one_construction_serves_all_rows_of_the_same_reach(stub):
+    """Leading dimensions that differ from call to call: only the first pays for a construction (about 30 ms)."""
+    import time
+    p = stub.gs.gemm_problem("f16", 3287, 2816, 712, 0, 1)
+    first = time.perf_counter()
+    assert stub.call(p, None, lda=6000000)[0] == ACCEPTED
+    second = time.perf_counter()
+    for lda in range(6000008, 6000008 + 20 * 1000, 1000):
+        assert stub.call(p, None, lda=lda)[0] == ACCEPTED
+    assert time.perf_counter() - second < 0.5 * (second - first)
+
+
 def test_rows_too_long_for_every_tile_stay_refused(stub):
     p = stub.gs.gemm_problem("f16", 3287, 2816, 704, 0, 1)
     for lda in (200000000, 2 ** 31, 2 ** 40):                          # (17 rows of 200 million 16-bit elements: beyond 2^31 bytes)
