@@ -374,7 +374,9 @@ double predict_rows(const GemmView& v, const gensor_hw& hw, int bm, int bn, int 
   const double hbm_bw_cu = hw.bandwidth_gbs[0] * 1e3 / hw.compute_units;
   const double t_epi = (double)bm * pl.tile_px * v.osize / (1.2 * hbm_bw_cu) * resident;
   const double rounds = std::ceil(cu_tiles / (double)occ);
-  const double t_cu = rounds * (nst * t_stage + t_epi) + 1.5 * hw.latency_ns[0] * 1e-3;
+  // (four waves a workgroup cover less of it than eight: 64x256 tiles of 64x64 waves 9.5 us against 8.2 of 32x64 ones on 16 x 3 x 112 x 112, 64
+  // filters 7x7; 32x128 tiles 7.3 against 6.7 of 32x256 on 6 x 82 x 40, 16 filters 7x7)
+  const double t_cu = (nwaves < 8 ? 1.1 : 1.0) * (rounds * (nst * t_stage + t_epi) + 1.5 * hw.latency_ns[0] * 1e-3);
   const double bytes = (double)(pl.in_bytes + pl.w_bytes + pl.out_bytes);
   const double t_hbm = bytes / (0.6 * hw.bandwidth_gbs[0] * 1e3);
   return (t_cu > t_hbm ? t_cu : t_hbm) + 0.3 * (t_cu > t_hbm ? t_hbm : t_cu) + hw.launch_us;
@@ -426,7 +428,8 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double peak = 0.9 * (e == 2 ? hw.mfma_tflops_16bit : hw.mfma_tflops_f32) * 1e6 / hw.compute_units;
   double simd_use = nwaves * resident / hw.simds_per_cu;
   if (simd_use > 1.0) simd_use = 1.0;
-  const double t_mfma = 2.0 * bm * bn * kp / (peak * simd_use * (mb == 32 ? 1.0 : 0.9));
+  const bool ring_16 = direct && stages > 2 && mb == 16;
+  const double t_mfma = 2.0 * bm * bn * kp / (peak * simd_use * (mb == 32 || ring_16 ? 1.0 : 0.9));
   const double lds_bw = hw.bandwidth_gbs[1] * 1e3 / hw.compute_units;
   // fragment reads of the two operand tiles, each slowed by its bank-conflict ways (Eq. 3), and the tile's deposit
   const double t_lds = e * kp * ((double)bm * (bn / wn) * conflict_ways(v, hw, bk, 0, vm) +
@@ -447,6 +450,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // (three k tiles in flight: whole tiles were priced 7-20 % above the measured time without; parts of split ones were not, against
   // the smaller tiles that share their units: 128 x 264 x 28672 in 16 parts 18.9 us against 16.4)
   if (stages >= 4 && split == 1 && v.K > 3 * bk) overlap += 0.12;
+  // (rings of 16x16 blocks, Cfg::RING_16: 3-12 % faster than the same ones of 32x32 blocks on every measured shape, least where
+  // operands are transposed while they are read)
+  if (ring_16) overlap += v.bsrc == B_KC && v.asrc == A_KC ? 0.06 : 0.04;
   // (the alternating groups: one multiplies while the other waits, 94-97 % of the MFMA rate on all-zero operands, so no boundary
   // of a k tile is exposed; 4096^3 105 us against 124 of the next tile, 3648 x 2624 x 1856 38 against 41)
   // (192 columns: a k tile takes 0.81 of the time of a wide one's with k-contiguous operands and 0.85-0.9 with transposing reads,
@@ -461,7 +467,8 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // (small register-staged tiles keep two k tiles of loads in flight, too: Cfg::RSETS; and whole tiles of 128x128 with an m-contiguous
   // A, without which the 64x64 ones were taken for 3-7 % more: 768 x 3072 x 1080 14.7 us against 13.9, 3328 x 832 x 2272 27.2 against 25.6)
   const bool small = bm * bn <= 128 * 64 || (v.asrc == A_MC && split == 1 && bm * bn <= 128 * 128);
-  const bool two_sets = !direct && vec && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
+  // (off the vector boundaries: the tiles of up to 64x64, and parts, 333 x 777 x 5001 bf16 128x64 in six 17.5 us, 128x128 in twelve 19.9)
+  const bool two_sets = !direct && (vec || bm * bn <= 64 * 64 || split > 1) && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
   const double t_ktile = alternate ? 0.0 : (two_sets ? 0.15 : 0.3) * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;
@@ -496,7 +503,10 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (alternate) hide = 1.3;
   // a part stores its partial tile
   const double t_swap = bm * bn * 4.0 / (1.2 * hbm_bw_cu);
-  const double t_cu = cu_whole * (t_main + t_epi / hide) + cu_part * (t_part + t_swap / hide) + t_fill;
+  // (small tiles of twice the k depth: the first k tile takes longer to arrive, and where a unit works through several tiles that is paid
+  // again: 389 x 595 x 76 fp32 6.6 us against 5.7 with half the depth, 53 images of 64 x 112 x 361 bf16 6.7 against 5.4 on 64x64 tiles)
+  const double t_deep = !direct && bk * e >= 256 && bm * bn <= 64 * 32 ? 0.3 + 0.15 * cu_tiles : 0.0;
+  const double t_cu = cu_whole * (t_main + t_epi / hide) + cu_part * (t_part + t_swap / hide) + t_fill + t_deep;
   const double bytes_total = (double)v.batch * ((double)e * ((double)v.M * v.K + (double)v.K * v.N) + (double)eo * v.M * v.N);
   const double bytes_swap = split > 1 ? (tiles - whole) * split * bm * bn * 4.0 : 0.0;       // written once, read once by the launch that adds up
   // (the store-bound shapes stream at 6.5-6.9 TB/s, measured)
@@ -521,7 +531,7 @@ bool usable(const InstanceDesc& d, const GemmView& v, bool vec_ok, const Leading
   if (!instance_serves(d, v)) return false;
   if (ld && !offsets_fit(d, v, *ld)) return false;
   if (d.vec && !vec_ok) return false;
-  if (d.direct && !d.alternate() && v.bsrc != B_CONV && v.K % d.bk != 0) return false;
+  if (d.direct && !d.any_k() && v.bsrc != B_CONV && v.K % d.bk != 0) return false;
   return true;
 }
 
@@ -570,7 +580,8 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
   std::set<Etir> seen;
   // What is kept of the priced choices: those that no better ranked one undercuts in workspace.  (`large`: alternating tiles whose
   // parts need more than the static scratch, see below.)
-  std::vector<Choice> best, large;
+  // (`others`: the same list without the rings of 16x16 blocks at a K that only they and the alternating tiles take directly)
+  std::vector<Choice> best, large, others;
   int scored = 0;
   const Etir* best_state = nullptr;
   double best_state_us = 0.0;
@@ -591,7 +602,9 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
         const double us = predict_instance(v, c.hw, d, split);
         if (us <= 0) continue;
         const Choice choice = {&d, split, us, split > 1 ? split_plan(d, v, split, c.hw.compute_units).bytes : 0};
-        keep_choice(&(d.alternate() && choice.bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES ? large : best), choice);
+        const bool beyond = d.alternate() && choice.bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES;
+        keep_choice(beyond ? &large : &best, choice);
+        if (!beyond && !(d.any_k() && !d.alternate() && v.K % d.bk != 0)) keep_choice(&others, choice);
       }
     }
     const double us0 = predict(v, c.hw, e.tile[0][0], e.tile[1][0], e.tile[2][0], e.tile[0][1], e.tile[1][1], e.tile[2][1],
@@ -601,7 +614,9 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
   // The partial tiles of the alternating 256x256 instances take twice the room of the 256x128 ones' for 0-5 % of the time (768 x 3072 x
   // 8192 transA in six parts of 57 MB 51.6 us against 51.9 in three of 28; inputs that change 51.4 against 54.3).  A shape that
   // otherwise fits the static scratch keeps fitting it: callers with that much room could not run the schedule at all.
-  if (!large.empty() && (best.empty() || best[0].bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))
+  // (Whether it does is asked of the tiles that were there before the rings of 16x16 blocks: 960 x 3840 x 6944 transA 69.8 us in four
+  // parts of 63 MB, 71.7 in the two ring parts that fit.)
+  if (!large.empty() && (others.empty() || others[0].bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))
     for (const Choice& x : large) keep_choice(&best, x);
   if (best.empty() && best_state) {
     const int target[8] = {best_state->tile[0][0], best_state->tile[1][0], best_state->tile[2][0], best_state->tile[0][1],

@@ -221,6 +221,10 @@ struct Cfg {
   static constexpr bool ALTERNATE = DIRECT_ && STAGES_ == 2 && MB_ == 16 && ES == 2 && BM_ == 256 && BK_ == 64 &&
                                     ((BN_ == 256 && WM_ == 128 && WN_ == 64) || (BN_ == 192 && WM_ == 64 && WN_ == 96));
   static constexpr bool HAS_NARROW = ALTERNATE && BN_ == 256;
+  // Rings of 16x16 blocks: the same products for less power than 32x32 ones (beside the alternating tiles' loop), and they take any K.
+  // 32x32 -> 16x16, us: 2048^3 f16 22.5 -> 20.4, 512 x 512 x 32768 in 16 parts 28.7 -> 26.7, 256x128 tiles 4096 x 2048 x 2048 36.4 ->
+  // 33.1, with 16-bit output 32.9 -> 30.3, 768 x 3072 x 8192 transA in three parts 50.8 -> 48.2.  (On all-zero operands they are level.)
+  static constexpr bool RING_16 = DIRECT_ && STAGES_ > 2 && MB_ == 16;
   static constexpr int LDS_BYTES = STAGE_BYTES * STAGES + (ALTERNATE ? B_BYTES : 0);
   static constexpr int A_CHUNKS = (ASRC == A_KC) ? BM * CPR : BK * (BM * ES / 16);
   static constexpr int B_CHUNKS = (BSRC == B_KC) ? BN * CPR : BK * (BN * ES / 16);
@@ -563,8 +567,8 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       for (int i = 0; i < C::A_LOADS; ++i) {
         if (C::A_CHUNKS % C::THREADS != 0 && tid + i * C::THREADS >= C::A_CHUNKS) break;
         if (i * parts < part * C::A_LOADS || i * parts >= (part + 1) * C::A_LOADS) continue;
-        // (direct staging is only launched for K a multiple of BK: every tile is full)
-        const uint32_t off = (C::ASRC == A_MC || C::DIRECT || full || (int)a_kch[i] < Kx - k0) ? a_voff[i] : OOB;
+        // (other direct staging is only launched for K a multiple of BK: every tile is full)
+        const uint32_t off = (C::ASRC == A_MC || (C::DIRECT && !C::RING_16) || full || (int)a_kch[i] < Kx - k0) ? a_voff[i] : OOB;
         if constexpr (C::DIRECT)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (GENSOR_LDS void*)(lds + st * C::STAGE_BYTES + (i * C::THREADS + wave * 64) * 16),
                                                    16, off, 0, 0, 0);
@@ -598,7 +602,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         if (C::B_CHUNKS % C::THREADS != 0 && tid + i * C::THREADS >= C::B_CHUNKS) break;
         if (i * parts < part * C::B_LOADS || i * parts >= (part + 1) * C::B_LOADS) continue;
         uint32_t off = b_voff[i];
-        if constexpr (C::BSRC == B_KC && !C::DIRECT) off = (full || (int)b_kch[i] < Kx - k0) ? off : OOB;
+        if constexpr (C::BSRC == B_KC && (!C::DIRECT || C::RING_16)) off = (full || (int)b_kch[i] < Kx - k0) ? off : OOB;
         if constexpr (C::DIRECT) {
           __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (GENSOR_LDS void*)(lds + st * C::STAGE_BYTES + C::A_BYTES + (i * C::THREADS + wave * 64) * 16),
                                                    16, off, 0, 0, 0);
@@ -1217,13 +1221,18 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     auto k_tile = [&](int kt, int cur, auto fetch_tag, auto more_tag) {
       constexpr bool fetch = decltype(fetch_tag)::value, more = decltype(more_tag)::value;
       const int nxt = cur + 1 == S ? 0 : cur + 1;
-      if constexpr (fetch) {
-        const int dst = cur == 0 ? S - 1 : cur - 1;
-        fetch_a((kt + S - 1) * BK, dst);
-        fetch_b((kt + S - 1) * BK, dst);
-      }
+      // The requests of tile kt+S-1 go out over the first two k steps: in one burst at the top they fill the queue of the address
+      // unit, and a wave that waits for room in it issues no MFMA (one 64x64 wave per SIMD: 2048^3 f16 22.4 -> 21.1 us, 512 x 512 x
+      // 32768 in 16 parts 28.2 -> 27.0; two 64x32 waves of 16x16 blocks 20.6 -> 20.0, 256x128 tiles 4096 x 2048 x 2048 33.9 -> 33.1).
 #pragma unroll
       for (int ks = 0; ks < C::KSTEPS; ++ks) {
+        if constexpr (fetch) {
+          if (ks < 2) {
+            const int dst = cur == 0 ? S - 1 : cur - 1;
+            fetch_a((kt + S - 1) * BK, dst, ks, 2);
+            fetch_b((kt + S - 1) * BK, dst, ks, 2);
+          }
+        }
         if (ks + 1 < C::KSTEPS) {
           read_frags(cur, ks + 1, (ks + 1) & 1);
         } else if constexpr (more) {
@@ -1234,7 +1243,8 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
         }
         if (ks + 1 < C::KSTEPS || more) mma(ks & 1, std::integral_constant<int, 1>{});
         else mma(ks & 1, std::integral_constant<int, 0>{});
-        interleave();
+        if (fetch && ks < 2) interleave_vmem(std::false_type{});
+        else interleave();
       }
       return nxt;
     };
@@ -1478,8 +1488,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     // Smaller wave tiles, whose stores run
     // under other waves' products, lose 1-3 % to the packing (96 x 1024 x 1024 x 64 fp16 57.9 -> 59.9, 8192 x 768 x 3072 40.4 ->
     // 40.9) and keep the element stores.
-    // (Waves of 96 columns, three pairs of 16x16 blocks: half lines.)
-    constexpr bool PAIRS = OS == 2 && (C::ALTERNATE || (C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0));
+    // (Waves of 96 or 32 columns, pairs of 16x16 blocks: half lines.)  Rings of 16x16 blocks, whose element stores are quarter lines, gain
+    // at every size: 2048^3 f16 128x128 21.3 -> 19.8 us, 8192 x 1024 x 4096 256x128 69.2 -> 62.2.
+    constexpr bool PAIRS = OS == 2 && (C::ALTERNATE || C::RING_16 || (C::WM * C::WN >= 128 * 64 && C::WN % 64 == 0));
     constexpr bool HALF_LINES = C::WN % 64 != 0;
     if (PAIRS && args.paired) {
       if constexpr (PAIRS) {
@@ -1529,8 +1540,8 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       return;
     }
     // fp32 output of 16x16 blocks: their rows are half lines, so two blocks side by side trade lane rows first and a store
-    // writes two whole lines
-    constexpr bool ROWS = C::ALTERNATE && OS == 4;
+    // writes two whole lines (rings: 8192 x 1024 x 4096 67.0 -> 65.6 us, 2048^3 20.8 -> 20.4)
+    constexpr bool ROWS = (C::ALTERNATE || C::RING_16) && OS == 4;
     if (ROWS && beta == 0.f) {
       if constexpr (ROWS) {
         auto put = [&](uint32_t x, uint32_t off) {

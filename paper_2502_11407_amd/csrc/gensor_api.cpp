@@ -363,11 +363,11 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   }
   const InstanceDesc* d = find_instance(s, v);
   if (d && !d->vec && (v.bsrc == B_KC || v.bsrc == B_NC) && !offsets_fit(*d, v, ld)) {
-    // Rows too far apart for this tile's offsets (a schedule does not know the leading dimensions): the smallest tile of the
-    // instances at any alignment takes about twice as long ones.
+    // Rows too far apart for this tile's offsets (a schedule does not know the leading dimensions): the 64x64 tile of 16x16 blocks of
+    // the instances at any alignment takes about twice as long ones.
     for (int i = 0; i < g_num_instances; ++i) {
       const InstanceDesc& e = g_instances[i];
-      if (e.vec || e.mb != 16 || !instance_serves(e, v) || !offsets_fit(e, v, ld)) continue;
+      if (e.vec || e.mb != 16 || e.bm != 64 || !instance_serves(e, v) || !offsets_fit(e, v, ld)) continue;
       const int32_t panel = s->wg_remap, units = s->round_units;
       schedule_from_instance(e, &local);
       local.wg_remap = panel;
@@ -379,7 +379,7 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   }
   if (!d) return GENSOR_ERR_NO_SCHEDULE;
   if (d->vec && !vec_ok) return GENSOR_ERR_NO_SCHEDULE;          // schedule asks for vector accesses the operands cannot give
-  if (d->direct && !d->alternate() && v.bsrc != B_CONV && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
+  if (d->direct && !d->any_k() && v.bsrc != B_CONV && v.K % d->bk != 0) return GENSOR_ERR_NO_SCHEDULE;
   if (s->split_k < 1 || !split_allowed(*d, v, s->split_k)) return GENSOR_ERR_NO_SCHEDULE;
   SplitPlan sp = split_plan(*d, v, s->split_k, s->round_units);
   if (sp.split > 1 && room < sp.bytes) return GENSOR_ERR_WORKSPACE;

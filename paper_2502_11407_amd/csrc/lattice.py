@@ -60,11 +60,11 @@ def pad_m(d):
 
 
 def splittable(d):
-    """Instances also compiled with split tiles (split-k): plainly fetched operands, two or three LDS stages; off the
+    """Instances also compiled with split tiles (split-k): plainly fetched operands, two or more LDS stages; off the
     vector boundaries the fp32-output ones with a deep k tile."""
     if d["bsrc"] not in ("KC", "NC") or d["units"] or d["stages"] == 1:
         return False
-    return d["vec"] == 1 or (d["out"] == "f32" and d["mb"] == 32)
+    return d["vec"] == 1 or (d["out"] == "f32" and d["bk"] * (4 if d["dt"] == "f32" else 2) >= 128)
 
 
 def lattice():
@@ -247,6 +247,35 @@ def lattice():
         # shapes took without them is slower still (1216 x 2880 x 3456 37.6, 4093 x 512 x 2048 21.7, 392 x 448 x 26688 28.0)
         for odt in ("f32", dt):
             out.append(_inst(dt, odt, 128, 128, 64, 64, 64, 32, stages=4, direct=1))
+    # the rings of 16x16 blocks (the kernel's RING_16).  128x128 tiles only where neither operand is transposed while it is read, of which
+    # 16x16 blocks need more: m-contiguous A 2048^3 22.9 against 23.9 us, 1536 x 2304 x 3072 29.1 against 30.9; n-contiguous B within 5 %
+    # either way (1600 x 1216 x 3776 32.0 against 33.6, 1280 x 1664 x 1664 16.7 against 17.5, 2048^3 23.8 against 22.7).
+    for dt in ("f16", "bf16"):
+        for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+            for odt in ("f32", dt):
+                if odt == "f32" or asrc == "KC":
+                    for (bm, bn) in ((256, 128), (128, 256)):
+                        out.append(_inst(dt, odt, bm, bn, 64, 64, 64, 16, bsrc=bsrc, stages=3, direct=1, asrc=asrc))
+                if asrc == "KC" and bsrc == "KC":
+                    out.append(_inst(dt, odt, 128, 128, 64, 64, 32, 16, stages=4, direct=1))
+    # Small products, whose k loop is a chain of waits (request, LDS, barrier, fragments, products on one wave per SIMD): twice the
+    # k depth per barrier (512^3 fp32 6.9 -> 6.0 us, 671 x 2304 x 576 f16 13.1 -> 10.7), and at any alignment tiles small enough for a workgroup on
+    # every compute unit (311 x 535 x 487 fp32 11.4 -> 8.2, 1277 x 1923 x 165 f16 12.6 -> 9.6).  64x64 tiles of that depth were 4-8 % faster than
+    # their halves where a compute unit holds one workgroup and 10-28 % slower where it holds more (704 x 2816 x 1480 transA 17.7 against 20.1).
+    for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+        for dt in ("f16", "bf16"):
+            out.append(_inst(dt, "f32", 32, 32, 128, 16, 16, 16, bsrc=bsrc, asrc=asrc))
+            for odt in ("f32", dt):
+                out.append(_inst(dt, odt, 32, 32, 128, 16, 16, 16, bsrc=bsrc, vec=0, asrc=asrc))
+        out.append(_inst("f32", "f32", 32, 32, 64, 16, 16, 16, bsrc=bsrc, asrc=asrc))
+        out.append(_inst("f32", "f32", 32, 32, 64, 16, 16, 16, bsrc=bsrc, vec=0, asrc=asrc))
+        out.append(_inst("f32", "f32", 64, 32, 64, 32, 16, 16, bsrc=bsrc, vec=0, asrc=asrc))
+    # eight 64x32 waves for the large any-alignment tile: one wave per SIMD covers none of its waits (2039 x 1511 x 1003 bf16 19.2 -> 17.3 us,
+    # 1533 x 2041 x 1999 f16 31.9 -> 28.0)
+    for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
+        for dt in ("f16", "bf16"):
+            for odt in ("f32", dt):
+                out.append(_inst(dt, odt, 128, 128, 64, 64, 32, 32, bsrc=bsrc, vec=0, asrc=asrc))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],

@@ -23,6 +23,8 @@ struct InstanceDesc {
   int units;                            // patch-staged convolution: transpose units per thread
   // 256x256 tiles whose wave groups alternate (Cfg::ALTERNATE); directly staged, they still take any K
   bool alternate() const { return direct && stages == 2 && mb == 16 && bm == 256 && bn == 256 && bk == 64; }
+  // directly staged instances that take a K that is not a multiple of bk (Cfg::RING_16 are the others)
+  bool any_k() const { return alternate() || (direct && stages > 2 && mb == 16); }
   bool conv_rows() const { return bsrc == B_CONV && direct && !vec; }      // the row-staged convolution
   hipError_t (*launch)(const KernelArgs&, hipStream_t);
   hipError_t (*launch_split)(const KernelArgs&, hipStream_t);   // the same instance with split tiles; null if not compiled
