@@ -1608,9 +1608,9 @@ __global__ __launch_bounds__(256) void split_reduce(const KernelArgs args, int b
   const int b = g / per_block, q = g - b * per_block;
   const int row = (wave / waves_n) * wm + (b / nblk) * mb + 8 * q + 4 * (lane / mb);
   const int col = (wave % waves_n) * wn + (b % nblk) * mb + lane % mb;
-  // A tile's slots through one descriptor: the loads of a step that lie behind the last part read zero, at no cost.  Eight are
-  // in flight from five parts on.  (Four and then one by one, with 64-bit divisions per thread: 768 x 3072 x 8192 transA in
-  // six parts 60.3 us against 59.0, 1832 x 576 x 2304 in three 17.4 against 16.6.)
+  // A tile's slots through one descriptor: the loads that lie behind the last part read zero, at no cost.  All are in flight together, and
+  // non-temporal, for nobody reads a slot again: with at most eight and without the hint 312 x 240 x 15552 in twelve parts of 64x64 tiles 14.3
+  // us against 13.5, 560 x 408 x 17536 in twelve of 128x128 21.5 against 20.8, 128 x 128 x 4096 in sixteen of 32x32 7.1 against 6.9.
   const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc((void*)((const f32x4*)args.partials + (int64_t)u * args.split * groups), 0,
                                                                         (uint32_t)(args.split * groups * 16), 0x00020000u);
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
@@ -1618,15 +1618,16 @@ __global__ __launch_bounds__(256) void split_reduce(const KernelArgs args, int b
     constexpr int n = decltype(n_tag)::value;
     u32x4 v[n];
 #pragma unroll
-    for (int i = 0; i < n; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(slots, (uint32_t)(((o + i) * groups + r) * 16), 0, 0);
+    for (int i = 0; i < n; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(slots, (uint32_t)(((o + i) * groups + r) * 16), 0, 2 /* nt */);
 #pragma unroll
     for (int i = 0; i < n; ++i)
 #pragma unroll
       for (int x = 0; x < 4; ++x) sum[x] += as_f32(v[i][x]);
   };
-  if (args.split <= 4) add(0, std::integral_constant<int, 4>{});
-  else
-    for (int o = 0; o < args.split; o += 8) add(o, std::integral_constant<int, 8>{});
+  if (args.split <= 2) add(0, std::integral_constant<int, 2>{});
+  else if (args.split <= 4) add(0, std::integral_constant<int, 4>{});
+  else if (args.split <= 8) add(0, std::integral_constant<int, 8>{});
+  else add(0, std::integral_constant<int, 16>{});            // (split_allowed: there are no more)
   const int bidx = wg / tiles_per_batch;
   int tile_m, tile_n;
   tile_of(args, wg - bidx * tiles_per_batch, tile_m, tile_n);
