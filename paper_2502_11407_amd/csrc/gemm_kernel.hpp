@@ -59,6 +59,7 @@ struct KernelArgs {
   float alpha, beta;
   int32_t through;                 // C is stored write-through (beside beta only with fp32 output)
   int32_t paired;                  // 16-bit C without beta whose columns 2j and 2j + 1 are one aligned dword
+  int32_t lds_stages;              // LDS stages a launch allocates at most (its k tiles, where fewer than the instance's)
   int32_t narrow;                  // tiles of 192 instead of 256 columns (instances whose wave groups alternate; the launch selects them)
   int32_t tiles_m, tiles_n, batch;
   int32_t panel;                   // tile rows per panel in the workgroup->tile map

@@ -440,6 +440,15 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
     const int64_t moved = v.batch * (wa + wb + v.M * v.N * v.osize);
     if (tiles * v.batch % 8 == 0 && moved > (int64_t)256 * 1024 * 1024 && wa + wb <= tiles * d->threads * 16) { a.ahead_a = wa; a.ahead_b = wb; }
   }
+  // A launch of fewer k tiles than its instance has LDS stages touches that many stages only; allocating no more lets another workgroup
+  // onto each compute unit, whose loads run under the others' stores.  fp32 output, us: 48 x 1024 x 1024 x 64 48.3 -> 40.6, 96 x 512 x 512
+  // x 64 27.1 -> 24.3, 64 x 384 x 384 x 64 9.3 -> 8.3, 50 x 1000 x 1000 x 64 52.0 -> 46.2; 16-bit 64 x 384 x 384 x 64 7.3 -> 6.4, 50 x 1000 x 1000
+  // x 64 41.1 -> 37.0.  Large outputs that are written through lose to more of them storing at once: 8192 x 8192 x 64 fp32 45.4 ->
+  // 48.0, 96 x 1024 x 1024 x 64 with the next batch read ahead 74.9 -> 77.0; 16-bit 48 x 1024 x 1024 x 64 (100 MB) 33.1 -> 36.1, 69 x 768 x
+  // 768 x 64 (81 MB) 31.3 -> 31.9, but 40 x 768 x 768 x 64 (47 MB) 13.3 -> 12.5.
+  const bool resident = !a.through || (a.ahead_a + a.ahead_b == 0 && c_bytes <= (v.osize == 2 ? 64ll : 224ll) * 1024 * 1024);
+  const int64_t k_tiles = (v.K + d->bk - 1) / d->bk;
+  a.lds_stages = resident && k_tiles < d->stages ? (int32_t)k_tiles : d->stages;
   a.partials = (float*)workspace;
   if (d->units) {
     ConvPlan pl;

@@ -59,10 +59,11 @@ hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
   static std::atomic<uint64_t> done{0};
   hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT, AHEAD>, C::LDS_BYTES, done);
   if (e != hipSuccess) return e;
+  const int lds_bytes = C::ALTERNATE || a.lds_stages >= C::STAGES ? C::LDS_BYTES : C::STAGE_BYTES * a.lds_stages;
   // one workgroup per whole tile and, in a split launch, a.split per tile behind them
   const unsigned tiles = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.batch;
   const unsigned grid = SPLIT ? (unsigned)a.whole + (tiles - (unsigned)a.whole) * (unsigned)a.split : tiles;
-  hipLaunchKernelGGL((contraction_kernel<C, SPLIT, AHEAD>), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, st, a);
+  hipLaunchKernelGGL((contraction_kernel<C, SPLIT, AHEAD>), dim3(grid), dim3(C::THREADS), lds_bytes, st, a);
   return hipGetLastError();
 }
 
