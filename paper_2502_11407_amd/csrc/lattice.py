@@ -276,6 +276,18 @@ def lattice():
         for dt in ("f16", "bf16"):
             for odt in ("f32", dt):
                 out.append(_inst(dt, odt, 128, 128, 64, 64, 32, 32, bsrc=bsrc, vec=0, asrc=asrc))
+    # Patch-staged convolution with twice (and four times) the channels per stage.  A stage is a round trip to memory, which a compute
+    # unit with one or two workgroups does not cover, and the smaller tiles fill a quarter to half of the staging units their threads have.
+    # Best with 16 channels -> best, us: 24 x 248 x 17 x 17, 112 filters, stride 2, f16 26.2 -> 15.2; 8 x 224 x 17 x 17, 192 filters, stride 2, bf16 20.3
+    # -> 13.6; 8 x 56 x 15 x 15, 208 filters 10.1 -> 7.2; 35 x 152 x 19 x 19, 72 filters 19.2 -> 14.3.  (64x256 tiles gain 3 % on inputs that stay and
+    # lose 2 on ones that change, 32 x 64 x 56 x 56, 64 filters.)
+    for dt in ("f16", "bf16"):
+        for odt in ("f32", dt):
+            for (bm, bn, wm, wn) in ((32, 128, 32, 32), (32, 256, 32, 64), (64, 128, 32, 64), (64, 64, 32, 32)):
+                out.append(_convp(dt, odt, bm, bn, 32, wm, wn, 1, stages=1))
+            out.append(_convp(dt, odt, 32, 128, 64, 32, 32, 1, stages=1))
+    for (bm, bn, wm, wn) in ((32, 128, 32, 32), (64, 64, 32, 32), (64, 128, 32, 64)):
+        out.append(_convp("f32", "f32", bm, bn, 16, wm, wn, 1, stages=1))
     for i, d in enumerate(out):
         d["id"] = i
     keys = [(d["dt"], d["out"], d["bm"], d["bn"], d["bk"], d["wm"], d["wn"], d["mb"], d["vm"], d["vn"], d["bsrc"], d["vec"],

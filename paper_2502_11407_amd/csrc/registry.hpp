@@ -93,7 +93,7 @@ hipError_t launch_conv_tail(const KernelArgs& a, hipStream_t st, int raw_bytes) 
   return hipGetLastError();
 }
 
-// The element-wise fetch of the input tensor's last vector is compiled only into the launches that can need it:
+// Moving back the vectors that would run past the input's end is compiled only into the launches that can need it:
 // 16-bit elements and an odd row length (any other vector that runs past the end starts on a dword boundary and
 // the buffer's range check returns its valid part).
 template <typename C, int FMODE, bool THROUGH>
