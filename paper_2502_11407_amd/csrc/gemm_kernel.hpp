@@ -174,8 +174,10 @@ template <> struct Mfma<f32_t, 16> {   // 16x16x4 per step
   static constexpr int NACC = 4;
   __device__ static inline void run(const u32x4& a, const u32x4& b, Acc& c) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(as_f32(a[t]), as_f32(b[t]), c, 0, 0, 0);
+    for (int t = 0; t < 4; ++t) step(a, b, t, c);
+  }
+  __device__ static inline void step(const u32x4& a, const u32x4& b, int t, Acc& c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(as_f32(a[t]), as_f32(b[t]), c, 0, 0, 0);
   }
 };
 
@@ -239,6 +241,11 @@ struct Cfg {
   static constexpr int STAGE_REGS = 4 * (A_LOADS + B_LOADS * (BSRC_ == B_NCS2 ? 2 : 1));
   static constexpr int OTHER_REGS = WM_ * WN_ / 64 + (MB_ == 16 ? 12 : 8) * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
   static constexpr int RSETS = (!DIRECT_ && STAGES_ == 2 && KSTEPS % 2 == 0 && BSRC_ != B_CONV && 2 * STAGE_REGS + OTHER_REGS <= 256) ? 2 : 1;
+  // Small tiles of deep k tiles stand where parts of split tiles stood, whose shorter chains of sums lose less to rounding: they keep as
+  // many sums per output as such a split had parts (fp32 a sixteenth or an eighth of the products each, 16-bit operands an eighth), added up at
+  // the end, at no cost in time (a wave has registers to spare).  In one chain an fp32 product of depth 600 was 3.7e-7 from 64 bits, where its
+  // split in eight had been 1.5e-7; over 85 drawn products whose schedule changed the distance is now 0.77 of what it was (geometric mean).
+  static constexpr int CHAINS = DIRECT_ || MB_ != 16 || BK_ * ES != 256 || MBLK * NBLK > 2 ? 1 : ES == 4 && MBLK * NBLK == 1 ? 16 : 8;
   // the tile that store-bound batches of a shallow k end in also exists with the next batch read ahead
   static constexpr bool HAS_AHEAD = VEC_ && DIRECT_ && STAGES_ == 2 && ES == 2 && ElemSize<OutT_>::value == 4 && BM_ == 128 && BN_ == 128 && WAVES == 8;
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");
@@ -376,6 +383,19 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     for (int j = 0; j < C::NBLK; ++j)
 #pragma unroll
       for (int v = 0; v < MF::NACC; ++v) acc[i][j][v] = 0.f;
+  constexpr int CHAINS = C::CHAINS;
+  Acc more_acc[CHAINS > 1 ? CHAINS - 1 : 1][C::MBLK][C::NBLK];       // ... of the further chains of a block
+  auto chain = [&](int n, int i, int j) -> Acc& { return n == 0 ? acc[i][j] : more_acc[n - 1][i][j]; };
+  if constexpr (CHAINS > 1) {
+#pragma unroll
+    for (int n = 1; n < CHAINS; ++n)
+#pragma unroll
+      for (int i = 0; i < C::MBLK; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NBLK; ++j)
+#pragma unroll
+          for (int v = 0; v < MF::NACC; ++v) chain(n, i, j)[v] = 0.f;
+  }
 
   // ---- buffer resources.  Each operand is addressed through a buffer descriptor whose
   // base is this workgroup's first row (or column) at the current k tile and whose extent
@@ -850,13 +870,19 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     if constexpr (ASM_TR) __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0); the other counters untouched
     __syncthreads();
   };
-  auto mma = [&](int buf, auto groups_tag) {
+  // (`at`: the k step, counted over the k tiles of the register sets, where a block has several chains)
+  auto mma = [&](int buf, auto groups_tag, int at = 0) {
     settle(buf, groups_tag);
 #pragma unroll
     for (int bi = 0; bi < C::MBLK; ++bi)
 #pragma unroll
       for (int bj = 0; bj < C::NBLK; ++bj) {
-        MF::run(fa[buf][bi], fb[buf][bj], acc[bi][bj]);
+        if constexpr (CHAINS > 1 && ES == 4) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) MF::step(fa[buf][bi], fb[buf][bj], t, chain((4 * at + t) % CHAINS, bi, bj));
+        } else {
+          MF::run(fa[buf][bi], fb[buf][bj], chain(at % CHAINS, bi, bj));
+        }
       }
   };
 
@@ -1292,7 +1318,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           block_sync();
           read_frags(nxt, 0, 0);
         }
-        mma(ks & 1, std::integral_constant<int, 0>{});
+        mma(ks & 1, std::integral_constant<int, 0>{}, set * C::KSTEPS + ks);
         interleave();
       }
     };
@@ -1379,6 +1405,20 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       wait_deposits();
       block_sync();
     }
+  }
+
+  if constexpr (CHAINS > 1) {
+    static_assert(C::RSETS == 2, "the chains are told apart in the loop of two register sets");
+#pragma unroll
+    for (int half = CHAINS / 2; half >= 1; half /= 2)
+#pragma unroll
+      for (int n = 0; n < half; ++n)
+#pragma unroll
+        for (int i = 0; i < C::MBLK; ++i)
+#pragma unroll
+          for (int j = 0; j < C::NBLK; ++j)
+#pragma unroll
+            for (int v = 0; v < MF::NACC; ++v) chain(n, i, j)[v] += chain(n + half, i, j)[v];
   }
 
   // ---- split tile: this part's sums go to its slot, 16 bytes per lane and store, a wave's store one contiguous KiB;
