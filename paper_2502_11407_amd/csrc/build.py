@@ -17,8 +17,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", HERE,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-# patch-staged convolution units only: accumulators stay in plain VGPRs (no copies to and from
-# AGPRs around the tap loop)
+# patch-staged convolutions and tiles of several sums per output: accumulators stay in plain VGPRs (no copies to and from
+# AGPRs around the tap loop, or in every k tile)
 CONV_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 PER_TU = 4
 
@@ -36,7 +36,9 @@ def generate():
     tus = []
     # translation units hold instances of one kernel template only (they are built with different flags)
     conv = [d for d in L if d["units"] or lattice.conv_rows(d)]
-    ordered = [d for d in L if not (d["units"] or lattice.conv_rows(d))]
+    small = [d for d in L if lattice.chains(d) > 1]
+    ordered = [d for d in L if not (d["units"] or lattice.conv_rows(d) or lattice.chains(d) > 1)]
+    ordered += [None] * (-len(ordered) % PER_TU) + small
     ordered += [None] * (-len(ordered) % PER_TU) + conv
     for t in range(0, len(ordered), PER_TU):
         group = [d for d in ordered[t:t + PER_TU] if d is not None]
@@ -49,7 +51,8 @@ def generate():
                 src.append("hipError_t launch_split_%d(const KernelArgs& a, hipStream_t st) { return launch_instance<C_%d, true>(a, st); }"
                            % (d["id"], d["id"]))
         src.append("}  // namespace gensor\n")
-        path = os.path.join(GEN, "%s_%03d.hip" % ("conv" if group[0]["units"] or lattice.conv_rows(group[0]) else "inst", t // PER_TU))
+        kind = "conv" if group[0]["units"] or lattice.conv_rows(group[0]) else "chains" if lattice.chains(group[0]) > 1 else "inst"
+        path = os.path.join(GEN, "%s_%03d.hip" % (kind, t // PER_TU))
         _write_if_changed(path, "\n".join(src))
         tus.append(path)
     for f in os.listdir(GEN):                      # units of an earlier lattice
@@ -93,7 +96,7 @@ def _compile(src):
     # host sources: no fused multiply-add contraction, so the constructor's double arithmetic
     # is the plain IEEE sequence its tests compare against
     extra = ["-ffp-contract=off"] if src.endswith(".cpp") else []
-    if os.path.basename(src).startswith("conv_"):
+    if os.path.basename(src).startswith(("conv_", "chains_")):
         extra += CONV_FLAGS
     cmd = [HIPCC] + FLAGS + extra + ["-x", "hip", "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)

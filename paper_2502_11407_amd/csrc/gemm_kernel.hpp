@@ -242,10 +242,11 @@ struct Cfg {
   static constexpr int OTHER_REGS = WM_ * WN_ / 64 + (MB_ == 16 ? 12 : 8) * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
   static constexpr int RSETS = (!DIRECT_ && STAGES_ == 2 && KSTEPS % 2 == 0 && BSRC_ != B_CONV && 2 * STAGE_REGS + OTHER_REGS <= 256) ? 2 : 1;
   // Small tiles of deep k tiles stand where parts of split tiles stood, whose shorter chains of sums lose less to rounding: they keep as
-  // many sums per output as such a split had parts (fp32 a sixteenth or an eighth of the products each, 16-bit operands an eighth), added up at
-  // the end, at no cost in time (a wave has registers to spare).  In one chain an fp32 product of depth 600 was 3.7e-7 from 64 bits, where its
+  // many sums per output as such a split had parts, an eighth of the products each, added up at the end (512^3 fp32 6.14 us, 5.97 with one
+  // chain and 6.28 with sixteen; compiled with the accumulators in plain registers, between which and the others they were copied in every k
+  // tile: 7.2).  In one chain an fp32 product of depth 600 was 3.7e-7 from 64 bits, where its
   // split in eight had been 1.5e-7; over 85 drawn products whose schedule changed the distance is now 0.77 of what it was (geometric mean).
-  static constexpr int CHAINS = DIRECT_ || MB_ != 16 || BK_ * ES != 256 || MBLK * NBLK > 2 ? 1 : ES == 4 && MBLK * NBLK == 1 ? 16 : 8;
+  static constexpr int CHAINS = DIRECT_ || MB_ != 16 || BK_ * ES != 256 || MBLK * NBLK > 2 ? 1 : 8;
   // the tile that store-bound batches of a shallow k end in also exists with the next batch read ahead
   static constexpr bool HAS_AHEAD = VEC_ && DIRECT_ && STAGES_ == 2 && ES == 2 && ElemSize<OutT_>::value == 4 && BM_ == 128 && BN_ == 128 && WAVES == 8;
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");

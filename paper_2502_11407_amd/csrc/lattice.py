@@ -42,6 +42,13 @@ def alternate(d):
     return d["direct"] == 1 and d["stages"] == 2 and d["mb"] == 16 and (d["bm"], d["bn"], d["bk"]) == (256, 256, 64)
 
 
+def chains(d):
+    """Sums that a lane keeps per output (the kernel's CHAINS)."""
+    es = 4 if d["dt"] == "f32" else 2
+    one = d["direct"] or d["units"] or d["bsrc"] not in ("KC", "NC") or d["mb"] != 16 or d["bk"] * es != 256 or d["wm"] * d["wn"] > 2 * 256
+    return 1 if one else 8
+
+
 def _pad(v, row_bytes):
     if v == 1:
         return 0
