@@ -582,8 +582,8 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
   std::set<Etir> seen;
   // What is kept of the priced choices: those that no better ranked one undercuts in workspace.  (`large`: alternating tiles whose
   // parts need more than the static scratch, see below.)
-  // (`others`: the same list without the rings of 16x16 blocks at a K that only they and the alternating tiles take directly)
-  std::vector<Choice> best, large, others;
+  // (`inside`: of the choices that are not `large` those of tiles that also serve without rings at any K, see below)
+  std::vector<Choice> best, large, inside;
   int scored = 0;
   const Etir* best_state = nullptr;
   double best_state_us = 0.0;
@@ -606,19 +606,21 @@ gensor_status construct_internal(const gensor_problem* p, const gensor_hw* hw, c
         const Choice choice = {&d, split, us, split > 1 ? split_plan(d, v, split, c.hw.compute_units).bytes : 0};
         const bool beyond = d.alternate() && choice.bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES;
         keep_choice(beyond ? &large : &best, choice);
-        if (!beyond && !(d.any_k() && !d.alternate() && v.K % d.bk != 0)) keep_choice(&others, choice);
+        if (!beyond && !(d.any_k() && !d.alternate() && v.K % d.bk != 0)) keep_choice(&inside, choice);
       }
     }
     const double us0 = predict(v, c.hw, e.tile[0][0], e.tile[1][0], e.tile[2][0], e.tile[0][1], e.tile[1][1], e.tile[2][1],
                                e.v[0], e.v[1], vec_ok ? 1 : 0, 2, 0, 1);
     if (us0 > 0 && (!best_state || us0 < best_state_us)) { best_state = &e; best_state_us = us0; }
   }
-  // The partial tiles of the alternating 256x256 instances take twice the room of the 256x128 ones' for 0-5 % of the time (768 x 3072 x
-  // 8192 transA in six parts of 57 MB 51.6 us against 51.9 in three of 28; inputs that change 51.4 against 54.3).  A shape that
-  // otherwise fits the static scratch keeps fitting it: callers with that much room could not run the schedule at all.
-  // (Whether it does is asked of the tiles that were there before the rings of 16x16 blocks: 960 x 3840 x 6944 transA 69.8 us in four
-  // parts of 63 MB, 71.7 in the two ring parts that fit.)
-  if (!large.empty() && (others.empty() || others[0].bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))
+  // The partial tiles of the alternating 256x256 instances take twice the room of the 256x128 ones'.  Where K is a multiple of 64, callers that
+  // hold the static scratch and no more run what is constructed here, and it keeps within that if the best of the other tiles does:
+  // 768 x 3072 x 8192 transA in six parts of 57 MB 51.6 us against 51.9 in three of 28, 4096 x 768 x 8320 64.4 against 69.5.  At other K only the alternating tiles were
+  // large ones that took their operands directly, so callers of such shapes already bring the larger workspace, and the rings of 16x16 blocks,
+  // which now take any K and fit, would cost them 2-16 %: 960 x 3840 x 6944 transA 67.0 us in four parts of 63 MB, 71.4 in the two
+  // ring parts that fit, x 8104 74.9 and 79.2, 4096 x 768 x 7976 62.4 and 67.8, 1936 x 2072 x 6504 74.6 and 86.4, 4096 x 1496 x 7584 104.9 and
+  // 106.6.  So rings at such a K do not count among what fits.  A caller with less room names no schedule and gets the ring.
+  if (!large.empty() && (inside.empty() || inside[0].bytes > (size_t)GENSOR_STATIC_SCRATCH_BYTES))
     for (const Choice& x : large) keep_choice(&best, x);
   if (best.empty() && best_state) {
     const int target[8] = {best_state->tile[0][0], best_state->tile[1][0], best_state->tile[2][0], best_state->tile[0][1],

@@ -89,6 +89,26 @@ def test_splits_beyond_the_static_scratch_where_no_other_fits_either(stub):
     assert stub.call(p, s, static=True) == (4, None)
 
 
+@pytest.mark.parametrize("M,N", [(960, 3840), (896, 3584), (4096, 768)])
+@pytest.mark.parametrize("K", [6912, 6944, 6952, 6976, 6984, 7008, 7040])
+def test_static_scratch_at_neighbouring_depths(stub, M, N, K):
+    """Multiples of 64: what is constructed fits the static scratch.  Other depths: it may be the alternating tile that does not, which is then
+    priced below what fits; a call that names no schedule runs within the scratch either way."""
+    from paper_2502_11407_amd.binding import STATIC_SCRATCH_BYTES
+    p = stub.gs.gemm_problem("f16", M, N, K, 1, 0)
+    s = stub.construct(p)
+    st, launch = stub.call(p, None, room=STATIC_SCRATCH_BYTES)
+    t = stub.gs.instance_schedule(launch["id"], p)
+    t.split_k = launch["split"]
+    assert st == ACCEPTED and stub.workspace_bytes(p, t) <= STATIC_SCRATCH_BYTES
+    if K % 64 == 0:
+        assert (t.kernel_id, t.split_k) == (s.kernel_id, s.split_k)
+    elif stub.workspace_bytes(p, s) > STATIC_SCRATCH_BYTES:
+        assert s.kernel_id == _alternating(stub, p).kernel_id and s.predicted_us < stub.gs.predict_us(t, p)
+    else:
+        assert (t.kernel_id, t.split_k) == (s.kernel_id, s.split_k)
+
+
 @pytest.mark.parametrize("dtype,M,N,K,ta,tb", [("f16", 768, 3072, 8192, 1, 0), ("bf16", 1024, 1024, 8192, 0, 1), ("f16", 512, 512, 32768, 0, 1),
                                                ("f16", 1096, 1568, 11552, 0, 0), ("f16", 2304, 576, 7944, 1, 0)])
 def test_unnamed_schedules_split_as_far_as_the_workspace_goes(stub, dtype, M, N, K, ta, tb):
