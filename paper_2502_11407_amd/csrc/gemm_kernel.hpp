@@ -242,7 +242,7 @@ struct Cfg {
   static constexpr int OTHER_REGS = WM_ * WN_ / 64 + (MB_ == 16 ? 12 : 8) * (MBLK + NBLK) + 2 * (A_LOADS + B_LOADS) + 24;
   static constexpr int RSETS = (!DIRECT_ && STAGES_ == 2 && KSTEPS % 2 == 0 && BSRC_ != B_CONV && 2 * STAGE_REGS + OTHER_REGS <= 256) ? 2 : 1;
   // Small tiles of deep k tiles stand where parts of split tiles stood, whose shorter chains of sums lose less to rounding: they keep as
-  // many sums per output as such a split had parts, an eighth of the products each, added up at the end (512^3 fp32 6.14 us, 5.97 with one
+  // many sums per output as such a split had parts, an eighth of the products each (16-bit: one k step of every other k tile), added up at the end (512^3 fp32 6.14 us, 5.97 with one
   // chain and 6.28 with sixteen; compiled with the accumulators in plain registers, between which and the others they were copied in every k
   // tile: 7.2).  In one chain an fp32 product of depth 600 was 3.7e-7 from 64 bits, where its
   // split in eight had been 1.5e-7; over 85 drawn products whose schedule changed the distance is now 0.77 of what it was (geometric mean).
@@ -1337,8 +1337,11 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       k_tile(kt, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
       k_tile(kt + 1, std::integral_constant<int, 1>{}, std::true_type{}, std::false_type{});
     }
-    if (kt + 1 < nk) k_tile(kt++, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
-    k_tile(kt, std::integral_constant<int, 0>{}, std::false_type{}, std::false_type{});
+    const bool even = kt + 1 < nk;
+    if (even) k_tile(kt++, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
+    // (the last tile requests and deposits nothing: its set only tells the chains apart)
+    if (CHAINS > 1 && even) k_tile(kt, std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
+    else k_tile(kt, std::integral_constant<int, 0>{}, std::false_type{}, std::false_type{});
   } else if constexpr (PIPE) {
     // Whether a further k tile follows is a compile-time property of the loop body: the last k
     // tile is peeled.  With a run-time test the two paths would meet in front of the last k
