@@ -247,6 +247,13 @@ struct Cfg {
   // tile: 7.2).  In one chain an fp32 product of depth 600 was 3.7e-7 from 64 bits, where its
   // split in eight had been 1.5e-7; over 85 drawn products whose schedule changed the distance is now 0.77 of what it was (geometric mean).
   static constexpr int CHAINS = DIRECT_ || MB_ != 16 || BK_ * ES != 256 || MBLK * NBLK > 2 ? 1 : 8;
+  // More sums per output in launches of a deep k, where tiles that others once took in (more) parts are whole (launch_instance; at 16-bit output
+  // its rounding is a thousand times larger).  Without them, distance from 64 bits with the parts and with the whole: 589 x 1163 x 1643
+  // f16 any-alignment, four parts 1.37e-7, one tile 2.59e-7 (four sums 1.36e-7); 3072 x 768 x 7352 f16 transA 2.28e-7, 3.16e-7 (two 2.27e-7);
+  // 1792 x 1152 x 2176 bf16 2.60e-7 (four 1.23e-7).  For it 64x32 waves of the rings have registers for four, 64x64 ones for two, and the
+  // any-alignment tile needs 150-160 instead of 96-104.
+  static constexpr bool LOOSE_64 = !DIRECT_ && !VEC_ && ES == 2 && BM_ == 64 && BN_ == 64 && BK_ == 64 && RSETS == 2;
+  static constexpr int DEEP_CHAINS = ElemSize<OutT_>::value != 4 ? CHAINS : RING_16 ? (BM_ * BN_ == 128 * 128 ? 4 : 2) : LOOSE_64 ? 4 : CHAINS;
   // the tile that store-bound batches of a shallow k end in also exists with the next batch read ahead
   static constexpr bool HAS_AHEAD = VEC_ && DIRECT_ && STAGES_ == 2 && ES == 2 && ElemSize<OutT_>::value == 4 && BM_ == 128 && BN_ == 128 && WAVES == 8;
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");
@@ -318,8 +325,8 @@ __device__ inline void tile_of(const KernelArgs& args, int t, int& tile_m, int& 
 // ---------------------------------------------------------------- the kernel
 // SPLIT: the launch has split tiles (KernelArgs::split > 1); without it the kernel knows at compile time
 // that every workgroup owns a whole tile.  AHEAD: workgroups read the next batch's operands ahead (KernelArgs::ahead_a;
-// carrying the unused load through every launch cost the small batched ones 1-2 %).
-template <typename C, bool SPLIT = false, bool AHEAD = false>
+// carrying the unused load through every launch cost the small batched ones 1-2 %).  MORE_SUMS: Cfg::DEEP_CHAINS.
+template <typename C, bool SPLIT = false, bool AHEAD = false, bool MORE_SUMS = false>
 __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArgs args) {
   typedef typename C::T T;
   typedef Mfma<T, C::MB> MF;
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     for (int j = 0; j < C::NBLK; ++j)
 #pragma unroll
       for (int v = 0; v < MF::NACC; ++v) acc[i][j][v] = 0.f;
-  constexpr int CHAINS = C::CHAINS;
+  constexpr int CHAINS = MORE_SUMS ? C::DEEP_CHAINS : C::CHAINS;
   Acc more_acc[CHAINS > 1 ? CHAINS - 1 : 1][C::MBLK][C::NBLK];       // ... of the further chains of a block
   auto chain = [&](int n, int i, int j) -> Acc& { return n == 0 ? acc[i][j] : more_acc[n - 1][i][j]; };
   if constexpr (CHAINS > 1) {
@@ -1246,8 +1253,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
       __builtin_amdgcn_s_waitcnt(0xC07F);
       __builtin_amdgcn_s_barrier();
     };
-    auto k_tile = [&](int kt, int cur, auto fetch_tag, auto more_tag) {
+    auto k_tile = [&](int kt, int cur, auto fetch_tag, auto more_tag, auto odd_tag) {
       constexpr bool fetch = decltype(fetch_tag)::value, more = decltype(more_tag)::value;
+      constexpr int first = CHAINS == 4 && decltype(odd_tag)::value ? 2 : 0;       // this tile's first chain
       const int nxt = cur + 1 == S ? 0 : cur + 1;
       // The requests of tile kt+S-1 go out over the first two k steps: in one burst at the top they fill the queue of the address
       // unit, and a wave that waits for room in it issues no MFMA (one 64x64 wave per SIMD: 2048^3 f16 22.4 -> 21.1 us, 512 x 512 x
@@ -1269,8 +1277,8 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
           ring_barrier();
           read_frags(nxt, 0, 0);
         }
-        if (ks + 1 < C::KSTEPS || more) mma(ks & 1, std::integral_constant<int, 1>{});
-        else mma(ks & 1, std::integral_constant<int, 0>{});
+        if (ks + 1 < C::KSTEPS || more) mma(ks & 1, std::integral_constant<int, 1>{}, first + ks);
+        else mma(ks & 1, std::integral_constant<int, 0>{}, first + ks);
         if (fetch && ks < 2) interleave_vmem(std::false_type{});
         else interleave();
       }
@@ -1287,9 +1295,15 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     ring_barrier();
     read_frags(0, 0, 0);
     int cur = 0, kt = 0;
-    for (; kt + S - 1 < nk; ++kt) cur = k_tile(kt, cur, std::true_type{}, std::true_type{});
-    for (; kt + 1 < nk; ++kt) cur = k_tile(kt, cur, std::false_type{}, std::true_type{});
-    k_tile(kt, cur, std::false_type{}, std::false_type{});
+    if constexpr (CHAINS == 4) {
+      for (; kt + S < nk; kt += 2) {
+        cur = k_tile(kt, cur, std::true_type{}, std::true_type{}, std::false_type{});
+        cur = k_tile(kt + 1, cur, std::true_type{}, std::true_type{}, std::true_type{});
+      }
+    }
+    for (; kt + S - 1 < nk; ++kt) cur = k_tile(kt, cur, std::true_type{}, std::true_type{}, std::false_type{});
+    for (; kt + 1 < nk; ++kt) cur = k_tile(kt, cur, std::false_type{}, std::true_type{}, std::true_type{});
+    k_tile(kt, cur, std::false_type{}, std::false_type{}, std::true_type{});
   } else if constexpr (C::RSETS == 2) {
     // Register-staged, two k tiles of loads in flight: tile kt+2 is requested at the top of tile kt into the register
     // set that tile kt left, and tile kt+1 (requested a whole k tile earlier) goes to LDS at the end of kt.  With one
@@ -1412,7 +1426,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
   }
 
   if constexpr (CHAINS > 1) {
-    static_assert(C::RSETS == 2, "the chains are told apart in the loop of two register sets");
+    static_assert(C::RSETS == 2 || (C::RING_16 && C::KSTEPS == 2), "the loops that tell the chains apart");
 #pragma unroll
     for (int half = CHAINS / 2; half >= 1; half /= 2)
 #pragma unroll

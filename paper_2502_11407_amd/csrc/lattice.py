@@ -43,8 +43,10 @@ def alternate(d):
 
 
 def chains(d):
-    """Sums that a lane keeps per output (the kernel's CHAINS)."""
+    """Sums that a lane keeps per output of a register-staged tile (the kernel's CHAINS or DEEP_CHAINS)."""
     es = 4 if d["dt"] == "f32" else 2
+    if not d["vec"] and es == 2 and d["out"] == "f32" and d["bsrc"] in ("KC", "NC") and (d["bm"], d["bn"]) == (64, 64):
+        return 4
     one = d["direct"] or d["units"] or d["bsrc"] not in ("KC", "NC") or d["mb"] != 16 or d["bk"] * es != 256 or d["wm"] * d["wn"] > 2 * 256
     return 1 if one else 8
 

@@ -48,7 +48,17 @@ hipError_t allow_dynamic_lds(K kernel, int bytes, std::atomic<uint64_t>& done) {
   return hipSuccess;
 }
 
-template <typename C, bool SPLIT = false, bool AHEAD = false>
+// Does a launch keep Cfg::DEEP_CHAINS sums per output?  They take 0.1-0.3 us to clear and to add up.  Rings: from 24 k tiles (whole tiles of fewer
+// never stood for parts; with four sums 1782 x 2048 x 512 took 7.4 us instead of 7.0, 1280 x 1408 x 1600 13.4 instead of 13.1).  Any-alignment
+// tiles: parts from seven, whole ones from sixteen (22 of 450 x 64 x 450 6.5 us instead of 6.2), as long as the three workgroups a compute unit
+// then holds, instead of four, are all there are (67 of 919 x 64 x 919, 1005 workgroups, 31.0 us instead of 29.3).
+template <typename C, bool SPLIT>
+bool more_sums(const KernelArgs& a, unsigned workgroups) {
+  const int depth = (a.K + C::BK - 1) / C::BK / (SPLIT && a.whole == 0 ? a.split : 1);
+  return C::DIRECT ? depth >= 24 : depth >= (SPLIT ? 7 : 16) && workgroups <= 3 * 256;
+}
+
+template <typename C, bool SPLIT = false, bool AHEAD = false, bool MORE_SUMS = false>
 hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
   if constexpr (C::HAS_AHEAD && !SPLIT && !AHEAD) {
     if (a.ahead_a + a.ahead_b > 0) return launch_instance<C, false, true>(a, st);
@@ -56,14 +66,17 @@ hipError_t launch_instance(const KernelArgs& a, hipStream_t st) {
   if constexpr (C::HAS_NARROW && !SPLIT) {
     if (a.narrow) return launch_instance<NarrowCfg<C>>(a, st);
   }
-  static std::atomic<uint64_t> done{0};
-  hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT, AHEAD>, C::LDS_BYTES, done);
-  if (e != hipSuccess) return e;
-  const int lds_bytes = C::ALTERNATE || a.lds_stages >= C::STAGES ? C::LDS_BYTES : C::STAGE_BYTES * a.lds_stages;
   // one workgroup per whole tile and, in a split launch, a.split per tile behind them
   const unsigned tiles = (unsigned)a.tiles_m * (unsigned)a.tiles_n * (unsigned)a.batch;
   const unsigned grid = SPLIT ? (unsigned)a.whole + (tiles - (unsigned)a.whole) * (unsigned)a.split : tiles;
-  hipLaunchKernelGGL((contraction_kernel<C, SPLIT, AHEAD>), dim3(grid), dim3(C::THREADS), lds_bytes, st, a);
+  if constexpr (C::DEEP_CHAINS != C::CHAINS && !MORE_SUMS) {
+    if (more_sums<C, SPLIT>(a, grid)) return launch_instance<C, SPLIT, AHEAD, true>(a, st);
+  }
+  static std::atomic<uint64_t> done{0};
+  hipError_t e = allow_dynamic_lds(contraction_kernel<C, SPLIT, AHEAD, MORE_SUMS>, C::LDS_BYTES, done);
+  if (e != hipSuccess) return e;
+  const int lds_bytes = C::ALTERNATE || a.lds_stages >= C::STAGES ? C::LDS_BYTES : C::STAGE_BYTES * a.lds_stages;
+  hipLaunchKernelGGL((contraction_kernel<C, SPLIT, AHEAD, MORE_SUMS>), dim3(grid), dim3(C::THREADS), lds_bytes, st, a);
   return hipGetLastError();
 }
 

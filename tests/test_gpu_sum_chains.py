@@ -16,10 +16,10 @@ def _small_tiles(gs, p):
     return found
 
 
-def _run(gs, p, s, A, B, M, N):
+def _run(gs, p, s, A, B, M, N, split=1):
     C = torch.full((M, N), float("nan"), device="cuda")
-    s.split_k = 1
-    gs.gemm(p, A, B, C, 1.0, 0.0, s)
+    s.split_k = split
+    gs.gemm(p, A, B, C, 1.0, 0.0, s, workspace=gs.gemm_workspace(p, s))
     torch.cuda.synchronize()
     return C
 
@@ -44,3 +44,50 @@ def test_last_tile_of_an_even_count_is_added_to_the_odd_tiles_sums(dtype, tiles,
         for s in _small_tiles(gs, p):
             print(dtype, tiles, tb, step, "instance", s.kernel_id, flush=True)
             assert (_run(gs, p, s, a, b, M, N) == 1.0).all(), (s.kernel_id, step)
+
+
+def _operands(dtype, M, N, K, ta, tb, terms):
+    """A and B of which only the products a * b at the given k are not zero."""
+    A, B = torch.zeros(M, K), torch.zeros(K, N)
+    for k, a, b in terms:
+        A[:, k], B[k, :] = a, b
+    return tuple(x.to(TORCH[dtype]).cuda() for x in (A.t().contiguous() if ta else A, B.t().contiguous() if tb else B))
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_deep_rings_of_16x16_blocks_keep_several_sums(dtype, ta, tb):
+    """2^24, then 1, then -2^24: the 1 survives where it is added to another sum.  Sums are told apart by the k step; in 128x128 tiles by the
+    parity of the k tile, too."""
+    from paper_2502_11407_amd import binding as gs
+    p = gs.gemm_problem(dtype, 64, 64, 64, ta, tb)
+    rings = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+             if s is not None and s.direct_lds and s.stages > 2 and s.tile[2][1] == 32]
+    assert len(rings) == (2 if ta or not tb else 3)
+    for s in rings:
+        M, N = s.tile[0][0] + 8, s.tile[1][0] + 16
+        for K, split in ((64 * 24, 1), (64 * 24 + 8, 1), (64 * 26 + 56, 1), (64 * 48, 2)):
+            q = gs.gemm_problem(dtype, M, N, K, ta, tb)
+            middles = [64 + 32 + 7] + ([64 + 7, 3 * 64 + 7] if s.stages == 4 else [])
+            for k in middles:
+                print(dtype, ta, tb, "instance", s.kernel_id, "K", K, "split", split, "k", k, flush=True)
+                a, b = _operands(dtype, M, N, K, ta, tb, ((5, 4096.0, 4096.0), (k, 1.0, 1.0), (4 * 64 + 9, 4096.0, -4096.0)))
+                assert (_run(gs, q, s, a, b, M, N, split) == 1.0).all(), (s.kernel_id, K, split, k)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_deep_any_alignment_tiles_keep_four_sums(dtype, ta, tb):
+    from paper_2502_11407_amd import binding as gs
+    p = gs.gemm_problem(dtype, 63, 63, 63, ta, tb)
+    tiles = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+             if s is not None and s.vec_bytes != 16 and (s.tile[0][0], s.tile[1][0], s.tile[2][0], s.tile[2][1]) == (64, 64, 64, 16)]
+    assert tiles
+    M, N = 67, 65
+    for s in tiles:
+        for K, split in ((64 * 15 + 1, 1), (64 * 16 + 63, 1), (64 * 13 + 5, 2), (64 * 14 + 1, 2)):
+            q = gs.gemm_problem(dtype, M, N, K, ta, tb)
+            for step in (1, 2, 3):
+                print(dtype, ta, tb, "instance", s.kernel_id, "K", K, "split", split, "step", step, flush=True)
+                a, b = _operands(dtype, M, N, K, ta, tb, ((5, 4096.0, 4096.0), (16 * step + 7, 1.0, 1.0), (4 * 64 + 9, 4096.0, -4096.0)))
+                assert (_run(gs, q, s, a, b, M, N, split) == 1.0).all(), (s.kernel_id, K, split, step)
