@@ -49,13 +49,13 @@ hipError_t allow_dynamic_lds(K kernel, int bytes, std::atomic<uint64_t>& done) {
 }
 
 // Does a launch keep Cfg::DEEP_CHAINS sums per output?  They take 0.1-0.3 us to clear and to add up.  Rings: from 24 k tiles (whole tiles of fewer
-// never stood for parts; with four sums 1782 x 2048 x 512 took 7.4 us instead of 7.0, 1280 x 1408 x 1600 13.4 instead of 13.1).  Any-alignment
-// tiles: parts from seven, whole ones from sixteen (22 of 450 x 64 x 450 6.5 us instead of 6.2), as long as the three workgroups a compute unit
+// never stood for parts; with four sums 1782 x 2048 x 512 took 7.4 us instead of 7.0, 1280 x 1408 x 1600 13.4 instead of 13.1), parts from
+// twelve with two sums (512 x 2048 x 4600 transA, six parts where there were eight) and from sixteen with four.  Any-alignment tiles: parts from seven, whole ones from sixteen (22 of 450 x 64 x 450 6.5 us instead of 6.2), as long as the three workgroups a compute unit
 // then holds, instead of four, are all there are (67 of 919 x 64 x 919, 1005 workgroups, 31.0 us instead of 29.3).
 template <typename C, bool SPLIT>
 bool more_sums(const KernelArgs& a, unsigned workgroups) {
   const int depth = (a.K + C::BK - 1) / C::BK / (SPLIT && a.whole == 0 ? a.split : 1);
-  return C::DIRECT ? depth >= 24 : depth >= (SPLIT ? 7 : 16) && workgroups <= 3 * 256;
+  return C::DIRECT ? depth >= (!SPLIT ? 24 : C::DEEP_CHAINS == 2 ? 12 : 16) : depth >= (SPLIT ? 7 : 16) && workgroups <= 3 * 256;
 }
 
 template <typename C, bool SPLIT = false, bool AHEAD = false, bool MORE_SUMS = false>
