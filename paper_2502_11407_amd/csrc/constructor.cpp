@@ -469,8 +469,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // (small register-staged tiles keep two k tiles of loads in flight, too: Cfg::RSETS; and whole tiles of 128x128 with an m-contiguous
   // A, without which the 64x64 ones were taken for 3-7 % more: 768 x 3072 x 1080 14.7 us against 13.9, 3328 x 832 x 2272 27.2 against 25.6)
   const bool small = bm * bn <= 128 * 64 || (v.asrc == A_MC && split == 1 && bm * bn <= 128 * 128);
-  // (off the vector boundaries: the tiles of up to 64x64, and parts, 333 x 777 x 5001 bf16 128x64 in six 17.5 us, 128x128 in twelve 19.9)
-  const bool two_sets = !direct && (vec || bm * bn <= 64 * 64 || split > 1) && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
+  // (off the vector boundaries, from six k tiles on: whole 128x64 tiles 951 x 1651 x 1031 f16 14.5 us, 64x64 15.8; 1433 x 975 x 1261 16.0 and
+  // 17.8; pointwise 18 x 384 x 21 x 21 -> 192 7.4 and 7.9; but 1543 x 659 x 297 7.0 and 6.5, 1087 x 1675 x 297 7.8 and 7.2)
+  const bool two_sets = !direct && (vec || bm * bn <= 64 * 64 || split > 1 || nk > 5) && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
   const double t_ktile = alternate ? 0.0 : (two_sets ? 0.15 : 0.3) * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;

@@ -167,3 +167,15 @@ def test_tall_products_of_few_tiles_stay_on_the_rings_of_three(dtype, out, M, N,
     p = gs.gemm_problem(dtype, M, N, K, 0, tb, 1, out)
     s = gs.construct(p)
     assert us_ring < us_narrow and s.split_k == 1 and s.stages == 3 and sorted((s.tile[0][0], s.tile[1][0])) == [128, 256]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,ta,tb,us_128x64,us_64x64", [
+    ("f16", 951, 1651, 1031, 0, 0, 14.45, 15.76), ("f16", 951, 1651, 1031, 0, 1, 14.18, 15.26), ("f16", 951, 1651, 1031, 1, 1, 14.92, 15.75),
+    ("bf16", 1433, 975, 1261, 0, 0, 16.04, 17.75), ("f16", 1909, 633, 567, 0, 1, 9.17, 9.70), ("f16", 1543, 659, 297, 0, 0, 7.02, 6.46),
+    ("f16", 1087, 1675, 297, 0, 0, 7.81, 7.19),
+])
+def test_whole_any_alignment_tiles_are_ranked_as_measured(dtype, M, N, K, ta, tb, us_128x64, us_64x64):
+    """Both have two k tiles of loads in flight (measured on inputs that change from call to call)."""
+    from paper_2502_11407_amd import binding as gs
+    s = gs.construct(gs.gemm_problem(dtype, M, N, K, ta, tb))
+    assert s.split_k == 1 and (s.tile[0][0], s.tile[1][0]) == ((128, 64) if us_128x64 < us_64x64 else (64, 64))
