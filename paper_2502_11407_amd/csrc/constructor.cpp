@@ -410,6 +410,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (regs > hw.regs_per_lane) return -1.0;
   int waves_per_simd = hw.regs_per_lane / regs;
   if (waves_per_simd > 8) waves_per_simd = 8;
+  // (eight sums per output, Cfg::CHAINS, and two register sets: 96-130 registers, 64x32 tiles 196-216)
+  const bool eight_sums = !direct && mb == 16 && bk * e == 256 && bm * bn <= 64 * 32 && wm * wn <= 2 * 16 * 16 && (v.bsrc == B_KC || v.bsrc == B_NC);
+  if (eight_sums) waves_per_simd = wm * wn > 16 * 16 ? 2 : 4;
   int occ = hw.lds_bytes_per_cu / lds;
   if ((hw.simds_per_cu * waves_per_simd) / nwaves < occ) occ = (hw.simds_per_cu * waves_per_simd) / nwaves;
   if (occ > 8) occ = 8;
@@ -492,7 +495,10 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double t_s2 = v.bsrc == B_NCS2 ? 2.0 * e * kp * bn / l2_bw : 0.0;
   // at equal area the taller tile is 1-3 % faster than the wider one on 10 of 13 measured pairs: priced as 1 %
   const double wide = bn > bm ? 1.01 : 1.0;
-  const double t_part = wide * (t_main * (nk_part / nk) / overlap + sync_time(nk_part) / share + (0.05 * t_lds + t_s2) * (nk_part / nk));     // one part of a split tile
+  // (small tiles of an n-contiguous B whose parts share a unit: 208 x 152 x 25536 bf16 in twelve 16.3 us, 64x64 tiles in sixteen 15.2, 160 x 248 x
+  // 29184 17.7 and 16.1)
+  const double shared_nc = eight_sums && v.bsrc == B_NC && cu_part > 1.0 ? 1.03 : 1.0;
+  const double t_part = wide * shared_nc * (t_main * (nk_part / nk) / overlap + sync_time(nk_part) / share + (0.05 * t_lds + t_s2) * (nk_part / nk));     // one part of a split tile
   t_main = wide * (t_main / overlap + sync_time(nk) / share + 0.05 * t_lds + t_s2);
   const double hbm_bw_cu = hw.bandwidth_gbs[0] * 1e3 / hw.compute_units;
   const double t_epi = bm * bn * eo / (1.2 * hbm_bw_cu);      // write-through stores

@@ -179,3 +179,23 @@ def test_whole_any_alignment_tiles_are_ranked_as_measured(dtype, M, N, K, ta, tb
     from paper_2502_11407_amd import binding as gs
     s = gs.construct(gs.gemm_problem(dtype, M, N, K, ta, tb))
     assert s.split_k == 1 and (s.tile[0][0], s.tile[1][0]) == ((128, 64) if us_128x64 < us_64x64 else (64, 64))
+
+
+@pytest.mark.parametrize("M,N,K,ta,tb,us_64x64,us_64x32", [
+    (1337, 809, 161, 0, 0, 11.2, 12.6), (901, 1565, 167, 0, 0, 11.6, 13.4), (979, 1473, 103, 1, 0, 8.9, 10.7), (757, 1859, 349, 1, 0, 17.8, 19.9),
+    (1819, 719, 305, 0, 0, 16.1, 17.5), (899, 987, 502, 0, 0, 16.6, 15.7), (1705, 269, 499, 0, 0, 15.6, 11.0), (952, 534, 712, 0, 0, 18.8, 14.4),
+])
+def test_small_fp32_tiles_of_eight_sums_are_ranked_as_measured(M, N, K, ta, tb, us_64x64, us_64x32):
+    """Any-alignment 64x32 tiles need about 200 registers: two workgroups a compute unit, so a third tile runs alone."""
+    from paper_2502_11407_amd import binding as gs
+    s = gs.construct(gs.gemm_problem("f32", M, N, K, ta, tb))
+    assert (s.tile[0][0], s.tile[1][0]) == ((64, 64) if us_64x64 < us_64x32 else (64, 32))
+
+
+def test_parts_of_small_tiles_that_share_a_unit_are_ranked_as_measured():
+    """208 x 152 x 25536 bf16 with a row-major B: 64x64 tiles in sixteen parts 15.2 us, 32x32 ones in twelve (420 parts) 16.3; 128 x 104 x 15680 11.2 and
+    9.2 (256 parts)."""
+    from paper_2502_11407_amd import binding as gs
+    for (M, N, K), tile in (((208, 152, 25536), 64), ((128, 104, 15680), 32)):
+        s = gs.construct(gs.gemm_problem("bf16", M, N, K))
+        assert (s.tile[0][0], s.tile[1][0]) == (tile, tile) and s.split_k == 16
