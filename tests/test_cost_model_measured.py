@@ -199,3 +199,18 @@ def test_parts_of_small_tiles_that_share_a_unit_are_ranked_as_measured():
     for (M, N, K), tile in (((208, 152, 25536), 64), ((128, 104, 15680), 32)):
         s = gs.construct(gs.gemm_problem("bf16", M, N, K))
         assert (s.tile[0][0], s.tile[1][0]) == (tile, tile) and s.split_k == 16
+
+
+@pytest.mark.parametrize("dtype,n,c,h,w,k,r,stride,us", [
+    ("bf16", 14, 6, 35, 63, 28, 7, 1, {(32, 256): 8.13, (32, 128): 9.01}), ("f16", 2, 6, 92, 61, 52, 7, 1, {(32, 256): 7.85, (32, 128): 8.70}),
+    ("f16", 3, 6, 42, 45, 22, 5, 2, {(32, 256): 5.62, (32, 128): 6.04}), ("f16", 15, 6, 64, 47, 56, 7, 2, {(32, 256): 7.32, (32, 128): 8.30}),
+])
+def test_row_staged_tiles_of_four_and_eight_waves_are_ranked_as_measured(dtype, n, c, h, w, k, r, stride, us):
+    from paper_2502_11407_amd import binding as gs
+    p = gs.conv_problem(dtype, n, c, h, w, k, r, r, stride, r // 2)
+    price = {}
+    for i in range(gs.num_instances()):
+        s = gs.instance_schedule(i, p)
+        if s is not None and s.direct_lds and s.vec_bytes != 16 and (s.tile[0][0], s.tile[1][0]) in us:
+            price[s.tile[0][0], s.tile[1][0]] = gs.predict_us(s, p)
+    assert len(price) == 2 and min(price, key=price.get) == min(us, key=us.get)
