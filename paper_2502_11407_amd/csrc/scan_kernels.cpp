@@ -131,18 +131,21 @@ __global__ __launch_bounds__(256) void gemv_kernel(const char* A, int64_t lda, c
 // (whole planes, or the rows under a run of output rows of one plane).  It is brought into
 // LDS with aligned 16-byte vector loads (2-byte loads per window element would make the load
 // pipeline, not HBM, the limit), and the windows are then read from LDS.
-// Bound by HBM.  fp32 outputs are stored non-temporal, so that they take no room from the input that neighbours share lines of
-// (16 x 48 x 299 x 299 fp32 70.8 -> 65.2 us, 32 x 168 x 83 x 83 fp16 21.6 -> 21.1, 4 x 16 x 300 x 300 36.6 -> 35.2; 5 MB and
-// less: level).  Whole planes are read non-temporal, too, where the input alone is more than the last cache keeps (STREAM):
-// 128 x 168 x 83 x 83 fp16 83.5 -> 81.2 us (441 MB: 5.4 TB/s), fp32 135 -> 117.  Smaller inputs may still be there from the step
-// that wrote them (32 x 168 x 83 x 83 fp16 21.1 -> 22.9 with the hint), and runs of rows read the rows between two of them twice.
+// Bound by HBM.  Whole planes are read, and fp32 outputs stored, non-temporal where the input alone is more than the last cache keeps
+// (STREAM): 128 x 168 x 83 x 83 fp16 83.5 -> 80.7 us (441 MB: 5.5 TB/s), fp32 135 -> 117.  Smaller inputs may still be there from the
+// step that wrote them (32 x 168 x 83 x 83 fp16 21.1 -> 22.9 with the hint), and runs of rows read the rows between two of them twice.
+// fp32 outputs that the L2s hold are stored non-temporal, too (THROUGH): they take no room from the input that neighbours share lines of, and the
+// step that reads them finds no dirty lines in front of it (pooling alone, and with a reader behind it: 16 x 96 x 83 x 83 fp16, 10 MB, 9.7 -> 8.9,
+// 16.4 -> 14.0; 32 x 64 x 112 x 112 fp16, 26 MB, 19.2 -> 17.7, 27.8 level; 16 x 64 x 112 x 112 fp32, 13 MB, 15.7 -> 14.8, 21.0 -> 20.6).  Beyond,
+// pooling alone gains less than its reader loses (64 x 168 x 83 x 83 fp16, 72 MB, 38.3 level, 60.7 -> 63.9; 16 x 48 x 299 x 299 fp32, 68 MB,
+// 65.5 -> 63.5, 85.0 -> 92.5; 16 x 168 x 83 x 83 fp32, 18 MB, 17.9 -> 17.8, 24.9 -> 25.8).
 // avgpool_direct_kernel: one thread per output straight from global memory, for inputs that
 // are not 16-byte aligned or whose rows do not fit the LDS span.
 // ---------------------------------------------------------------------------------------
 constexpr int POOL_SPAN_BYTES = 32768;
 constexpr int POOL_VECS = (POOL_SPAN_BYTES + 16 + 15) / 16 / 256 + 1;     // 16-byte vectors per thread covering span + skew
 
-template <typename T, typename OutT, bool STREAM>
+template <typename T, typename OutT, bool STREAM, bool THROUGH>
 __global__ __launch_bounds__(256) void avgpool_lds_kernel(const char* in, void* out, int64_t in_bytes, int planes, int H, int W, int P,
                                                           int Q, int F, int S, int planes_per_wg, int rows_per_wg, int chunks_per_plane) {
   constexpr int ES = ElemSize<T>::value;
@@ -204,7 +207,7 @@ __global__ __launch_bounds__(256) void avgpool_lds_kernel(const char* in, void* 
     for (int i = 0; i < F; ++i)
       for (int j = 0; j < F; ++j) acc += to_float<T>(span + skew, base + i * W + j);
     const int64_t o = ((int64_t)(plane0 + g) * P + p0 + pr) * Q + q;
-    if constexpr (ElemSize<OutT>::value == 4) __builtin_nontemporal_store(acc / count, (float*)out + o);
+    if constexpr (THROUGH) __builtin_nontemporal_store(acc / count, (float*)out + o);
     else store_out<OutT>(out, o, acc / count);
     q += dq;
     pr += dp;
@@ -271,7 +274,11 @@ hipError_t launch_pool(const void* in, void* out, int64_t planes, int64_t h, int
   if (G && groups <= INT32_MAX && planes <= INT32_MAX) {
     const int64_t span_elems = cpp == 1 ? G * h * w : ((R - 1) * s + f) * w;
     const size_t lds_bytes = (size_t)((span_elems * ES + 15 + 15) / 16 * 16 + 16);      // span + skew, whole vectors
-    const auto kernel = cpp == 1 && planes * plane_bytes > 256ll * 1024 * 1024 ? avgpool_lds_kernel<T, OutT, true> : avgpool_lds_kernel<T, OutT, false>;
+    constexpr bool FP32_OUT = ElemSize<OutT>::value == 4;
+    const bool stream = cpp == 1 && planes * plane_bytes > 256ll * 1024 * 1024;
+    const bool through = planes * P * Q * 4 <= (ES == 2 ? 32ll : 16ll) * 1024 * 1024;
+    const auto kernel = stream ? avgpool_lds_kernel<T, OutT, true, FP32_OUT>
+                               : through ? avgpool_lds_kernel<T, OutT, false, FP32_OUT> : avgpool_lds_kernel<T, OutT, false, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(256), lds_bytes, st, (const char*)in, out, planes * plane_bytes, (int)planes,
                        (int)h, (int)w, (int)P, (int)Q, (int)f, (int)s, (int)G, (int)R, (int)cpp);
   } else {

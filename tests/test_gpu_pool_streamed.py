@@ -1,4 +1,5 @@
-"""AvgPooling of inputs of more than 256 MiB, whose whole planes are read past the caches, beside the same planes pooled a few at a time."""
+"""AvgPooling on both sides of the sizes from which inputs are read, and up to which fp32 outputs are stored, past the caches, beside the same planes
+pooled a few at a time."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -7,7 +8,9 @@ pytestmark = pytest.mark.gpu
 # planes on both sides of the size, the last of them ending inside a 16-byte vector, a workgroup's share not dividing them
 @pytest.mark.parametrize("dtype,out,planes,h,w,f,stride", [
     ("f16", "f32", 19501, 83, 83, 2, 2), ("f16", "f32", 19481, 83, 83, 2, 2), ("bf16", "bf16", 149331, 29, 31, 3, 2), ("f32", "f32", 152203, 21, 21, 3, 1),
-    ("f16", "f16", 12001, 106, 107, 2, 2)])
+    ("f16", "f16", 12001, 106, 107, 2, 2),
+    # outputs of 1 KiB a plane: 32 MiB (16-bit input) and 16 MiB (fp32), and a plane more
+    ("f16", "f32", 32768, 33, 33, 2, 2), ("bf16", "f32", 32769, 33, 33, 2, 2), ("f32", "f32", 16384, 33, 33, 2, 2), ("f32", "f32", 16385, 33, 33, 2, 2)])
 def test_large_pools_equal_pools_of_their_planes(dtype, out, planes, h, w, f, stride):
     import torch
     from paper_2502_11407_amd import binding as gs
