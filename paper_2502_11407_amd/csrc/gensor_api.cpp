@@ -443,10 +443,17 @@ gensor_status run(const gensor_schedule* s, const gensor_problem* p, const GemmV
   // A launch of fewer k tiles than its instance has LDS stages touches that many stages only; allocating no more lets another workgroup
   // onto each compute unit, whose loads run under the others' stores.  fp32 output, us: 48 x 1024 x 1024 x 64 48.3 -> 40.6, 96 x 512 x 512
   // x 64 27.1 -> 24.3, 64 x 384 x 384 x 64 9.3 -> 8.3, 50 x 1000 x 1000 x 64 52.0 -> 46.2; 16-bit 64 x 384 x 384 x 64 7.3 -> 6.4, 50 x 1000 x 1000
-  // x 64 41.1 -> 37.0.  Large outputs that are written through lose to more of them storing at once: 8192 x 8192 x 64 fp32 45.4 ->
-  // 48.0, 96 x 1024 x 1024 x 64 with the next batch read ahead 74.9 -> 77.0; 16-bit 48 x 1024 x 1024 x 64 (100 MB) 33.1 -> 36.1, 69 x 768 x
-  // 768 x 64 (81 MB) 31.3 -> 31.9, but 40 x 768 x 768 x 64 (47 MB) 13.3 -> 12.5.
-  const bool resident = !a.through || (a.ahead_a + a.ahead_b == 0 && c_bytes <= (v.osize == 2 ? 64ll : 224ll) * 1024 * 1024);
+  // x 64 41.1 -> 37.0.  Larger outputs lose to more of them storing at once.  Written through: fp32 8192 x 8192 x 64 45.4 -> 48.0, 7680 x 8192 x 64
+  // 41.3 -> 44.5 (up to 210 MB a step that reads the output gains what the product loses, 50 x 1024 x 1024 x 64 34.4 -> 36.5, with a reader
+  // 119.6 -> 114.9); 16-bit 48 x 1024 x 1024 x 64 (100 MB) with a reader 59.6 -> 66.0, 40 of them 50.1 -> 55.4, but 34 (71 MB) 41.3 -> 37.4.
+  // Written back: fp32 8192 x 8200 x 64 (269 MB) 60.1 -> 63.7, 16384 x 5000 x 64 71.6 -> 77.5, but 60 x 1000 x 1000 x 64 63.7 -> 55.2; 16-bit at
+  // every size (16384 x 8200 x 64 70.7 -> 67.3, 200 x 1000 x 1000 x 64 166 -> 132).  Where the next batch is read ahead, the stages it
+  // does without are no gain, and with written back outputs a loss: 96 x 1024 x 1024 x 64 62.4 and 62.8, 64 x 1024 x 1152 x 64 49.0 and 54.2,
+  // 96 x 1000 x 1000 x 64 85.4 and 102.9, 70 x 1020 x 1020 x 64 71.9 and 84.4.
+  const bool ahead_form = d->vec && d->direct && d->stages == 2 && v.esize == 2 && v.osize == 4 && d->bm == 128 && d->bn == 128 && d->threads == 512;      // Cfg::HAS_AHEAD
+  const bool ahead = ahead_form && a.ahead_a + a.ahead_b > 0;
+  const int64_t most = v.osize == 2 ? (a.through ? 64ll * 1024 * 1024 : INT64_MAX) : (a.through ? 224ll : 256ll) * 1024 * 1024;
+  const bool resident = !ahead && c_bytes <= most;
   const int64_t k_tiles = (v.K + d->bk - 1) / d->bk;
   a.lds_stages = resident && k_tiles < d->stages ? (int32_t)k_tiles : d->stages;
   a.partials = (float*)workspace;

@@ -11,17 +11,17 @@ CSRC = os.path.join(ROOT, "paper_2502_11407_amd", "csrc")
 RECORDER = """
 #include "registry.hpp"
 namespace gensor {
-static int32_t last[10];
+static int32_t last[11];
 static hipError_t record(int id, int split, const KernelArgs& a) {
-  const int32_t v[10] = {last[0] + 1, id, split, a.narrow, a.tiles_m, a.tiles_n, a.batch, a.whole, a.split, a.paired};
-  for (int i = 0; i < 10; ++i) last[i] = v[i];
+  const int32_t v[11] = {last[0] + 1, id, split, a.narrow, a.tiles_m, a.tiles_n, a.batch, a.whole, a.split, a.paired, a.lds_stages};
+  for (int i = 0; i < 11; ++i) last[i] = v[i];
   return hipErrorNotSupported;
 }
 %s
 }
 extern "C" const int32_t* last_launch(void) { return gensor::last; }
 """
-FIELDS = ("count", "id", "split_launch", "narrow", "tiles_m", "tiles_n", "batch", "whole", "split", "paired")
+FIELDS = ("count", "id", "split_launch", "narrow", "tiles_m", "tiles_n", "batch", "whole", "split", "paired", "lds_stages")
 ACCEPTED = 5          # GENSOR_ERR_DEVICE: what the recorder's error becomes, once everything before the launch has passed
 A, B, OUT, WORKSPACE = (1 << 40) * 1, (1 << 40) * 2, (1 << 40) * 3, (1 << 40) * 4
 

@@ -167,3 +167,21 @@ def test_width_of_alternating_tiles(stub, M, N, batch, units, columns):
     assert need == rows * -(-N // 256) * batch * 2 * 256 * 256 * 4
     st, launch = stub.call(p, s, room=need)
     assert st == ACCEPTED and launch["split_launch"] and not launch["narrow"] and launch["tiles_n"] == -(-N // 256)
+
+
+@pytest.mark.parametrize("dtype,out,batch,M,N,K,stages", [
+    ("f16", "f32", 96, 1000, 1000, 64, 2),         # the next batch is read ahead, rows of C are not whole lines
+    ("bf16", "f32", 72, 1024, 1024, 64, 2),        # ... and where they are
+    ("f16", "f32", 60, 1000, 1000, 64, 1),         # 240 MB, not read ahead
+    ("f16", "f32", 1, 8192, 8200, 64, 2),          # 269 MB
+    ("f16", "f32", 48, 1024, 1024, 64, 1), ("f16", "f32", 1, 8192, 8192, 64, 2),         # 201 MB, 268 MB written through
+    ("bf16", "bf16", 200, 1000, 1000, 64, 1),      # 16-bit outputs are not read ahead for: 400 MB written back
+    ("f16", "f16", 30, 1024, 1024, 64, 1), ("f16", "f16", 40, 1024, 1024, 64, 2),        # 63 MB, 84 MB written through
+])
+def test_stages_allocated_for_products_of_one_k_tile(stub, dtype, out, batch, M, N, K, stages):
+    """Of the two stages of a directly staged tile a product of one k tile touches one; large outputs keep both allocated."""
+    p = stub.gs.gemm_problem(dtype, M, N, K, 0, 1, batch, out)
+    tile = [s for s in (stub.gs.instance_schedule(i, p) for i in range(stub.gs.num_instances())) if s is not None and s.direct_lds and s.stages == 2
+            and (s.tile[0][0], s.tile[1][0], s.tile[2][0], s.tile[0][1], s.tile[1][1]) == (128, 128, 64, 64, 32)]
+    st, launch = stub.call(p, tile[0])
+    assert st == ACCEPTED and launch["lds_stages"] == stages
