@@ -338,13 +338,9 @@ __global__ __launch_bounds__(C::THREADS) void conv_patch_kernel(const KernelArgs
           for (int i = 0; i < EPC; ++i) {
             const uint32_t off = first + (uint32_t)(i * HW * ES);
             for (uint32_t at = last_vec; at < off; at += ES) {                                 // one element at a time towards the front
-              if constexpr (ES == 4) {
-                u_reg[u][i] = u32x4{u_reg[u][i][1], u_reg[u][i][2], u_reg[u][i][3], 0u};
-              } else {
-                const u32x4 v = u_reg[u][i];
-                u_reg[u][i] = u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], 2u), __builtin_amdgcn_alignbyte(v[2], v[1], 2u),
-                                    __builtin_amdgcn_alignbyte(v[3], v[2], 2u), v[3] >> 16};
-              }
+              const u32x4 v = u_reg[u][i];
+              u_reg[u][i] = u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], 2u), __builtin_amdgcn_alignbyte(v[2], v[1], 2u),
+                                  __builtin_amdgcn_alignbyte(v[3], v[2], 2u), v[3] >> 16};
             }
           }
         }

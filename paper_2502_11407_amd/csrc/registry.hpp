@@ -111,8 +111,10 @@ hipError_t launch_conv_tail(const KernelArgs& a, hipStream_t st, int raw_bytes) 
 // the buffer's range check returns its valid part).
 template <typename C, int FMODE, bool THROUGH>
 hipError_t launch_conv_route(const KernelArgs& a, hipStream_t st, int raw_bytes) {
-  return ((a.cW * C::ES) & 3) != 0 ? launch_conv_tail<C, FMODE, THROUGH, true>(a, st, raw_bytes)
-                                   : launch_conv_tail<C, FMODE, THROUGH, false>(a, st, raw_bytes);
+  if constexpr (C::ES == 2) {
+    if (a.cW & 1) return launch_conv_tail<C, FMODE, THROUGH, true>(a, st, raw_bytes);
+  }
+  return launch_conv_tail<C, FMODE, THROUGH, false>(a, st, raw_bytes);
 }
 
 // The output is stored write-through when the reduction is shallow (the stores are then a large share of
