@@ -120,3 +120,25 @@ def test_batches_that_read_the_next_one_ahead(gs, ta, tb, K, shared):
         for b in range(batch):
             a, w = (A[b].T if ta else A[b]).float().contiguous(), (B[b].T if tb else B[b]).float().contiguous()
             assert torch.equal(C[b], a @ w), b
+
+
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+@pytest.mark.parametrize("ta,tb,K", [(0, 1, 64), (0, 0, 64), (1, 0, 64), (1, 1, 128)])
+def test_batches_that_read_the_next_one_ahead_and_store_whole_lines(gs, ta, tb, K, beta):
+    """The same with rows of C that are whole lines, which are stored non-temporal, or beside C as they are without the read-ahead."""
+    import torch
+    batch, M, N = 72, 1000, 1024
+    A, B = (_ints(gs, (batch,) + x, "f16", K + i, -3, 3) for i, x in enumerate(((K, M) if ta else (M, K), (N, K) if tb else (K, N))))
+    p = gs.gemm_problem("f16", M, N, K, ta, tb, batch)
+    scheds = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+              if s is not None and (s.tile[0][0], s.tile[1][0]) == (128, 128) and s.tile[0][1] * s.tile[1][1] == 64 * 32 and s.direct_lds and s.stages == 2]
+    assert scheds
+    before = _ints(gs, (batch, M, N), "f32", 9, -5, 5)
+    C = gs.empty_device((batch, M, N))
+    for s in scheds:
+        print("read-ahead instance", s.kernel_id, ta, tb, K, beta, flush=True)
+        C.copy_(before) if beta else C.fill_(float("nan"))
+        gs.bmm(p, A, B, C, 1.0, beta, s)
+        for b in range(batch):
+            a, w = (A[b].T if ta else A[b]).float().contiguous(), (B[b].T if tb else B[b]).float().contiguous()
+            assert torch.equal(C[b], a @ w + before[b] if beta else a @ w), b

@@ -49,3 +49,27 @@ def test_rings_of_16x16_blocks_at_any_k(gs, dtype, out, ta, tb):
                 gs.gemm(q, A, B, C, 2.0, 1.0, t, workspace=ws)
                 torch.cuda.synchronize()
                 assert torch.equal(C, (2.0 * want + want.to(C.dtype).float()).to(C.dtype)), (s.kernel_id, K, split)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_rings_of_16x16_blocks_at_odd_k(gs, dtype):
+    """An m-contiguous A beside a row-major B leaves K free of the vector width: below, at and beyond one k tile, whole and in parts."""
+    import torch
+    p = gs.gemm_problem(dtype, 64, 64, 64, 1, 0)
+    rings = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+             if s is not None and s.direct_lds and s.stages > 2 and s.tile[2][1] == 32]
+    assert len(rings) == 2
+    for s in rings:
+        M, N = s.tile[0][0] + 40, s.tile[1][0] + 24
+        for K, splits in ((1, (1,)), (7, (1,)), (33, (1,)), (63, (1,)), (65, (1, 2)), (127, (1, 2)), (193, (1, 2, 3)), (257, (1, 4)), (451, (1, 3)), (1601, (1, 2))):
+            A, B = _embedded(gs, K, M, dtype, K), _embedded(gs, K, N, dtype, K + 1)
+            want = A.T.float().contiguous() @ B.float().contiguous()
+            q = gs.gemm_problem(dtype, M, N, K, 1, 0)
+            for split in splits:
+                t = gs.Schedule.from_buffer_copy(s)
+                t.split_k = split
+                print("instance", s.kernel_id, dtype, "K", K, "split", split, flush=True)
+                C = gs.empty_device((M, N)).fill_(float("nan"))
+                gs.gemm(q, A, B, C, 1.0, 0.0, t, workspace=gs.gemm_workspace(q, t))
+                torch.cuda.synchronize()
+                assert torch.equal(C, want), (s.kernel_id, K, split)
