@@ -258,7 +258,10 @@ def lattice():
             out.append(_inst(dt, odt, 128, 128, 64, 64, 64, 32, stages=4, direct=1))
     # the rings of 16x16 blocks (the kernel's RING_16).  128x128 tiles only where neither operand is transposed while it is read, of which
     # 16x16 blocks need more: m-contiguous A 2048^3 22.9 against 23.9 us, 1536 x 2304 x 3072 29.1 against 30.9; n-contiguous B within 5 %
-    # either way (1600 x 1216 x 3776 32.0 against 33.6, 1280 x 1664 x 1664 16.7 against 17.5, 2048^3 23.8 against 22.7).
+    # either way (1600 x 1216 x 3776 32.0 against 33.6, 1280 x 1664 x 1664 16.7 against 17.5, 2048^3 23.8 against 22.7).  128x256 tiles are taken by a
+    # tenth as many of 4800 drawn products as 256x128 ones, three quarters of them weight gradients of 576 to 960 rows (576 x 2304 x 6192 transA
+    # 36.9 -> 34.0, 896 x 3584 x 4720 51.8 -> 47.0), the others where they leave fewer partial tiles (2688 x 3072 x 1088 25.0 -> 23.1,
+    # 2049 x 3840 x 960 with 16-bit output 21.5 -> 20.8; pointwise 6 x 304 x 52 x 52 -> 336 10.1 -> 9.3).
     for dt in ("f16", "bf16"):
         for bsrc, asrc in product(("KC", "NC"), ("KC", "MC")):
             for odt in ("f32", dt):
