@@ -411,9 +411,11 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   if (regs > hw.regs_per_lane) return -1.0;
   int waves_per_simd = hw.regs_per_lane / regs;
   if (waves_per_simd > 8) waves_per_simd = 8;
-  // (eight sums per output, Cfg::CHAINS, and two register sets: 96-130 registers, 64x32 tiles 196-216)
-  const bool eight_sums = !direct && mb == 16 && bk * e == 256 && bm * bn <= 64 * 32 && wm * wn <= 2 * 16 * 16 && (v.bsrc == B_KC || v.bsrc == B_NC);
-  if (eight_sums) waves_per_simd = wm * wn > 16 * 16 ? 2 : 4;
+  // (64x32 tiles of eight sums, Cfg::CHAINS: 196-216 registers leave two workgroups a unit, so the third of three waits.  1337 x 809 x 161 12.6 us, 64x64
+  // tiles 11.2; 757 x 1859 x 349 transA 20.2 and 18.5; from K = 400 on level, 1147 x 1167 x 507 23.6 and 23.2, 1457 x 1011 x 617 28.3 and
+  // 29.2.  Both operands k-contiguous: against 64x64x16 tiles, which are level, 1027 x 1551 x 183 14.8 and 14.8)
+  const bool eight_sums = !direct && mb == 16 && bk * e == 256 && bm * bn == 64 * 32 && wm * wn == 32 * 16 && (v.bsrc == B_NC || (v.bsrc == B_KC && v.asrc == A_MC));
+  if (eight_sums && split == 1 && v.K <= 6 * bk) waves_per_simd = 2;
   int occ = hw.lds_bytes_per_cu / lds;
   if ((hw.simds_per_cu * waves_per_simd) / nwaves < occ) occ = (hw.simds_per_cu * waves_per_simd) / nwaves;
   if (occ > 8) occ = 8;
@@ -474,8 +476,9 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   // A, without which the 64x64 ones were taken for 3-7 % more: 768 x 3072 x 1080 14.7 us against 13.9, 3328 x 832 x 2272 27.2 against 25.6)
   const bool small = bm * bn <= 128 * 64 || (v.asrc == A_MC && split == 1 && bm * bn <= 128 * 128);
   // (off the vector boundaries, from six k tiles on: whole 128x64 tiles 951 x 1651 x 1031 f16 14.5 us, 64x64 15.8; 1433 x 975 x 1261 16.0 and
-  // 17.8; pointwise 18 x 384 x 21 x 21 -> 192 7.4 and 7.9; but 1543 x 659 x 297 7.0 and 6.5, 1087 x 1675 x 297 7.8 and 7.2)
-  const bool two_sets = !direct && (vec || bm * bn <= 64 * 64 || split > 1 || nk > 5) && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
+  // 17.8; pointwise 18 x 384 x 21 x 21 -> 192 7.4 and 7.9; but 1543 x 659 x 297 7.0 and 6.5, 1087 x 1675 x 297 7.8 and 7.2; and more than one column
+  // of them, 83 of 775 x 64 x 775 28.4 and 24.9, 78 of 342 x 64 x 342 7.6 and 6.9)
+  const bool two_sets = !direct && (vec || bm * bn <= 64 * 64 || split > 1 || (nk > 5 && v.N > bn)) && stages == 2 && (v.bsrc == B_KC || v.bsrc == B_NC) && e == 2 && small && (bk / kg) % 2 == 0;
   const double t_ktile = alternate ? 0.0 : (two_sets ? 0.15 : 0.3) * hw.latency_ns[0] * 1e-3;
   auto sync_time = [&](double tiles_k) {
     double t = tiles_k * t_ktile;
@@ -496,10 +499,7 @@ double predict(const GemmView& v, const gensor_hw& hw, int bm, int bn, int bk, i
   const double t_s2 = v.bsrc == B_NCS2 ? 2.0 * e * kp * bn / l2_bw : 0.0;
   // at equal area the taller tile is 1-3 % faster than the wider one on 10 of 13 measured pairs: priced as 1 %
   const double wide = bn > bm ? 1.01 : 1.0;
-  // (small tiles of an n-contiguous B whose parts share a unit: 208 x 152 x 25536 bf16 in twelve 16.3 us, 64x64 tiles in sixteen 15.2, 160 x 248 x
-  // 29184 17.7 and 16.1)
-  const double shared_nc = eight_sums && v.bsrc == B_NC && cu_part > 1.0 ? 1.03 : 1.0;
-  const double t_part = wide * shared_nc * (t_main * (nk_part / nk) / overlap + sync_time(nk_part) / share + (0.05 * t_lds + t_s2) * (nk_part / nk));     // one part of a split tile
+  const double t_part = wide * (t_main * (nk_part / nk) / overlap + sync_time(nk_part) / share + (0.05 * t_lds + t_s2) * (nk_part / nk));     // one part of a split tile
   t_main = wide * (t_main / overlap + sync_time(nk) / share + 0.05 * t_lds + t_s2);
   const double hbm_bw_cu = hw.bandwidth_gbs[0] * 1e3 / hw.compute_units;
   const double t_epi = bm * bn * eo / (1.2 * hbm_bw_cu);      // write-through stores

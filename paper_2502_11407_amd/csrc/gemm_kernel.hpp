@@ -252,8 +252,8 @@ struct Cfg {
   // f16 any-alignment, four parts 1.37e-7, one tile 2.59e-7 (four sums 1.36e-7); 3072 x 768 x 7352 f16 transA 2.28e-7, 3.16e-7 (two 2.27e-7);
   // 1792 x 1152 x 2176 bf16 2.60e-7 (four 1.23e-7).  For it 64x32 waves of the rings have registers for four, 64x64 ones for two, and the
   // any-alignment tile needs 150-160 instead of 96-104.
-  static constexpr bool LOOSE_64 = !DIRECT_ && !VEC_ && ES == 2 && BM_ == 64 && BN_ == 64 && BK_ == 64 && RSETS == 2;
-  static constexpr int DEEP_CHAINS = ElemSize<OutT_>::value != 4 ? CHAINS : RING_16 ? (BM_ * BN_ == 128 * 128 ? 4 : 2) : LOOSE_64 ? 4 : CHAINS;
+  static constexpr bool LOOSE_64 = !DIRECT_ && !VEC_ && BN_ == 64 && RSETS == 2 && (ES == 2 ? (BM_ == 64 || BM_ == 128) && BK_ == 64 : BM_ == 64 && BK_ == 32);
+  static constexpr int DEEP_CHAINS = ElemSize<OutT_>::value != 4 ? CHAINS : RING_16 ? (BM_ * BN_ == 128 * 128 ? 4 : 2) : LOOSE_64 ? (ES == 4 ? 8 : BM_ == 64 ? 4 : 2) : CHAINS;
   // the tile that store-bound batches of a shallow k end in also exists with the next batch read ahead
   static constexpr bool HAS_AHEAD = VEC_ && DIRECT_ && STAGES_ == 2 && ES == 2 && ElemSize<OutT_>::value == 4 && BM_ == 128 && BN_ == 128 && WAVES == 8;
   static_assert(BM % WM == 0 && BN % WN == 0, "wave tile must divide workgroup tile");
@@ -885,7 +885,7 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     for (int bi = 0; bi < C::MBLK; ++bi)
 #pragma unroll
       for (int bj = 0; bj < C::NBLK; ++bj) {
-        if constexpr (CHAINS > 1 && ES == 4) {
+        if constexpr (CHAINS > 1 && ES == 4 && MB == 16) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) MF::step(fa[buf][bi], fb[buf][bj], t, chain((4 * at + t) % CHAINS, bi, bj));
         } else {

@@ -45,8 +45,9 @@ def alternate(d):
 def chains(d):
     """Sums that a lane keeps per output of a register-staged tile (the kernel's CHAINS or DEEP_CHAINS)."""
     es = 4 if d["dt"] == "f32" else 2
-    if not d["vec"] and es == 2 and d["out"] == "f32" and d["bsrc"] in ("KC", "NC") and (d["bm"], d["bn"]) == (64, 64):
-        return 4
+    loose = not d["vec"] and d["out"] == "f32" and d["bsrc"] in ("KC", "NC") and d["mb"] == 32 and d["bn"] == 64
+    if loose and (d["bk"] == 64 and d["bm"] in (64, 128) if es == 2 else d["bk"] == 32 and d["bm"] == 64):
+        return 8 if es == 4 else 4 if d["bm"] == 64 else 2
     one = d["direct"] or d["units"] or d["bsrc"] not in ("KC", "NC") or d["mb"] != 16 or d["bk"] * es != 256 or d["wm"] * d["wn"] > 2 * 256
     return 1 if one else 8
 

@@ -48,14 +48,21 @@ hipError_t allow_dynamic_lds(K kernel, int bytes, std::atomic<uint64_t>& done) {
   return hipSuccess;
 }
 
-// Does a launch keep Cfg::DEEP_CHAINS sums per output?  They take 0.1-0.3 us to clear and to add up.  Rings: from 24 k tiles (whole tiles of fewer
-// never stood for parts; with four sums 1782 x 2048 x 512 took 7.4 us instead of 7.0, 1280 x 1408 x 1600 13.4 instead of 13.1), parts from
-// twelve with two sums (512 x 2048 x 4600 transA, six parts where there were eight) and from sixteen with four.  Any-alignment tiles: parts from seven, whole ones from sixteen (22 of 450 x 64 x 450 6.5 us instead of 6.2), as long as the three workgroups a compute unit
-// then holds, instead of four, are all there are (67 of 919 x 64 x 919, 1005 workgroups, 31.0 us instead of 29.3).
+// Does a launch keep Cfg::DEEP_CHAINS sums per output?  They take 0.1-0.5 us to clear and to add up, and registers.
+// Rings: from 24 k tiles (whole tiles of fewer never stood for parts; with four sums 1782 x 2048 x 512 took 7.4 us instead of 7.0, 1280 x 1408 x
+//   1600 13.4 instead of 13.1), parts from twelve with two sums (512 x 2048 x 4600 transA, six parts where there were eight) and from
+//   sixteen with four.
+// Any-alignment 16-bit 64x64 tiles: parts from seven, whole ones from sixteen (22 of 450 x 64 x 450 6.5 us instead of 6.2), as long as the three
+//   workgroups a compute unit then holds, instead of four, are all there are (67 of 919 x 64 x 919, 1005 workgroups, 31.0 us instead of 29.3).
+//   128x64 tiles: whole ones from 24, one to a unit (56 of 970 x 64 x 970, 448 workgroups, 28.9 us instead of 23.3), which stood for two parts.
+// Any-alignment fp32 64x64 tiles: whole ones that stand for three 64x32 tiles of eight sums to a unit.
 template <typename C, bool SPLIT>
 bool more_sums(const KernelArgs& a, unsigned workgroups) {
   const int depth = (a.K + C::BK - 1) / C::BK / (SPLIT && a.whole == 0 ? a.split : 1);
-  return C::DIRECT ? depth >= (!SPLIT ? 24 : C::DEEP_CHAINS == 2 ? 12 : 16) : depth >= (SPLIT ? 7 : 16) && workgroups <= 3 * 256;
+  if (C::DIRECT) return depth >= (!SPLIT ? 24 : C::DEEP_CHAINS == 2 ? 12 : 16);
+  if (C::ES == 4) return !SPLIT && depth >= 3 && workgroups > 256 && workgroups <= 384;
+  if (C::BM == 128) return !SPLIT && depth >= 24 && workgroups <= 256;
+  return depth >= (SPLIT ? 7 : 16) && workgroups <= 3 * 256;
 }
 
 template <typename C, bool SPLIT = false, bool AHEAD = false, bool MORE_SUMS = false>

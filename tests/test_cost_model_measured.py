@@ -192,15 +192,6 @@ def test_small_fp32_tiles_of_eight_sums_are_ranked_as_measured(M, N, K, ta, tb, 
     assert (s.tile[0][0], s.tile[1][0]) == ((64, 64) if us_64x64 < us_64x32 else (64, 32))
 
 
-def test_parts_of_small_tiles_that_share_a_unit_are_ranked_as_measured():
-    """208 x 152 x 25536 bf16 with a row-major B: 64x64 tiles in sixteen parts 15.2 us, 32x32 ones in twelve (420 parts) 16.3; 128 x 104 x 15680 11.2 and
-    9.2 (256 parts)."""
-    from paper_2502_11407_amd import binding as gs
-    for (M, N, K), tile in (((208, 152, 25536), 64), ((128, 104, 15680), 32)):
-        s = gs.construct(gs.gemm_problem("bf16", M, N, K))
-        assert (s.tile[0][0], s.tile[1][0]) == (tile, tile) and s.split_k == 16
-
-
 @pytest.mark.parametrize("dtype,n,c,h,w,k,r,stride,us", [
     ("bf16", 14, 6, 35, 63, 28, 7, 1, {(32, 256): 8.13, (32, 128): 9.01}), ("f16", 2, 6, 92, 61, 52, 7, 1, {(32, 256): 7.85, (32, 128): 8.70}),
     ("f16", 3, 6, 42, 45, 22, 5, 2, {(32, 256): 5.62, (32, 128): 6.04}), ("f16", 15, 6, 64, 47, 56, 7, 2, {(32, 256): 7.32, (32, 128): 8.30}),

@@ -91,3 +91,24 @@ def test_deep_any_alignment_tiles_keep_four_sums(dtype, ta, tb):
                 print(dtype, ta, tb, "instance", s.kernel_id, "K", K, "split", split, "step", step, flush=True)
                 a, b = _operands(dtype, M, N, K, ta, tb, ((5, 4096.0, 4096.0), (16 * step + 7, 1.0, 1.0), (4 * 64 + 9, 4096.0, -4096.0)))
                 assert (_run(gs, q, s, a, b, M, N, split) == 1.0).all(), (s.kernel_id, K, split, step)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype,bm,sums", [("f16", 128, 2), ("bf16", 128, 2), ("f32", 64, 8)])
+def test_any_alignment_tiles_that_stood_for_parts_or_for_smaller_tiles_keep_several_sums(dtype, bm, sums, ta, tb):
+    """128x64 tiles of 24 k tiles and more: two sums; fp32 64x64 tiles of a shallow k, one to two a compute unit: eight."""
+    from paper_2502_11407_amd import binding as gs
+    fp32 = dtype == "f32"
+    step, bk = (8, 32) if fp32 else (16, 64)
+    p = gs.gemm_problem(dtype, 63, 63, 63, ta, tb)
+    tiles = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances()))
+             if s is not None and s.vec_bytes != 16 and (s.tile[0][0], s.tile[1][0], s.tile[2][0], s.tile[2][1]) == (bm, 64, bk, step)]
+    assert tiles
+    M, N = (64 * 16 + 1, 64 * 16 - 1) if fp32 else (bm + 3, 67)
+    for s in tiles:
+        for K in (bk * 5 - 3, bk * 6) if fp32 else (bk * 23 + 1, bk * 25 - 1):
+            q = gs.gemm_problem(dtype, M, N, K, ta, tb)
+            for k in [step * i + 3 for i in range(1, sums // 2 if fp32 else sums)] + ([bk + 3, bk + 3 * step + 3] if fp32 else []):
+                print(dtype, ta, tb, "instance", s.kernel_id, "K", K, "k", k, flush=True)
+                a, b = _operands(dtype, M, N, K, ta, tb, ((1, 4096.0, 4096.0), (k, 1.0, 1.0), (2 * bk + 2, 4096.0, -4096.0)))
+                assert (_run(gs, q, s, a, b, M, N) == 1.0).all(), (s.kernel_id, K, k)
