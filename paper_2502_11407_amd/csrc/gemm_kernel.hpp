@@ -1353,8 +1353,9 @@ __global__ __launch_bounds__(C::THREADS) void contraction_kernel(const KernelArg
     }
     const bool even = kt + 1 < nk;
     if (even) k_tile(kt++, std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{});
-    // (the last tile requests and deposits nothing: its set only tells the chains apart)
-    if (CHAINS > 1 && even) k_tile(kt, std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
+    // (the last tile requests and deposits nothing: its set only tells the chains apart, which 16x16 fp32 products do by themselves: a copy of
+    // the tile less, 512^3 fp32 6.46 -> 6.29 us)
+    if (CHAINS > 1 && !(ES == 4 && MB == 16) && even) k_tile(kt, std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
     else k_tile(kt, std::integral_constant<int, 0>{}, std::false_type{}, std::false_type{});
   } else if constexpr (PIPE) {
     // Whether a further k tile follows is a compile-time property of the loop body: the last k
