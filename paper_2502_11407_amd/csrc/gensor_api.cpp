@@ -191,7 +191,8 @@ bool instance_serves(const InstanceDesc& d, const GemmView& v) {
   if (d.in_dtype != v.in_dtype || d.out_dtype != v.out_dtype || d.bsrc != v.bsrc || d.asrc != v.asrc) return false;
   if (d.units) return conv_patch_plan(d, v, nullptr);
   if (d.conv_rows()) return conv_rows_plan(d.bm, d.bn, v, nullptr);
-  return true;
+  // the kernels number k, and the requests that run to the end of the last k tile, in 32 bits
+  return v.bsrc == B_CONV || v.K <= INT32_MAX - d.bk + 1;
 }
 
 // Does instance d realise schedule s (same lattice point)?
