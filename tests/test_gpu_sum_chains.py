@@ -112,3 +112,37 @@ def test_any_alignment_tiles_that_stood_for_parts_or_for_smaller_tiles_keep_seve
                 print(dtype, ta, tb, "instance", s.kernel_id, "K", K, "k", k, flush=True)
                 a, b = _operands(dtype, M, N, K, ta, tb, ((1, 4096.0, 4096.0), (k, 1.0, 1.0), (2 * bk + 2, 4096.0, -4096.0)))
                 assert (_run(gs, q, s, a, b, M, N) == 1.0).all(), (s.kernel_id, K, k)
+
+
+def _distance(C, A, B):
+    want = A.double() @ B.double()
+    return ((C.double() - want).norm() / want.norm()).item()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_several_sums_lose_less_than_one(dtype):
+    """Distance from 64 bits at even and odd counts of k tiles, beside a 64x64 tile of a single sum on the same operands.  Rounding a running sum of n
+    terms loses about sqrt(n / 2) roundings, so s sums that are then added up lose 1 / sqrt(s) of that, and the last rounding on top:
+    bounds of 0.75 (eight sums, measured 0.37-0.68), 0.65 (four) and 0.8 (two: 0.67-0.73)."""
+    from paper_2502_11407_amd import binding as gs
+    M = N = 384
+    fp32 = dtype == "f32"
+    for K, tile, bound in ([(64 * n, (32, 32), 0.75) for n in (2, 3, 5, 8)] if fp32 else
+                           [(128 * n, (32, 32), 0.75) for n in (2, 3, 4, 5, 8)] + [(64 * n, (128, 128), 0.65) for n in (24, 25, 40)] +
+                           [(64 * n, (256, 128), 0.8) for n in (24, 25, 40)]):
+        gen = torch.Generator(device="cuda").manual_seed(K)
+        A, B = (torch.empty(s, device="cuda").uniform_(-1, 1, generator=gen).to(TORCH[dtype]) for s in ((M, K), (K, N)))
+        b = B.t().contiguous()
+        p = gs.gemm_problem(dtype, M, N, K, 0, 1)
+        every = [s for s in (gs.instance_schedule(i, p) for i in range(gs.num_instances())) if s is not None and s.vec_bytes == 16]
+        one = next(s for s in every if (s.tile[0][0], s.tile[1][0]) == (64, 64) and s.stages == 2)
+        if tile == (32, 32):
+            several = [s for s in every if (s.tile[0][0], s.tile[1][0]) == tile and s.tile[2][0] == (64 if fp32 else 128) and s.tile[0][1] == 16]
+        else:
+            several = [s for s in every if (s.tile[0][0], s.tile[1][0]) == tile and s.direct_lds and s.stages > 2 and s.tile[2][1] == 32]
+        alone = _distance(_run(gs, p, one, A, b, M, N), A, B)
+        assert several
+        for s in several:
+            d = _distance(_run(gs, p, s, A, b, M, N), A, B)
+            print(dtype, K, "instance", s.kernel_id, "distance %.2e, one sum %.2e: %.2f" % (d, alone, d / alone), flush=True)
+            assert d <= bound * alone, (s.kernel_id, K)
