@@ -60,3 +60,26 @@ def test_row_staged_convolution_does_not_spill(tmp_path):
     assert len(insts) == 12
     for name, regs, spilled in _counts(tmp_path, insts, ("launch_conv_rows<%s>",), kernel_build.CONV_FLAGS):
         assert spilled == 0, (name, regs, spilled)
+
+
+def test_tiles_of_several_sums_do_not_spill(tmp_path):
+    """Rings of 16x16 blocks with 64x64 waves (one workgroup of eight waves a CU: 256 registers) and the any-alignment tiles that keep more sums in
+    deep launches: 64x64 16-bit ones with three workgroups a CU (170 registers), 128x64 and fp32 ones with two."""
+    insts = [d for d in lattice.lattice() if d["dt"] in ("f16", "f32") and d["out"] == "f32" and d["bsrc"] in ("KC", "NC") and not d["units"]]
+    rings = [d for d in insts if d["direct"] and d["stages"] == 3 and d["mb"] == 16]
+    loose = [d for d in insts if d["mb"] == 32 and lattice.chains(d) > 1]
+    assert len(rings) == 8 and len(loose) == 12
+    launches = ("launch_instance<%s>", "launch_instance<%s, true>")
+
+    def one(item):
+        d, extra = item
+        folder = tmp_path / str(d["id"])
+        folder.mkdir()
+        return d, _counts(folder, [d], launches, extra)
+
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        for d, kernels in ex.map(one, [(d, ()) for d in rings] + [(d, kernel_build.CONV_FLAGS) for d in loose]):
+            assert len(kernels) == 4                           # whole and split, each with one sum and with several
+            most = 256 if d in rings or d["dt"] == "f32" or d["bm"] == 128 else 170
+            for name, regs, spilled in kernels:
+                assert regs <= most and spilled == 0, (d["id"], name, regs, spilled)
